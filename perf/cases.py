@@ -13,8 +13,8 @@ Kinds:
   multirate  SpiirMultiRate.filter_block_z: the full-rate sums of a multi-rate bank
   adjoint    SpiirBank.forward_z with its tape, then SpiirBank.backward
   whiten     Whitener.process of the next block (train > 0: the PSD is estimated first)
-  cluster    TriggerClusterer.run and its result
-  pipeline   raw strain: Whitener.process, SpiirBank.trigger_max, TriggerStream.push
+  cluster    TriggerClusterer.run
+  pipeline   raw strain: Whitener.process, SpiirBank.trigger_max, TriggerStream.push_into
 """
 import math
 
@@ -298,7 +298,10 @@ def prepare(case, seed):
     for i in range(0, w, 4096):
         mx, _ = bk.trigger_max(wh.process(xd[i:i + 4096]))
     ts = lib.TriggerStream(float(torch.quantile(mx, 0.99)), case["window"], n)
-    return dict(case=case, bank=bk, wh=wh, ts=ts, x=xd[w:].contiguous())
+    triggers = [torch.zeros(c, device="cuda", dtype=t) for c, t in
+                ((ts.capacity, torch.int64), (ts.capacity, torch.int32), (ts.capacity, torch.float32),
+                 (1, torch.int64))]
+    return dict(case=case, bank=bk, wh=wh, ts=ts, triggers=triggers, x=xd[w:].contiguous())
 
 
 def _prepare_cluster(case, seed, lib):
@@ -313,6 +316,8 @@ def _prepare_cluster(case, seed, lib):
         mx[lo:hi] = torch.maximum(mx[lo:hi], h * torch.exp(-0.5 * (t / float(w)) ** 2).float())
     at = torch.sort(mx).values[min(n - 1, int(case["quantile"] * n))]
     cl = lib.TriggerClusterer(n, n // (case["window"] + 1) + 1)
+    for t in (cl.index, cl.template, cl.snr):
+        t.zero_()
     return dict(case=case, cl=cl, mx=mx, am=am, threshold=float(at))
 
 
@@ -333,12 +338,13 @@ def run(state):
         return state["wh"].process(state["x"], out=state["out"])
     if kind == "cluster":
         c = state["case"]
-        state["cl"].run(state["mx"], state["am"], state["threshold"], c["window"])
-        index, template, snr, total = state["cl"].result()
-        return dict(index=index, template=template, snr=snr, total=total)
+        cl = state["cl"]
+        cl.run(state["mx"], state["am"], state["threshold"], c["window"])
+        return dict(index=cl.index, template=cl.template, snr=cl.snr, total=cl.count)
     white = state["wh"].process(state["x"])
     mx, am = state["bank"].trigger_max(white)
-    index, template, snr, total = state["ts"].push(mx, am)
+    state["ts"].push_into(mx, am, *state["triggers"])
+    index, template, snr, total = state["triggers"]
     return dict(white=white, max=mx, index=index, template=template, snr=snr, total=total)
 
 
