@@ -105,7 +105,7 @@ struct spiir_bank {
     double2 *aL = nullptr, *dL = nullptr, *a64 = nullptr;
     float4 *state = nullptr, *zstate = nullptr;
     RowInfo *rows = nullptr;
-    int tt = 16;
+    int tt = 16;                  // 16: the full pass sums batches of 64 steps, 8: of 8
     float *hist[2] = {nullptr, nullptr};
     int hist_cur = 0;
     uint64_t *keys = nullptr;     // [groups + (split templates ? 1 : 0)][max_block]
@@ -118,14 +118,13 @@ struct spiir_bank {
     int n_split = 0;
     int band = 0;                  // delay band width (0: none); group_lo [groups] on the device
     int32_t *group_lo = nullptr;
-    int nseg = 1;                 // time segments per streaming launch
-    int64_t seg_len_max = 0;
-    size_t lds_carry = 0;
+    int nseg = 1;                 // most time segments per streaming launch
+    bool seg_auto = false;        // the call chooses their number and length (plan_segments)
+    int64_t slots_main = 1, slots_pre = 1;   // resident workgroups of the full / the state pass
+    size_t lds_tile = 0;          // LDS of a full pass whose window stays in global memory
     float4 *seg_end = nullptr, *seg_start = nullptr;
-    float2 *zl = nullptr;
-    // per-template comparator: segment states [pl_cap][one workgroup's slots], local z [pl_cap - 1][T][L]
+    // per-template comparator: segment states [pl_cap][one workgroup's slots]
     float4 *pl_seg_end = nullptr, *pl_seg_start = nullptr;
-    float2 *pl_zl = nullptr;
     int pl_cap = 0;
     int tsplit_opt = 0;           // opts.time_split as given (the adjoint honours it too)
     // adjoint scratch, grown on demand: (lambda, nu) pairs [2][cap][S], gpart [cap][2][S]
@@ -148,6 +147,7 @@ struct spiir_bank {
         p.dmax = dmax;
         p.L = L;
         p.nb = nb;
+        p.sumb = layout::sum_batch(tt);
         p.prec = prec;
         p.wpg = lay.wpg;
         p.only_tpl = -1;
@@ -164,7 +164,6 @@ struct spiir_bank {
         p.ld_part = max_block;
         p.band_w = band ? band - 1 : dmax;
         p.group_lo = band ? group_lo : nullptr;
-        p.zl = zl;
         return p;
     }
 };
@@ -182,7 +181,7 @@ struct spiir_tape {
 
 struct spiir_batch {
     int device = 0;
-    int ns = 0, B = 0, fl = 1, tt = 16, wpg = 1, grid = 0, nitems = 0;
+    int ns = 0, B = 0, fl = 1, wpg = 1, grid = 0, nitems = 0;
     size_t lds = 0;
     std::vector<spiir_bank *> banks;
     std::vector<int64_t> len;
@@ -198,9 +197,8 @@ struct spiir_batch {
     // sgraph[k - 1]: the k longest streams live (streams end in order of length)
     std::vector<hipGraph_t> sgraph;
     std::vector<hipGraphExec_t> sexec;
-    int2 *seg_items = nullptr, *carry_items = nullptr;
+    int2 *pre_items = nullptr, *seg_items = nullptr;
     std::vector<float4 *> seg_bufs;
-    std::vector<float2 *> zl_bufs;
     std::vector<int> groups;
     int64_t slots_dev = 0;   // resident workgroups on the device
     int split_mode = 0;      // 0 auto, 1 never, 2 always
@@ -208,6 +206,52 @@ struct spiir_batch {
 };
 
 namespace {
+
+// Segments of one time-split launch over n samples (nseg = 1: no split).
+struct SegPlan {
+    int nseg = 1;
+    int64_t len = 0;
+};
+
+// A forced split (opts.time_split) cuts whole chunks. The automatic one takes
+// the number of segments, of whole kSegGrain samples, that needs the least
+// time by this count, in steps of the full pass: a round of resident
+// workgroups takes its segment's steps plus the window fill and start-up
+// (`fixed`), a state-pass round about 0.4 of the steps plus the same. Small
+// banks end up with segments as short as the fixed part allows, banks near
+// the device's size with whole rounds.
+constexpr int64_t kSegGrain = 64;
+
+SegPlan plan_segments(const spiir_bank *bk, int64_t n, int max_seg) {
+    SegPlan best;
+    best.len = n;
+    if (max_seg < 2 || n < 2) return best;
+    if (!bk->seg_auto) {
+        best.len = ((n + max_seg - 1) / max_seg + bk->L - 1) / bk->L * bk->L;
+        best.nseg = (int)((n + best.len - 1) / best.len);
+        return best;
+    }
+    const int64_t win = bk->xlds ? (bk->band ? bk->band : bk->dmax) : 0;
+    const int64_t G = bk->lay.groups;
+    double cost = 0.0;
+    for (int want = 1; want <= max_seg; ++want) {
+        SegPlan p;
+        p.len = ((n + want - 1) / want + kSegGrain - 1) / kSegGrain * kSegGrain;
+        p.nseg = (int)((n + p.len - 1) / p.len);
+        if (want > 1 && p.nseg == best.nseg) continue;
+        if (p.nseg == 1) p.len = n;
+        const double fixed = 24.0 + (double)(win + p.len) / 512.0;
+        const double rm = (double)((G * p.nseg + bk->slots_main - 1) / bk->slots_main);
+        const double rp = (double)((G * (p.nseg - 1) + bk->slots_pre - 1) / bk->slots_pre);
+        const double c = rm * ((double)p.len + fixed) + rp * (0.4 * (double)p.len + fixed) +
+                         (p.nseg > 1 ? 40.0 + p.nseg : 0.0);
+        if (want == 1 || c < cost) {
+            cost = c;
+            best = p;
+        }
+    }
+    return best;
+}
 
 // Slot arrays on the host, then uploaded.
 int upload_coeffs(spiir_bank *bk) {
@@ -219,8 +263,9 @@ int upload_coeffs(spiir_bank *bk) {
     HIPCHK(hipMemcpy(bk->xoff, h.xoff.data(), S * sizeof(int32_t), hipMemcpyHostToDevice));
     HIPCHK(hipMemcpy(bk->flags, h.flags.data(), S * sizeof(int32_t), hipMemcpyHostToDevice));
     HIPCHK(hipMemcpy(bk->aL, h.aL.data(), S * sizeof(double2), hipMemcpyHostToDevice));
-    HIPCHK(hipMemcpy(bk->dL, h.dL.data(), S * sizeof(double2), hipMemcpyHostToDevice));
     HIPCHK(hipMemcpy(bk->a64, h.a64.data(), S * sizeof(double2), hipMemcpyHostToDevice));
+    HIPCHK(launch_chunk_drift(bk->a64, bk->b32, S, bk->L, bk->dL, nullptr));
+    HIPCHK(hipStreamSynchronize(nullptr));
     return SPIIR_OK;
 }
 
@@ -268,8 +313,8 @@ void free_bank_buffers(spiir_bank *bk) {
     dfree(bk->aL); dfree(bk->dL); dfree(bk->a64); dfree(bk->state); dfree(bk->zstate);
     dfree(bk->rows); dfree(bk->hist[0]); dfree(bk->hist[1]); dfree(bk->keys); dfree(bk->xwin);
     dfree(bk->zpart); dfree(bk->split_tpl); dfree(bk->split_off); dfree(bk->group_lo);
-    dfree(bk->bpair); dfree(bk->bgpart); dfree(bk->seg_end); dfree(bk->seg_start); dfree(bk->zl);
-    dfree(bk->pl_seg_end); dfree(bk->pl_seg_start); dfree(bk->pl_zl);
+    dfree(bk->bpair); dfree(bk->bgpart); dfree(bk->seg_end); dfree(bk->seg_start);
+    dfree(bk->pl_seg_end); dfree(bk->pl_seg_start);
     bk->pl_cap = 0;
 }
 
@@ -302,11 +347,9 @@ int scratch_setup(int dev, unsigned char **out) {
     return SPIIR_OK;
 }
 
-// seg_cap: most time segments the automatic time split may choose (8 for
-// banks created through the ABI; the multi-rate object allows more for its
-// small levels, whose calls are short serial recursions).
+// seg_cap: most time segments the automatic time split may choose.
 int create_bank(spiir_bank **out, int32_t T, const int64_t *off, const double *a, const double *b,
-                const int32_t *d, const spiir_bank_opts &o, int seg_cap = 8) {
+                const int32_t *d, const spiir_bank_opts &o, int seg_cap = 64) {
     int dmax = 0;
     int rc = check_bank_args(T, off, a, b, d, o, dmax);
     if (rc) return rc;
@@ -351,12 +394,12 @@ int create_bank(spiir_bank **out, int32_t T, const int64_t *off, const double *a
     // rule's 2 filters per lane, one template per workgroup and 8 segments.
     bool seg_layout = false;
     if (!global_window && !band && o.filters_per_lane == 0 && o.waves_per_group == 0 && o.time_split == 0 &&
-        max_block >= 8192 && off[T] > 128 * (int64_t)df.n_cu) {
+        max_block >= 2048 && off[T] > 128 * (int64_t)df.n_cu) {
         const Plan p4 = plan_rows(T, off, 4);
         const Plan pw = plan_rows(T, off, choose_fl(T, off, df.n_cu));
         seg_layout = p4.max_nr <= 4 * kMaxWaves && (pw.total_rows + 3) / 4 < (int64_t)7 * df.n_cu;
     }
-    if (seg_layout) seg_cap = std::max(seg_cap, 16);
+    if (seg_layout) seg_cap = std::min(seg_cap, 16);
     int fl = o.filters_per_lane;
     if (fl == 0 && seg_layout) fl = 4;
     if (fl == 0) {
@@ -376,7 +419,7 @@ int create_bank(spiir_bank **out, int32_t T, const int64_t *off, const double *a
         wpg = w0;
         for (int w = w0; w <= kMaxWaves; ++w) {
             const Geometry gm = plan_geometry(w, win_delay, L, nb_cap, df.lds_cap);
-            const int occ = std::max(1, forward_occupancy(fl, gm.tt, w, gm.lds));
+            const int occ = std::max(1, forward_occupancy(fl, w, gm.lds));
             Layout trial;
             if (build_layout(T, off, d, fl, w, band, trial)) continue;
             wpg = w;
@@ -413,24 +456,29 @@ int create_bank(spiir_bank **out, int32_t T, const int64_t *off, const double *a
     bk->xlds = gm.xlds;
     bk->nb = gm.nb;
     bk->lds = gm.lds;
-    bk->lds_carry = fwd_lds_bytes(wpg, 0, 0, false, gm.tt);
+    bk->lds_tile = fwd_lds_bytes(wpg, 0, 0, false, gm.tt);
     bk->tsplit_opt = o.time_split;
     // time split: only when the bank's workgroups fill at most half the device
-    if (o.time_split != 1) {
-        if (o.time_split >= 2) {
-            bk->nseg = o.time_split;
-        } else {
-            const int occ = std::max(1, forward_occupancy(fl, gm.tt, wpg, gm.lds));
-            const int64_t slots_dev = (int64_t)df.n_cu * occ;
-            // segments oversubscribe the resident workgroup slots twice: on the
-            // 64 x 1,000-filter precision bank (64 groups, one resident per CU)
-            // 8 segments ran 23% faster than 4, and 16 or 32 no faster than 8
-            if (2 * (int64_t)bk->lay.groups <= slots_dev)
-                bk->nseg = (int)std::min<int64_t>(seg_cap, 2 * slots_dev / std::max(1, bk->lay.groups));
-        }
-        bk->nseg = std::min(bk->nseg, std::max(1, max_block / L));
+    bk->slots_main = (int64_t)df.n_cu * std::max(1, forward_occupancy(fl, wpg, gm.lds));
+    if (o.time_split == 0 && !band && 2 * (int64_t)bk->lay.groups <= bk->slots_main) {
+        // its segments are short: a window of 2,048 samples beside the delays lets more
+        // workgroups share a compute unit than one of max_block samples
+        const Geometry gs = plan_geometry(wpg, dmax, L, std::min(max_block, std::max(L, 2048 / L * L)), df.lds_cap);
+        bk->tt = gs.tt;
+        bk->xlds = gs.xlds;
+        bk->nb = gs.nb;
+        bk->lds = gs.lds;
+        bk->slots_main = (int64_t)df.n_cu * std::max(1, forward_occupancy(fl, wpg, gs.lds));
     }
-    if (bk->nseg > 1) bk->seg_len_max = ((max_block + bk->nseg - 1) / bk->nseg + L - 1) / L * L;
+    bk->slots_pre = (int64_t)df.n_cu * std::max(1, state_occupancy(fl, wpg, bk->base_args(), bk->xlds));
+    if (o.time_split >= 2) {
+        bk->nseg = std::min<int>(o.time_split, std::max(1, max_block / L));
+    } else if (o.time_split == 0) {
+        bk->seg_auto = true;
+        if (2 * (int64_t)bk->lay.groups <= bk->slots_main)
+            bk->nseg = (int)std::min<int64_t>(seg_cap, 2 * bk->slots_main / std::max(1, bk->lay.groups));
+        bk->nseg = (int)std::min<int64_t>(bk->nseg, std::max<int64_t>(1, max_block / std::min<int64_t>(L, kSegGrain)));
+    }
 
     const int64_t S = bk->lay.nslots;
     const int G = bk->lay.groups;
@@ -451,7 +499,6 @@ int create_bank(spiir_bank **out, int32_t T, const int64_t *off, const double *a
     if (bk->nseg > 1) {
         A(dalloc(&bk->seg_end, (size_t)bk->nseg * S));
         A(dalloc(&bk->seg_start, (size_t)bk->nseg * S));
-        A(dalloc(&bk->zl, (size_t)(bk->nseg - 1) * T * bk->seg_len_max));
     }
     if (e != hipSuccess) {
         free_bank_buffers(bk);
@@ -490,8 +537,6 @@ int create_bank(spiir_bank **out, int32_t T, const int64_t *off, const double *a
         if (e == hipSuccess && bk->n_split)
             e = hipMemcpy(bk->split_off, bk->lay.split_off.data(), bk->lay.split_off.size() * sizeof(int32_t),
                           hipMemcpyHostToDevice);
-        if (e == hipSuccess && bk->nseg > 1) e = hipMemset(bk->seg_end, 0, (size_t)bk->nseg * S * sizeof(float4));
-        if (e == hipSuccess && bk->nseg > 1) e = hipMemset(bk->seg_start, 0, (size_t)bk->nseg * S * sizeof(float4));
         if (e == hipSuccess && dmax > 0) e = hipMemset(bk->hist[0], 0, (size_t)dmax * sizeof(float));
         if (e == hipSuccess && dmax > 0) e = hipMemset(bk->hist[1], 0, (size_t)dmax * sizeof(float));
         if (e == hipSuccess) e = hipDeviceSynchronize();
@@ -525,7 +570,6 @@ struct CallScratch {
     int64_t keys_ld = 0;
     int nseg = 0;   // time segments per launch for this call (0: the bank's)
     float4 *seg_end = nullptr, *seg_start = nullptr;
-    float2 *zl = nullptr;
     float *xwin = nullptr;
 };
 
@@ -555,7 +599,6 @@ int stream_call(spiir_bank *bk, const float *x, int64_t n, int mode, float *snr,
         if (cs) {
             a.seg_end = cs->seg_end;
             a.seg_start = cs->seg_start;
-            a.zl = cs->zl;
         }
         a.state = bk->state;
         a.x = x;
@@ -574,12 +617,9 @@ int stream_call(spiir_bank *bk, const float *x, int64_t n, int mode, float *snr,
             a.keys = keys;
             a.ld = keys_ld;
         }
-        int nseg = 1;
-        const int bn = (cs && cs->nseg > 0) ? cs->nseg : bk->nseg;
-        if (bn > 1) {
-            a.seg_len = ((np + bn - 1) / bn + bk->L - 1) / bk->L * bk->L;
-            nseg = (int)((np + a.seg_len - 1) / a.seg_len);
-        }
+        const SegPlan sp = plan_segments(bk, np, (cs && cs->nseg > 0) ? cs->nseg : bk->nseg);
+        const int nseg = sp.nseg;
+        a.seg_len = sp.len;
         // the next call's history is written by a launch that follows every
         // strain read of this call or by the last reading launch itself (it
         // goes to the other history buffer): the last key finalisation, else
@@ -593,10 +633,9 @@ int stream_call(spiir_bank *bk, const float *x, int64_t n, int mode, float *snr,
         KernelEvents ev;
         HIPCHK(timer_next(bk, &ev));
         if (nseg >= 2)
-            HIPCHK(launch_forward_split(a, mode, bk->lay.fl, bk->tt, bk->xlds, nseg, bk->lds, bk->lds_carry,
-                                        bk->slot_filter, st, ev));
+            HIPCHK(launch_forward_split(a, mode, bk->lay.fl, bk->xlds, nseg, bk->lds, st, ev));
         else
-            HIPCHK(launch_forward(a, mode, bk->lay.fl, bk->tt, bk->xlds, bk->lay.groups, bk->lds, st, ev));
+            HIPCHK(launch_forward(a, mode, bk->lay.fl, bk->xlds, bk->lay.groups, bk->lds, st, ev));
         if (bk->n_split)   // split templates: their parts' sums, then their SNR / z / keys
             HIPCHK(launch_combine_parts(bk->zpart, bk->max_block, bk->split_tpl, bk->split_off, bk->n_split, np,
                                         mode, a.snr, a.z, a.ld, a.obase, keys + (int64_t)bk->lay.groups * keys_ld,
@@ -634,11 +673,10 @@ bool banks_multi_ok(spiir_bank *const *bks, int nb, const int64_t *n) {
     for (int b = 0; b < nb; ++b) {
         const spiir_bank *bk = bks[b];
         if (!bk || !bk->xlds || bk->n_split || bk->nseg < 2 || !bk->tev0.empty()) return false;
-        if (bk->device != b0->device || bk->lay.fl != b0->lay.fl || bk->tt != b0->tt || bk->lay.wpg != b0->lay.wpg)
+        if (bk->device != b0->device || bk->lay.fl != b0->lay.fl || bk->lay.wpg != b0->lay.wpg)
             return false;
         if (n[b] <= 0 || n[b] > bk->max_block) return false;
-        const int64_t seg_len = ((n[b] + bk->nseg - 1) / bk->nseg + bk->L - 1) / bk->L * bk->L;
-        if (n[b] <= seg_len) return false;   // one segment: the call would not be time-split
+        if (plan_segments(bk, n[b], bk->nseg).nseg < 2) return false;   // the call would not be time-split
     }
     return true;
 }
@@ -650,7 +688,7 @@ int banks_stream_z_multi(spiir_bank *const *bks, int nb, const float *const *x, 
     MultiFwd m;
     std::memset(&m, 0, sizeof m);
     m.count = nb;
-    size_t lds = 0, lds_carry = 0;
+    size_t lds = 0;
     for (int b = 0; b < nb; ++b) {
         spiir_bank *bk = bks[b];
         const float *hist = bk->hist[bk->hist_cur];
@@ -665,21 +703,21 @@ int banks_stream_z_multi(spiir_bank *const *bks, int nb, const float *const *x, 
         a.obase = 0;
         a.z = reinterpret_cast<float2 *>(z[b]);
         a.ld = ld[b];
-        a.seg_len = ((n[b] + bk->nseg - 1) / bk->nseg + bk->L - 1) / bk->L * bk->L;
+        const SegPlan sp = plan_segments(bk, n[b], bk->nseg);
+        a.seg_len = sp.len;
         a.hist_next = HistCopy{hist, bk->hist[bk->hist_cur ^ 1], x[b], n[b], bk->dmax};
-        const int nseg = (int)((n[b] + a.seg_len - 1) / a.seg_len);
-        const int cb = (int)((a.seg_stride + 255) / 256);
+        const int nseg = sp.nseg;
+        const int cb = (int)((a.seg_stride + 63) / 64);
         const int hb = bk->dmax > 0 ? (bk->dmax + 255) / 256 : 0;
         m.a[b] = a;
         m.nseg[b] = nseg;
         m.chain_blocks[b] = cb;
-        m.seg_first[b + 1] = m.seg_first[b] + bk->lay.groups * nseg;
+        m.pre_first[b + 1] = m.pre_first[b] + bk->lay.groups * (nseg - 1);
         m.chain_first[b + 1] = m.chain_first[b] + cb + hb;
-        m.carry_first[b + 1] = m.carry_first[b] + bk->lay.groups * (nseg - 1);
+        m.seg_first[b + 1] = m.seg_first[b] + bk->lay.groups * nseg;
         lds = std::max(lds, bk->lds);
-        lds_carry = std::max(lds_carry, bk->lds_carry);
     }
-    HIPCHK(launch_forward_split_multi(m, bks[0]->lay.fl, bks[0]->tt, bks[0]->lay.wpg, lds, lds_carry, st));
+    HIPCHK(launch_forward_split_multi(m, bks[0]->lay.fl, bks[0]->lay.wpg, lds, st));
     for (int b = 0; b < nb; ++b) bks[b]->hist_cur ^= 1;
     return SPIIR_OK;
 }
@@ -968,10 +1006,8 @@ size_t plan_scratch(const spiir_bank *bk, int64_t n, int nseg, unsigned char *sc
         take((size_t)(bk->lay.groups + (bk->n_split ? 1 : 0)) * keys_ld * sizeof(uint64_t)));
     const size_t seg_bytes = (size_t)nseg * bk->lay.nslots * sizeof(float4);
     if (nseg > 1) {
-        const int64_t seg_len = ((keys_ld + nseg - 1) / nseg + bk->L - 1) / bk->L * bk->L;
         cs.seg_end = reinterpret_cast<float4 *>(take(seg_bytes));
         cs.seg_start = reinterpret_cast<float4 *>(take(seg_bytes));
-        cs.zl = reinterpret_cast<float2 *>(take((size_t)(nseg - 1) * bk->T * seg_len * sizeof(float2)));
     }
     if (!bk->xlds) cs.xwin = reinterpret_cast<float *>(take((size_t)(n + bk->dmax + 16) * sizeof(float)));
     return at;
@@ -1000,14 +1036,7 @@ int spiir_trigger_max_noalloc(spiir_bank *bk, const float *x, int64_t n, float *
     const int rc = scratch_setup(bk->device, &scr);   // the address looked up when the bank was created
     if (rc) return rc;
     plan_scratch(bk, n, nseg, scr, cs);
-    hipStream_t st = as_stream(stream);
-    if (nseg > 1) {
-        // slots outside every template are chained from these buffers; start them at zero as the bank's own
-        const size_t seg_bytes = (size_t)nseg * bk->lay.nslots * sizeof(float4);
-        HIPCHK(launch_fill_zero(cs.seg_end, seg_bytes, st));
-        HIPCHK(launch_fill_zero(cs.seg_start, seg_bytes, st));
-    }
-    return stream_call(bk, x, n, kModeKeys, nullptr, 0, mx, am, st, &cs);
+    return stream_call(bk, x, n, kModeKeys, nullptr, 0, mx, am, as_stream(stream), &cs);
 }
 
 int spiir_trigger_max_per_template(spiir_bank *bk, const float *x, int64_t n, float *mx, int32_t *am,
@@ -1039,17 +1068,12 @@ int spiir_trigger_max_per_template(spiir_bank *bk, const float *x, int64_t n, fl
         HIPCHK(hipDeviceSynchronize());
         dfree(bk->pl_seg_end);
         dfree(bk->pl_seg_start);
-        dfree(bk->pl_zl);
         bk->pl_cap = 0;
         hipError_t e = dalloc(&bk->pl_seg_end, (size_t)nseg_max * gslots);
         if (e == hipSuccess) e = dalloc(&bk->pl_seg_start, (size_t)nseg_max * gslots);
-        if (e == hipSuccess) e = dalloc(&bk->pl_zl, (size_t)(nseg_max - 1) * bk->T * L);
-        if (e == hipSuccess) e = launch_fill_zero(bk->pl_seg_end, (size_t)nseg_max * gslots * sizeof(float4), st);
-        if (e == hipSuccess) e = launch_fill_zero(bk->pl_seg_start, (size_t)nseg_max * gslots * sizeof(float4), st);
         if (e != hipSuccess) {
             dfree(bk->pl_seg_end);
             dfree(bk->pl_seg_start);
-            dfree(bk->pl_zl);
             return fail(SPIIR_ENOMEM, "per-template scratch allocation failed: %s", hipGetErrorString(e));
         }
         bk->pl_cap = nseg_max;
@@ -1075,13 +1099,11 @@ int spiir_trigger_max_per_template(spiir_bank *bk, const float *x, int64_t n, fl
                 a.seg_len = L;
                 a.seg_end = bk->pl_seg_end;
                 a.seg_start = bk->pl_seg_start;
-                a.zl = bk->pl_zl;
                 a.seg_slot0 = (int64_t)a.gbase * gslots;
                 a.seg_stride = gslots;
-                HIPCHK(launch_forward_split(a, kModeSnr, bk->lay.fl, bk->tt, false, nseg, bk->lds_carry, bk->lds_carry,
-                                            bk->slot_filter, st, KernelEvents()));
+                HIPCHK(launch_forward_split(a, kModeSnr, bk->lay.fl, false, nseg, bk->lds_tile, st));
             } else {
-                HIPCHK(launch_forward(a, kModeSnr, bk->lay.fl, bk->tt, false, 1, bk->lds_carry, st));
+                HIPCHK(launch_forward(a, kModeSnr, bk->lay.fl, false, 1, bk->lds_tile, st));
             }
         }
     }
@@ -1132,19 +1154,16 @@ int spiir_forward_z(spiir_bank *bk, const float *x, int64_t n, float *z, spiir_t
         a.obase = P;
         a.z = reinterpret_cast<float2 *>(z);
         a.ld = n;
-        int nseg = 1;
-        if (bk->nseg > 1) {
-            a.seg_len = ((np + bk->nseg - 1) / bk->nseg + bk->L - 1) / bk->L * bk->L;
-            nseg = (int)((np + a.seg_len - 1) / a.seg_len);
-        }
+        const SegPlan sp = plan_segments(bk, np, bk->nseg);
+        const int nseg = sp.nseg;
+        a.seg_len = sp.len;
         KernelEvents ev;
         e = timer_next(bk, &ev);
         if (e != hipSuccess) break;
         if (nseg >= 2)
-            e = launch_forward_split(a, kModeZ, bk->lay.fl, bk->tt, bk->xlds, nseg, bk->lds, bk->lds_carry,
-                                     bk->slot_filter, st, ev);
+            e = launch_forward_split(a, kModeZ, bk->lay.fl, bk->xlds, nseg, bk->lds, st, ev);
         else
-            e = launch_forward(a, kModeZ, bk->lay.fl, bk->tt, bk->xlds, bk->lay.groups, bk->lds, st, ev);
+            e = launch_forward(a, kModeZ, bk->lay.fl, bk->xlds, bk->lay.groups, bk->lds, st, ev);
         if (e == hipSuccess && bk->n_split)
             e = launch_combine_parts(bk->zpart, bk->max_block, bk->split_tpl, bk->split_off, bk->n_split, np, kModeZ,
                                      nullptr, a.z, a.ld, a.obase, nullptr, st);
@@ -1267,7 +1286,6 @@ int spiir_batch_create(spiir_batch **out, int32_t ns, spiir_bank *const *banks, 
     bt->B = B;
     bt->fl = banks[0]->lay.fl;
     bt->wpg = banks[0]->lay.wpg;
-    bt->tt = banks[0]->tt;
     bt->banks.assign(banks, banks + ns);
     bt->len.assign(lengths, lengths + ns);
     int max_groups = 0;
@@ -1316,7 +1334,7 @@ int spiir_batch_create(spiir_batch **out, int32_t ns, spiir_bank *const *banks, 
         A(hipMemset(bt->counter, 0, sizeof(int)));
         A(hipMemset(bt->pos, 0, ns * sizeof(int64_t)));
     }
-    const int occ = std::max(1, batch_occupancy(bt->fl, bt->tt, bt->wpg, bt->lds));
+    const int occ = std::max(1, batch_occupancy(bt->fl, bt->wpg, bt->lds));
     bt->grid = std::min(bt->nitems, banks[0]->dev.n_cu * occ);
     bt->slots_dev = (int64_t)banks[0]->dev.n_cu * occ;
     // time-split plan per stream: segments of whole chunks, enough to fill the
@@ -1326,8 +1344,8 @@ int spiir_batch_create(spiir_batch **out, int32_t ns, spiir_bank *const *banks, 
     std::vector<int> order(ns);
     for (int s = 0; s < ns; ++s) order[s] = s;
     std::stable_sort(order.begin(), order.end(), [&](int p, int q) { return lengths[p] > lengths[q]; });
-    std::vector<int2> si, ci;
-    std::vector<int> sp(ns + 1, 0), cp(ns + 1, 0);   // prefix item counts over `order`
+    std::vector<int2> pi, si;                        // state pass, full pass
+    std::vector<int> pp(ns + 1, 0), sp(ns + 1, 0);   // prefix item counts over `order`
     int64_t max_slots = 0;
     bool any_split = false;
     for (int s = 0; s < ns; ++s) bt->groups.push_back(banks[s]->lay.groups);
@@ -1343,18 +1361,14 @@ int spiir_batch_create(spiir_batch **out, int32_t ns, spiir_bank *const *banks, 
         const int nseg = (int)((B + seg_len - 1) / seg_len);
         hs[s].args.seg_len = seg_len;
         any_split = any_split || nseg >= 2;
-        // every stream takes part in the split step (a single segment needs only its end state)
+        // every stream takes part in the split step (a single segment has no state pass)
         float4 *se = nullptr, *ss = nullptr;
-        float2 *zl = nullptr;
         A(dalloc(&se, (size_t)nseg * bk->lay.nslots));
         A(dalloc(&ss, (size_t)nseg * bk->lay.nslots));
-        if (nseg >= 2) A(dalloc(&zl, (size_t)(nseg - 1) * bk->T * seg_len));
         bt->seg_bufs.push_back(se);
         bt->seg_bufs.push_back(ss);
-        if (zl) bt->zl_bufs.push_back(zl);
         hs[s].args.seg_end = se;
         hs[s].args.seg_start = ss;
-        hs[s].args.zl = zl;
         // this stream's items, largest workgroups first
         std::vector<int64_t> gf(bk->lay.groups, 0);
         for (int j = 0; j < bk->T; ++j) gf[bk->lay.tpl_group[j]] += bk->off[j + 1] - bk->off[j];
@@ -1364,21 +1378,21 @@ int spiir_batch_create(spiir_batch **out, int32_t ns, spiir_bank *const *banks, 
         for (int k = 0; k < nseg; ++k)
             for (int g : gord) {
                 si.push_back(make_int2(s, (g << 4) | k));
-                if (k > 0) ci.push_back(make_int2(s, (g << 4) | k));
+                if (k + 1 < nseg) pi.push_back(make_int2(s, (g << 4) | k));
             }
+        pp[oi + 1] = (int)pi.size();
         sp[oi + 1] = (int)si.size();
-        cp[oi + 1] = (int)ci.size();
     }
     if (!any_split) {
+        pi.clear();
         si.clear();
-        ci.clear();
     }
     if (!si.empty() && e == hipSuccess) {
         A(dalloc(&bt->seg_items, si.size()));
-        A(dalloc(&bt->carry_items, std::max<size_t>(1, ci.size())));
+        A(dalloc(&bt->pre_items, std::max<size_t>(1, pi.size())));
         if (e == hipSuccess) A(hipMemcpy(bt->seg_items, si.data(), si.size() * sizeof(int2), hipMemcpyHostToDevice));
-        if (e == hipSuccess && !ci.empty())
-            A(hipMemcpy(bt->carry_items, ci.data(), ci.size() * sizeof(int2), hipMemcpyHostToDevice));
+        if (e == hipSuccess && !pi.empty())
+            A(hipMemcpy(bt->pre_items, pi.data(), pi.size() * sizeof(int2), hipMemcpyHostToDevice));
     }
     // segment plans are part of the stream descriptors
     if (e == hipSuccess) A(hipMemcpy(bt->streams, hs.data(), ns * sizeof(BatchStream), hipMemcpyHostToDevice));
@@ -1387,7 +1401,7 @@ int spiir_batch_create(spiir_batch **out, int32_t ns, spiir_bank *const *banks, 
     if (e == hipSuccess) {
         A(hipStreamBeginCapture(cap, hipStreamCaptureModeThreadLocal));
         if (e == hipSuccess) {
-            A(launch_batch(bt->streams, bt->items, bt->nitems, bt->counter, bt->pos, B, bt->fl, bt->tt,
+            A(launch_batch(bt->streams, bt->items, bt->nitems, bt->counter, bt->pos, B, bt->fl,
                            bt->grid, bt->wpg, bt->lds, cap));
             A(launch_batch_finalize(bt->streams, ns, bt->keys, bt->key_stride, bt->pos, B, max_groups, cap));
             A(launch_batch_advance(bt->pos, bt->streams, ns, bt->counter, B, cap));
@@ -1399,11 +1413,10 @@ int spiir_batch_create(spiir_batch **out, int32_t ns, spiir_bank *const *banks, 
         if (e == hipSuccess) A(hipGraphInstantiate(&bt->exec, bt->graph, nullptr, nullptr, 0));
     }
     for (int k = 1; k <= ns && e == hipSuccess && !si.empty(); ++k) {
-        const size_t lds_carry = fwd_lds_bytes(bt->wpg, 0, 0, false, bt->tt);
         A(hipStreamBeginCapture(cap, hipStreamCaptureModeThreadLocal));
         if (e == hipSuccess) {
-            A(launch_batch_split(bt->streams, bt->seg_items, sp[k], bt->carry_items, cp[k], bt->pos, B, ns,
-                                 max_slots, bt->fl, bt->tt, bt->wpg, bt->lds, lds_carry, cap));
+            A(launch_batch_split(bt->streams, bt->pre_items, pp[k], bt->seg_items, sp[k], bt->pos, B, ns,
+                             max_slots, bt->fl, bt->wpg, bt->lds, cap));
             A(launch_batch_finalize(bt->streams, ns, bt->keys, bt->key_stride, bt->pos, B, max_groups, cap));
             A(launch_batch_advance(bt->pos, bt->streams, ns, bt->counter, B, cap));
             hipGraph_t g = nullptr;
@@ -1487,9 +1500,8 @@ int spiir_batch_destroy(spiir_batch *bt) {
         for (auto g : bt->sgraph)
             if (g) (void)hipGraphDestroy(g);
         dfree(bt->seg_items);
-        dfree(bt->carry_items);
+        dfree(bt->pre_items);
         for (auto &p : bt->seg_bufs) dfree(p);
-        for (auto &p : bt->zl_bufs) dfree(p);
         dfree(bt->streams);
         dfree(bt->items);
         dfree(bt->counter);

@@ -6,13 +6,14 @@
 // iterations, the strain window shared by all filters is staged once per
 // workgroup, and the per-template sum of filter outputs is a parallel
 // reduction. The MI355X mapping:
-//   * one workgroup = up to 16 waves = a packed set of whole templates;
+//   * one workgroup = up to 8 waves = a packed set of whole templates;
 //     every lane holds FL filters of one template in registers;
 //   * the delayed strain window x[m - d] of a whole block lives in LDS and is
 //     read with immediate offsets (no address arithmetic in the hot loop);
+//   * the recursion runs in blocks of 4 steps in a frame that does not rotate;
 //   * the template sum is done per tile of 8 time steps: an in-lane sum over
-//     the lane's FL filters, a wave-local LDS transpose + 8-lane butterfly,
-//     and a cross-wave sum by the template's first wave after one barrier;
+//     the lane's FL filters and a wave-local LDS transpose into sums of 16-lane
+//     rows, which all waves add up per template once per 64 steps;
 //   * every L samples each filter's carried state gets its FP64 correction
 //     (chunked time scan: the chunk-end state is a^L times the chunk-start
 //     state plus the in-chunk response);
@@ -40,12 +41,6 @@ __device__ __forceinline__ double2 cpow64(double2 a, int e) {
     return r;
 }
 
-// LDS writes by one lane become visible to reads by other lanes of the same wave.
-__device__ __forceinline__ void wave_lds_sync() {
-    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-    __builtin_amdgcn_wave_barrier();
-}
-
 __device__ __forceinline__ float dpp_swap_pairs(float v) {
     // quad_perm [1,0,3,2]: the value of lane ^ 1
     return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), 0xB1, 0xF, 0xF, false));
@@ -58,12 +53,68 @@ __device__ __forceinline__ int64_t slot_index(int g, int wpg, int wave, int f, i
 // Four floats at a 4-byte aligned address (global loads accept this alignment).
 typedef float f4u __attribute__((ext_vector_type(4), aligned(4)));
 
-// Per-lane register state of FL filter slots.
+// The recursion y[t] = a y[t-1] + b x[t] in blocks of kRot steps. Inside a
+// block the state is kept in a frame that does not rotate: S is y scaled to
+// the block's last step, so each input is only added,
+//     S <- S + c_j x[j],  c_j = a^(3-j) b     (the block's first step also
+//     S <- a^4 S),        y[j] = v_j S,  v_j = a^-(3-j)  (v_3 = 1),
+// and the template sum takes v_j S by multiply-adds into the sum. Per update
+// that is 6.5 VALU operations with the in-lane sum, against 8 for turning y by
+// a every step and adding it (the kernels are bound by VALU issue); the carried
+// state also meets one rounded power a^4 per four steps instead of four rounded
+// a. On the 1,024-template bank: see the forward kernel's comment.
+constexpr int kRot = 4;
+// Below this |a| the inverse powers could leave the FP32 range for small
+// inputs (|v_0| = |a|^-3; a = 0 is allowed): a wave that holds such a filter
+// runs the plain recursion for all of its filters.
+constexpr double kRotMin = 0.1;
+
+struct RotCoeffs {
+    float2 a4, c[kRot], v[kRot - 1];
+};
+
+__device__ __forceinline__ float2 f32c(double2 z) { return make_float2((float)z.x, (float)z.y); }
+__device__ __forceinline__ double2 f64c(float2 z) { return make_double2((double)z.x, (double)z.y); }
+
+// FP64 powers, rounded once. |a| < kRotMin: zeros (never used, see above).
+__device__ __forceinline__ RotCoeffs rot_coeffs(double2 a, float2 b) {
+    RotCoeffs r;
+    const double n2 = a.x * a.x + a.y * a.y;
+    const bool ok = n2 >= kRotMin * kRotMin;
+    const double q = ok ? 1.0 / n2 : 0.0;
+    const double2 a2 = cmul64(a, a), b64 = f64c(b), inv = make_double2(a.x * q, -a.y * q), inv2 = cmul64(inv, inv);
+    r.a4 = f32c(cmul64(a2, a2));
+    r.c[0] = f32c(cmul64(cmul64(a2, a), b64));
+    r.c[1] = f32c(cmul64(a2, b64));
+    r.c[2] = f32c(cmul64(a, b64));
+    r.c[3] = b;
+    r.v[0] = f32c(cmul64(inv2, inv));
+    r.v[1] = f32c(inv2);
+    r.v[2] = f32c(inv);
+    return r;
+}
+
+// v[j] by value (a choice between the elements' addresses would put the array in memory).
+__device__ __forceinline__ float2 rot_v(const float2 (&v)[kRot - 1], int j) {
+    const float v0x = v[0].x, v0y = v[0].y, v1x = v[1].x, v1y = v[1].y, v2x = v[2].x, v2y = v[2].y;
+    return make_float2(j == 0 ? +v0x : j == 1 ? +v1x : +v2x, j == 0 ? +v0y : j == 1 ? +v1y : +v2y);
+}
+
+// What the FP32 recursion above multiplies a carried state by over len steps.
+__device__ __forceinline__ double2 rot_pow(float2 a4, const float2 (&v)[kRot - 1], int len) {
+    double2 r = cpow64(f64c(a4), len / kRot);
+    const int rem = len % kRot;
+    if (rem) r = cmul64(r, cmul64(f64c(a4), f64c(rot_v(v, rem - 1))));
+    return r;
+}
+
+// Per-lane register state of FL filter slots. Plain waves (see kRotMin) hold a
+// in a4 and b in c[3].
 template <int FL>
 struct Lane {
-    float ar[FL], ai[FL], br[FL], bi[FL];
+    float2 a4[FL], c[FL][kRot], v[FL][kRot - 1];
     int xo[FL];
-    float yr[FL], yi[FL];     // running state (FP32)
+    float yr[FL], yi[FL];     // running state (FP32): S inside a block, y between blocks
     float y0r[FL], y0i[FL];   // state at the chunk start (hi part)
     float l0r[FL], l0i[FL];   // low part of the chunk-start carry
     unsigned flags;           // bit f: slot f carries in FP64 (hybrid mode)
@@ -71,99 +122,147 @@ struct Lane {
     __device__ __forceinline__ int64_t slot(int f) const { return slot0 + 64 * f; }
 };
 
-// Steps of x[m - d] read ahead of their use: short for the LDS window, longer
-// when the window stays in global memory (so more of the load latency is
-// covered by the recursion itself).
-template <bool XLDS, int TT>
-struct Ahead {
-    static constexpr int value = XLDS ? 2 : (TT >= 16 ? 8 : 4);
+// x values of a lane's filters, RING rows of one step each, read RING / 2 steps
+// ahead of their use: one block in the full pass on an LDS window (a block's
+// arithmetic covers the LDS latency), one tile in the state pass (a third of
+// the arithmetic) and where the window stays in global memory (VEC).
+template <bool SUM, bool VEC>
+struct Ring {
+    static constexpr int value = VEC || !SUM ? 2 * kFwdTile : kFwdTile;
 };
 
-// x[m - d] of every filter for steps t0 .. t0 + AH - 1 of a tile. The window
-// is padded by one tile, so reads past the sub-block end stay inside it (their
-// values are never used).
-template <int FL, int TT, int AH>
-__device__ __forceinline__ void load_ahead(float (&xv)[TT][FL], const float *xw, const Lane<FL> &s, int t0) {
+// x[m - d] of every filter for one block of steps, t0 .. t0 + kRot - 1, into
+// rows k .. of xv. The window is padded by one tile, so reads past the
+// sub-block end stay inside it (their values are never used). The scheduling
+// barrier keeps the LDS reads here: left alone, the compiler sinks them to
+// just before their use to save registers and every step then waits for the
+// LDS. Window in global memory: one 16-byte load.
+template <int FL, int ROWS, bool VEC>
+__device__ __forceinline__ void load_block(float (&xv)[ROWS][FL], const float *xw, const Lane<FL> &s, int t0, int k) {
+    static_assert(kRot == 4, "one 16-byte load per block");
 #pragma unroll
     for (int f = 0; f < FL; ++f) {
         const float *xp = xw + (s.xo[f] + t0);
+        if (VEC) {
+            const f4u q = *reinterpret_cast<const f4u *>(xp);
+            xv[k][f] = q.x;
+            xv[k + 1][f] = q.y;
+            xv[k + 2][f] = q.z;
+            xv[k + 3][f] = q.w;
+        } else {
 #pragma unroll
-        for (int t = 0; t < AH; ++t) xv[t][f] = xp[t];
-    }
-}
-
-// Window in global memory: steps t0 .. t0 + AH - 1 as 16-byte loads.
-template <int FL, int TT, int AH>
-__device__ __forceinline__ void load_ahead_vec(float (&xv)[TT][FL], const float *xw, const Lane<FL> &s, int t0) {
-#pragma unroll
-    for (int f = 0; f < FL; ++f) {
-#pragma unroll
-        for (int u = 0; u < AH; u += 4) {
-            const f4u q = *reinterpret_cast<const f4u *>(xw + (s.xo[f] + t0 + u));
-            xv[u][f] = q.x;
-            xv[u + 1][f] = q.y;
-            xv[u + 2][f] = q.z;
-            xv[u + 3][f] = q.w;
+            for (int t = 0; t < kRot; ++t) xv[k + t][f] = xp[t];
         }
     }
+    if (!VEC) __builtin_amdgcn_sched_barrier(0);
 }
 
-// One tile: FL filter updates per step and per lane, the lane's partial
-// template sum of every step written to the wave's LDS tile [TT][64]. x for
-// step t + AH is read while step t computes (xv[0..AH) arrive loaded).
-// VEC (window in global memory): every 4 steps, 4 consecutive samples of each
-// filter are read with one 16-byte load; reads for steps past the tile go to
-// the slots of the next tile's first AH steps (already consumed here) when
-// `more` says a next tile follows.
-template <int FL, int TT, bool FULL, bool CARRY, int AH, bool VEC>
-__device__ __forceinline__ void compute_tile(Lane<FL> &s, float (&xv)[TT][FL], const float *xw, int t0,
-                                             int steps, float2 *wt, int lane, bool more) {
-    static_assert(!VEC || (AH % 4 == 0 && TT % 4 == 0 && AH < TT), "vector read-ahead layout");
+// One tile of kFwdTile steps: FL filter updates per step and per lane, the lane's
+// partial template sum of every step written to the wave's LDS tile
+// [kFwdTile][64] (SUM; without it only the states advance). Rows BASE .. of xv
+// hold the tile's x, or its first block in a ring of one tile; the rows that
+// follow in the ring are read here (AHEAD; without it xv arrives complete).
+// Tiles start on a block of kRot steps; a partial tile (not FULL) leaves y.
+template <int FL, int ROWS, bool FULL, bool SUM, bool PLAIN, bool VEC, bool AHEAD, int BASE>
+__device__ __forceinline__ void compute_tile(Lane<FL> &s, float (&xv)[ROWS][FL], const float *xw, int t0, int steps,
+                                             float2 *wt, int lane) {
+    constexpr int kLast = kRot - 1;
+    static_assert(kFwdTile == 2 * kRot, "ring of two blocks / two tiles");
 #pragma unroll
-    for (int t = 0; t < TT; ++t) {
-        if (!CARRY && VEC && t % 4 == 0) {
-            const int u = t + AH;
-            if (u < TT || more) {
-                const int k = u < TT ? u : u - TT;
-#pragma unroll
-                for (int f = 0; f < FL; ++f) {
-                    const f4u q = *reinterpret_cast<const f4u *>(xw + (s.xo[f] + t0 + u));
-                    xv[k][f] = q.x;
-                    xv[k + 1][f] = q.y;
-                    xv[k + 2][f] = q.z;
-                    xv[k + 3][f] = q.w;
-                }
-            }
-        }
-        if (!CARRY && !VEC && t + AH < TT) {
-#pragma unroll
-            for (int f = 0; f < FL; ++f) xv[t + AH][f] = xw[s.xo[f] + t0 + t + AH];
+    for (int t = 0; t < kFwdTile; ++t) {
+        if (AHEAD && t % kRot == 0) {
+            const int u = t + ROWS / 2;   // step whose x is read now
+            load_block<FL, ROWS, VEC>(xv, xw, s, t0 + u, (BASE + u) % ROWS);
         }
         if (!FULL && t >= steps) continue;  // uniform; keeps every index static
+        const int j = t % kRot;
         float pr = 0.f, pi = 0.f;
 #pragma unroll
         for (int f = 0; f < FL; ++f) {
+            const float x = xv[BASE + t][f];
             float nr, ni;
-            if (CARRY) {  // free response of the carried state: y <- a y
-                nr = fmaf(-s.ai[f], s.yi[f], s.ar[f] * s.yr[f]);
-                ni = fmaf(s.ai[f], s.yr[f], s.ar[f] * s.yi[f]);
+            if (PLAIN || j == 0) {
+                const float2 m = s.a4[f], c = s.c[f][PLAIN ? kLast : 0];
+                nr = fmaf(-m.y, s.yi[f], fmaf(m.x, s.yr[f], c.x * x));
+                ni = fmaf(m.y, s.yr[f], fmaf(m.x, s.yi[f], c.y * x));
             } else {
-                const float xv_ = xv[t][f];
-                nr = fmaf(-s.ai[f], s.yi[f], fmaf(s.ar[f], s.yr[f], s.br[f] * xv_));
-                ni = fmaf(s.ai[f], s.yr[f], fmaf(s.ar[f], s.yi[f], s.bi[f] * xv_));
+                nr = fmaf(s.c[f][j].x, x, s.yr[f]);
+                ni = fmaf(s.c[f][j].y, x, s.yi[f]);
             }
             s.yr[f] = nr;
             s.yi[f] = ni;
-            if (f == 0) {
-                pr = nr;
-                pi = ni;
+            if (!SUM) continue;
+            if (PLAIN || j == kLast) {
+                pr = f == 0 ? nr : pr + nr;
+                pi = f == 0 ? ni : pi + ni;
             } else {
-                pr += nr;
-                pi += ni;
+                const float2 v = s.v[f][j < kLast ? j : 0];
+                pr = fmaf(-v.y, ni, f == 0 ? v.x * nr : fmaf(v.x, nr, pr));
+                pi = fmaf(v.y, nr, f == 0 ? v.x * ni : fmaf(v.x, ni, pi));
             }
         }
-        wt[t * 64 + lane] = make_float2(pr, pi);
+        if (SUM) wt[t * 64 + lane] = make_float2(pr, pi);
     }
+    if (!FULL && !PLAIN && steps % kRot) {   // S of an unfinished block -> y
+#pragma unroll
+        for (int f = 0; f < FL; ++f) {
+            const float2 v = rot_v(s.v[f], steps % kRot - 1);
+            const float yr = fmaf(-v.y, s.yi[f], v.x * s.yr[f]);
+            s.yi[f] = fmaf(v.y, s.yr[f], v.x * s.yi[f]);
+            s.yr[f] = yr;
+        }
+    }
+}
+
+// A tile outside the ring: waves that run the plain recursion, the last tile
+// of a pass that ends inside it, a tile without a partner in a ring of two.
+template <int FL, bool SUM, bool VEC>
+__device__ __forceinline__ void lone_tile(Lane<FL> &s, const float *xw, int t0, int steps, float2 *wt, int lane,
+                                          bool plain) {
+    float xv[kFwdTile][FL];
+    load_block<FL, kFwdTile, VEC>(xv, xw, s, t0, 0);
+    load_block<FL, kFwdTile, VEC>(xv, xw, s, t0 + kRot, kRot);
+    if (plain && steps == kFwdTile)
+        compute_tile<FL, kFwdTile, true, SUM, true, VEC, false, 0>(s, xv, xw, t0, steps, wt, lane);
+    else if (plain)
+        compute_tile<FL, kFwdTile, false, SUM, true, VEC, false, 0>(s, xv, xw, t0, steps, wt, lane);
+    else
+        compute_tile<FL, kFwdTile, false, SUM, false, VEC, false, 0>(s, xv, xw, t0, steps, wt, lane);
+}
+
+template <int FL, bool SUM, bool VEC>
+__device__ __forceinline__ void fill_ring(const Lane<FL> &s, float (&xv)[Ring<SUM, VEC>::value][FL], const float *xw,
+                                          int t0) {
+    constexpr int RING = Ring<SUM, VEC>::value;
+    load_block<FL, RING, VEC>(xv, xw, s, t0, 0);
+    if (RING > kFwdTile) load_block<FL, RING, VEC>(xv, xw, s, t0 + kRot, kRot);
+}
+
+// Tiles of steps [t0, t1) of a sub-block, each followed by post(its first step,
+// its steps). The ring holds the x that the first tile expects on entry and the
+// next tile's at the end (refilled after lone tiles).
+template <int FL, bool SUM, bool VEC, class Post>
+__device__ __forceinline__ void run_tiles(Lane<FL> &s, float (&xv)[Ring<SUM, VEC>::value][FL], const float *xw, int t0,
+                                          int t1, float2 *wt, int lane, bool plain, Post post) {
+    constexpr int RING = Ring<SUM, VEC>::value;
+    if (!plain) {
+        for (; t0 + RING <= t1; t0 += RING) {
+            compute_tile<FL, RING, true, SUM, false, VEC, true, 0>(s, xv, xw, t0, kFwdTile, wt, lane);
+            post(t0, kFwdTile);
+            if (RING > kFwdTile) {
+                constexpr int kOdd = RING > kFwdTile ? kFwdTile : 0;
+                compute_tile<FL, RING, true, SUM, false, VEC, true, kOdd>(s, xv, xw, t0 + kFwdTile, kFwdTile, wt, lane);
+                post(t0 + kFwdTile, kFwdTile);
+            }
+        }
+        if (t0 >= t1) return;
+    }
+    for (; t0 < t1; t0 += kFwdTile) {
+        const int steps = min(kFwdTile, t1 - t0);
+        lone_tile<FL, SUM, VEC>(s, xw, t0, steps, wt, lane, plain);
+        post(t0, steps);
+    }
+    if (!plain) fill_ring<FL, SUM, VEC>(s, xv, xw, t1);
 }
 
 // Row sums of a wave tile: wsum[t][4 * wave + r] = sum of the 16 lanes of row
@@ -171,54 +270,39 @@ __device__ __forceinline__ void compute_tile(Lane<FL> &s, float (&xv)[TT][FL], c
 // 2p and 2p+1 read the two halves of one unit together (the LDS serves a
 // ds_read_b128 per lane pair), and pair p walks its row's units in an order
 // rotated by p / 2, so the 8 pairs served in one cycle hit distinct banks.
-// Each lane sums its halves; one DPP swap adds the partner's half.
-template <int TT>
-struct RowSumPlan {
-    static constexpr int kReads = TT == 16 ? 8 : 4;
-    int off[kReads];   // byte offsets inside the wave tile, in read order
-    int k0, k1;        // tile rows this pair sums (TT = 16: two rows; TT = 8: one)
+// Each lane sums its halves; one DPP swap adds the partner's half. The reads
+// (row_reads) are issued right after the tile's writes - a wave's LDS
+// operations take effect in order, so neither they nor the next tile's writes
+// need a wait - and are added up after the next tile's recursion (row_add),
+// which hides their latency.
+struct RowReads {
+    float4 v[4];
 };
 
-template <int TT>
-__device__ __forceinline__ RowSumPlan<TT> row_sum_plan(int lane) {
-    RowSumPlan<TT> pl;
-    const int p = lane >> 1, h = lane & 1;
-    pl.k0 = p;
-    pl.k1 = p + 32;
-#pragma unroll
-    for (int i = 0; i < pl.kReads; ++i) {
-        const int k = (i < 4) ? pl.k0 : pl.k1;
-        const int q = ((i & 3) + (p >> 1)) & 3;
-        pl.off[i] = k * 128 + (2 * q + h) * 16;
-    }
-    return pl;
-}
-
-__device__ __forceinline__ float2 sum_chunks4(const float4 &a, const float4 &b, const float4 &c, const float4 &d) {
-    return make_float2(((a.x + a.z) + (b.x + b.z)) + ((c.x + c.z) + (d.x + d.z)),
-                       ((a.y + a.w) + (b.y + b.w)) + ((c.y + c.w) + (d.y + d.w)));
-}
-
-template <int TT>
-__device__ __forceinline__ void row_sums(const float2 *wt, const RowSumPlan<TT> &pl, float2 *wsum_buf,
-                                         int Rp, int wave, int lane) {
+__device__ __forceinline__ RowReads row_reads(const float2 *wt, int lane) {
     const char *base = reinterpret_cast<const char *>(wt);
-    const bool lo = (lane & 1) == 0;
-    float4 v[RowSumPlan<TT>::kReads];
+    const int p = lane >> 1, h = lane & 1;
+    RowReads r;
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_wave_barrier();
 #pragma unroll
-    for (int i = 0; i < RowSumPlan<TT>::kReads; ++i) v[i] = *reinterpret_cast<const float4 *>(base + pl.off[i]);
-    const float2 s0 = sum_chunks4(v[0], v[1], v[2], v[3]);
-    const float o0r = dpp_swap_pairs(s0.x), o0i = dpp_swap_pairs(s0.y);
-    if (TT == 16) {
-        const float2 s1 = sum_chunks4(v[4], v[5], v[6], v[7]);
-        const float o1r = dpp_swap_pairs(s1.x), o1i = dpp_swap_pairs(s1.y);
-        // the even lane writes row k0, the odd lane row k1; both as (even half) + (odd half)
-        const int k = lo ? pl.k0 : pl.k1;
-        const float2 tot = lo ? make_float2(s0.x + o0r, s0.y + o0i) : make_float2(o1r + s1.x, o1i + s1.y);
-        wsum_buf[(k >> 2) * Rp + wave * 4 + (k & 3)] = tot;
-    } else {
-        if (lo) wsum_buf[(pl.k0 >> 2) * Rp + wave * 4 + (pl.k0 & 3)] = make_float2(s0.x + o0r, s0.y + o0i);
+    for (int i = 0; i < 4; ++i) {
+        const int q = (i + (p >> 1)) & 3;
+        r.v[i] = *reinterpret_cast<const float4 *>(base + p * 128 + (2 * q + h) * 16);
     }
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_wave_barrier();
+    return r;
+}
+
+__device__ __forceinline__ void row_add(const RowReads &r, float2 *wsum, int Rp, int wave, int lane) {
+    const float sx = ((r.v[0].x + r.v[0].z) + (r.v[1].x + r.v[1].z)) +
+                     ((r.v[2].x + r.v[2].z) + (r.v[3].x + r.v[3].z));
+    const float sy = ((r.v[0].y + r.v[0].w) + (r.v[1].y + r.v[1].w)) +
+                     ((r.v[2].y + r.v[2].w) + (r.v[3].y + r.v[3].w));
+    const float ox = dpp_swap_pairs(sx), oy = dpp_swap_pairs(sy);
+    const int k = lane >> 1;
+    if ((lane & 1) == 0) wsum[(k >> 2) * Rp + wave * 4 + (k & 3)] = make_float2(sx + ox, sy + oy);
 }
 
 // xs[i] = src[off + i] (0 if ZERO) for i in [i0, i1), by the whole workgroup:
@@ -251,32 +335,9 @@ __device__ __forceinline__ void stage_range(float *xs, const float *src, int64_t
     for (int i = ia + 4 * nv + tid; i < i1; i += nt) xs[i] = ZERO ? 0.f : src[off + i];
 }
 
-// Template sum over its nr row sums of one step: N reads issued together
-// (rows past nr read other rows or the buffer's slack and are zeroed), then a
-// fixed pairwise tree; templates of more than 16 rows loop.
-template <int N>
-__device__ __forceinline__ void sum_rows(const float2 *ws, int nr, float &zr, float &zi) {
-    float vr[N], vi[N];
-#pragma unroll
-    for (int i = 0; i < N; ++i) {
-        const float2 v = ws[i];
-        vr[i] = i < nr ? v.x : 0.f;
-        vi[i] = i < nr ? v.y : 0.f;
-    }
-#pragma unroll
-    for (int w = 1; w < N; w *= 2)
-#pragma unroll
-        for (int i = 0; i < N; i += 2 * w) {
-            vr[i] += vr[i + w];
-            vi[i] += vi[i + w];
-        }
-    zr = vr[0];
-    zi = vi[0];
-}
-
-__device__ __forceinline__ void sum_rows_loop(const float2 *ws, int nr, float &zr, float &zi) {
-    zr = 0.f;
-    zi = 0.f;
+// Template sum over its nr row sums of one step, in a fixed order.
+__device__ __forceinline__ float2 sum_rows(const float2 *ws, int nr) {
+    float zr = 0.f, zi = 0.f;
     int r = 0;
     for (; r + 4 <= nr; r += 4) {
         const float2 v0 = ws[r], v1 = ws[r + 1], v2 = ws[r + 2], v3 = ws[r + 3];
@@ -287,28 +348,28 @@ __device__ __forceinline__ void sum_rows_loop(const float2 *ws, int nr, float &z
         zr += ws[r].x;
         zi += ws[r].y;
     }
+    return make_float2(zr, zi);
 }
 
 // Chunk-end correction of the carried state (len = samples in the chunk).
 template <int FL>
-__device__ __forceinline__ void carry_correct(Lane<FL> &s, const SlotArrays &sa, int prec,
+__device__ __forceinline__ void carry_correct(Lane<FL> &s, const SlotArrays &sa, int prec, bool plain,
                                               int len, int L) {
 #pragma unroll
     for (int f = 0; f < FL; ++f) {
         float hr = s.yr[f], hi = s.yi[f], lr = 0.f, li = 0.f;
         if (prec != kPrecFp32) {
             double2 al, dl;
-            if (len == L) {
+            if (len == L && !plain) {
                 al = sa.aL[s.slot(f)];
                 dl = sa.dL[s.slot(f)];
             } else {
-                const double2 a = sa.a64[s.slot(f)];
-                al = cpow64(a, len);
-                const double2 ah = cpow64(make_double2((double)s.ar[f], (double)s.ai[f]), len);
+                al = cpow64(sa.a64[s.slot(f)], len);
+                const double2 ah = plain ? cpow64(f64c(s.a4[f]), len) : rot_pow(s.a4[f], s.v[f], len);
                 dl = make_double2(al.x - ah.x, al.y - ah.y);
             }
             if (prec == kPrecFp64 || ((s.flags >> f) & 1u)) {
-                // c_end = y_end + (a^l - fl(a)^l) * hi_start + a^l * lo_start, in FP64
+                // c_end = y_end + (a^l - what FP32 carried) * hi_start + a^l * lo_start, in FP64
                 const double y0r = s.y0r[f], y0i = s.y0i[f], l0r = s.l0r[f], l0i = s.l0i[f];
                 const double cr = (double)hr + (dl.x * y0r - dl.y * y0i) + (al.x * l0r - al.y * l0i);
                 const double ci = (double)hi + (dl.x * y0i + dl.y * y0r) + (al.x * l0i + al.y * l0r);
@@ -331,193 +392,308 @@ __device__ __forceinline__ void carry_correct(Lane<FL> &s, const SlotArrays &sa,
     }
 }
 
-// Time range and data routing of one workgroup item.
+// Time range and state routing of one workgroup item.
 struct SegCtx {
     int64_t tb, tn;          // launch samples [tb, tb + tn)
     const float4 *st_in;     // initial state per slot (null: cold start), entry slot - in_off
     float4 *st_out;          // final state per slot (null: not stored), entry slot - out_off
     int64_t in_off, out_off;
-    float2 *zl_out;          // local z goes here ([T][ld_zl]) instead of the mode's output
-    const float2 *zl_in;     // added to z before the mode's output (carry pass)
-    int64_t ld_zl;
+    // seg > 0: the initial state is composed from the end states of the segments before it,
+    // st_in[k * stride] for segment k (segment 0's from the carried state), each `len` samples
+    int seg;
+    int64_t stride, len;
 };
 
+// One step of the carry chain: c <- al c + e, e = hi + lo.
+__device__ __forceinline__ void chain_step(double2 &c, double2 al, float4 e) {
+    const double2 m = cmul64(al, c);
+    c.x = m.x + ((double)e.x + (double)e.z);
+    c.y = m.y + ((double)e.y + (double)e.w);
+}
+
+__device__ __forceinline__ float4 hi_lo(double2 c) {
+    const float hr = (float)c.x, hi = (float)c.y;
+    return make_float4(hr, hi, (float)(c.x - (double)hr), (float)(c.y - (double)hi));
+}
+
+// Up to this many segments every workgroup of the full pass composes its own
+// start state (at most 7 reads per slot); beyond it a launch of its own does.
+// The launch costs about 6 us with its gaps: 21.7 -> 15.1 us per 512-sample
+// call of a 4 x 128-filter bank.
+constexpr int kChainInline = 8;
+
+// Coefficients and initial states of a lane's slots; true if the wave runs
+// the plain recursion. The block powers are formed here in FP64 (full rate on
+// this chip): 72 bytes of tables less to read per slot and launch.
+template <int FL>
+__device__ __forceinline__ bool load_lane(Lane<FL> &s, const FwdArgs &p, int g, int wave, int lane, bool ract,
+                                          int xshift, const SegCtx &sc) {
+    s.slot0 = slot_index(g, p.wpg, wave, 0, FL, lane);
+    s.flags = 0u;
+    double2 a[FL];
+    float2 b[FL];
+    bool small = false;
+#pragma unroll
+    for (int f = 0; f < FL; ++f) {
+        a[f] = make_double2(0.0, 0.0);
+        b[f] = make_float2(0.f, 0.f);
+        s.xo[f] = 0;
+        float4 st = make_float4(0.f, 0.f, 0.f, 0.f);
+        if (ract) {
+            a[f] = p.s.a64[s.slot(f)];
+            if (p.prec == kPrecFp32) a[f] = f64c(f32c(a[f]));
+            b[f] = p.s.b32[s.slot(f)];
+            s.xo[f] = p.s.xoff[s.slot(f)] - xshift;
+            s.flags |= (unsigned)(p.s.flags[s.slot(f)] & 1) << f;
+            if (sc.st_in && sc.seg <= 1) st = sc.st_in[s.slot(f) - sc.in_off];
+            if (sc.seg > 1) {
+                float4 e[kChainInline - 1];
+#pragma unroll
+                for (int k = 0; k < kChainInline - 1; ++k)
+                    if (k < sc.seg) e[k] = sc.st_in[(int64_t)k * sc.stride + s.slot(f) - sc.in_off];
+                const double2 al = cpow64(a[f], (int)sc.len);
+                double2 c = make_double2(0.0, 0.0);
+#pragma unroll
+                for (int k = 0; k < kChainInline - 1; ++k)
+                    if (k < sc.seg) chain_step(c, al, e[k]);
+                st = hi_lo(c);
+            }
+        }
+        s.yr[f] = s.y0r[f] = st.x;
+        s.yi[f] = s.y0i[f] = st.y;
+        s.l0r[f] = st.z;
+        s.l0i[f] = st.w;
+        // padding slots (a = b = 0) stay zero in either form
+        const double n2 = a[f].x * a[f].x + a[f].y * a[f].y;
+        small = small || (n2 < kRotMin * kRotMin && (n2 > 0.0 || b[f].x != 0.f || b[f].y != 0.f));
+    }
+    const bool plain = __ballot(small) != 0;
+#pragma unroll
+    for (int f = 0; f < FL; ++f) {
+        const RotCoeffs r = rot_coeffs(a[f], b[f]);
+        s.a4[f] = plain ? f32c(a[f]) : r.a4;
+#pragma unroll
+        for (int j = 0; j < kRot; ++j) s.c[f][j] = r.c[j];
+#pragma unroll
+        for (int j = 0; j < kRot - 1; ++j) s.v[f][j] = r.v[j];
+    }
+    return plain;
+}
+
+// Stages xs[i] = x[m0 + i], i in [0, gw + nbs), m0 = first sample - glo - gw;
+// samples before x[0] come from the history. The caller syncs around it.
+__device__ __forceinline__ void stage_window(float *xs, const FwdArgs &p, int64_t xfirst, int glo, int gw, int nbs) {
+    const int cnt = gw + nbs;
+    const int64_t m0 = xfirst - glo - gw;
+    const int nneg = (int)min((int64_t)cnt, max((int64_t)0, -m0));
+    // a band's window may reach past the largest delay (glo + gw > max_delay):
+    // samples before the history (m < -max_delay) are read by no filter and
+    // staged as zeros, so the history is only read at indices >= 0
+    const int nz = (int)min((int64_t)nneg, max((int64_t)0, -(int64_t)p.dmax - m0));
+    if (p.hist) {
+        stage_range<true>(xs, nullptr, 0, 0, nz);
+        stage_range<false>(xs, p.hist, p.dmax + m0, nz, nneg);
+    } else {
+        stage_range<true>(xs, nullptr, 0, 0, nneg);
+    }
+    stage_range<false>(xs, p.x, m0, nneg, cnt);
+}
+
+__host__ __device__ __forceinline__ size_t window_bytes(int gw, int nb) {
+    return (size_t)((gw + nb + kFwdTile + 3) & ~3) * 4;
+}
+
 // The whole forward pass of workgroup g over launch samples [sc.tb, sc.tb + sc.tn).
-// CARRY: free response of the given state only (no input), z_local added.
+// The waves run tiles on their own and meet once per batch of sumb (64) steps,
+// when every row sum of the batch is in LDS: then each wave takes some of the
+// workgroup's templates, lane = step, adds their row sums and writes 64
+// consecutive samples.
+// Bound: VALU issue at 2 waves per SIMD (FL = 4: 230 registers), so a wave that
+// waits is hardly covered. Per 4,096-sample call of the 1,024-template bank:
+// 541 us with the rotating recursion (8 operations per update), a barrier per
+// 16 steps and the template sums on the waves that hold a template's first row;
+// 577 with blocks of 4 steps alone (its LDS reads were sunk to their use), 545
+// with the reads pinned a block ahead, 507 with batches of 64 steps and the
+// row-sum reads left in flight, 463 with a hot loop that no other case joins:
+// 7.1 operations per update, 4.06e12 updates/s.
 // PARTS: the bank has templates split over workgroups (rows with part >= 0);
 // banks without them run the variant that has no part branch.
-template <int FL, int TT, int MODE, bool XLDS, bool CARRY, bool PARTS = false>
+template <int FL, int MODE, bool XLDS, bool PARTS = false>
 __device__ void fwd_group(const FwdArgs &p, int g, unsigned char *smem, const SegCtx &sc) {
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int W = p.wpg, R = 4 * W, Rp = R + 1;  // odd row stride of wsum: no bank aliasing over t
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int W = p.wpg, R = 4 * W, Rp = R + 1;  // odd row stride of wsum: no bank aliasing over steps
     // LDS window: x[m - d] for the group's delays d in [glo, glo + gw]; slot offsets are
     // max_delay - d, so a lane's window offset is that minus (max_delay - glo - gw)
     const int glo = XLDS && p.group_lo ? p.group_lo[g] : 0;
     const int gw = XLDS ? p.band_w : p.dmax;
-    const int xshift = p.dmax - glo - gw;
-    const size_t win_bytes = XLDS ? (size_t)((gw + p.nb + TT + 3) & ~3) * 4 : 0;
+    const size_t win_bytes = XLDS ? window_bytes(gw, p.nb) : 0;
     float *xs = reinterpret_cast<float *>(smem);
-    float2 *wt = reinterpret_cast<float2 *>(smem + win_bytes) + wave * TT * 64;
-    float2 *wsum = reinterpret_cast<float2 *>(smem + win_bytes) + W * TT * 64;  // [2][TT][Rp]
-    // [2][TT] after wsum and 16 float2 of slack (row-sum reads past a template's last row)
-    unsigned long long *kmax = reinterpret_cast<unsigned long long *>(wsum + 2 * TT * Rp + 16);
-    const RowSumPlan<TT> rsp = row_sum_plan<TT>(lane);
-    constexpr int AH = Ahead<XLDS, TT>::value;
+    float2 *tiles = reinterpret_cast<float2 *>(smem + win_bytes);
+    float2 *wt = tiles + wave * kFwdTile * 64;
+    const int sb = p.sumb;
+    float2 *wsum = tiles + W * kFwdTile * 64;   // [2][sb][Rp]
+    unsigned long long *kmax = reinterpret_cast<unsigned long long *>(wsum + 2 * sb * Rp);  // [2][sb]
+    int *nitems = reinterpret_cast<int *>(kmax + 2 * sb);
+    unsigned char *items = reinterpret_cast<unsigned char *>(nitems + 1);   // [R]: first rows of the templates here
 
-    const int row = wave * 4 + (lane >> 4);
-    const RowInfo ri = p.rows[(int64_t)g * R + row];
+    const RowInfo ri = p.rows[(int64_t)g * R + wave * 4 + (lane >> 4)];
     const bool ract = ri.tpl >= 0 && (p.only_tpl < 0 || ri.tpl == p.only_tpl);
     const bool wact = __ballot(ract) != 0;
-    const int tl16 = lane & 15;
-    const bool leader = ract && ri.r0 == row && tl16 < TT;
+    if (wave == 0) {
+        RowInfo it = {-1, 0, 0, -1};
+        if (lane < R) it = p.rows[(int64_t)g * R + lane];
+        const bool first = it.tpl >= 0 && it.r0 == lane && (p.only_tpl < 0 || it.tpl == p.only_tpl);
+        const unsigned long long m = __ballot(first);
+        if (first) items[__popcll(m & ((1ull << lane) - 1))] = (unsigned char)lane;
+        if (lane == 0) *nitems = __popcll(m);
+    }
+    if (MODE == kModeKeys)
+        for (int i = tid; i < 2 * sb; i += W * 64) kmax[i] = 0ull;
 
     Lane<FL> s;
-    s.slot0 = slot_index(g, W, wave, 0, FL, lane);
-    s.flags = 0u;
-#pragma unroll
-    for (int f = 0; f < FL; ++f) {
-        if (ract) {
-            const float2 a = p.s.a32[s.slot(f)], b = p.s.b32[s.slot(f)];
-            s.ar[f] = a.x; s.ai[f] = a.y; s.br[f] = b.x; s.bi[f] = b.y;
-            s.xo[f] = p.s.xoff[s.slot(f)] - xshift;
-            s.flags |= (unsigned)(p.s.flags[s.slot(f)] & 1) << f;
-            float4 st = make_float4(0.f, 0.f, 0.f, 0.f);
-            if (sc.st_in) st = sc.st_in[s.slot(f) - sc.in_off];
-            s.yr[f] = st.x; s.yi[f] = st.y; s.l0r[f] = st.z; s.l0i[f] = st.w;
-        } else {
-            s.ar[f] = s.ai[f] = s.br[f] = s.bi[f] = 0.f;
-            s.xo[f] = 0;
-            s.yr[f] = s.yi[f] = s.l0r[f] = s.l0i[f] = 0.f;
-        }
-        s.y0r[f] = s.yr[f];
-        s.y0i[f] = s.yi[f];
-    }
-    const bool keys_out = MODE == kModeKeys && sc.zl_out == nullptr;
+    const bool plain = load_lane<FL>(s, p, g, wave, lane, ract, p.dmax - glo - gw, sc);
     const int64_t n = sc.tn;
     const int64_t xbase = p.xbase + sc.tb;
-    if (keys_out && tid < 2 * TT) kmax[tid] = 0ull;
 
-    int64_t chunk_start = 0;
-    int buf = 0;
-    bool pending = false;
+    int chunk_done = 0;   // samples of the current chunk so far
+    int buf = 0, pend_steps = 0;
     int64_t pend_t = 0;
-    int pend_steps = 0;
-    float xv[TT][FL];
+    float xv[Ring<true, !XLDS>::value][FL];
+    RowReads rr;
+
+    auto flush_keys = [&](int b) {   // the keys of the batch before the last barrier
+        if (MODE == kModeKeys && wave == 0 && lane < pend_steps) {
+            p.keys[(int64_t)g * p.ld + sc.tb + pend_t + lane] = kmax[b * sb + lane];
+            kmax[b * sb + lane] = 0ull;
+        }
+    };
+    // template sums and outputs of one batch: launch samples sc.tb + t + [0, steps)
+    auto emit = [&](int64_t t, int steps) {
+        const int ni = *nitems;
+        unsigned long long best = 0ull;
+        for (int i = wave; i < ni; i += W) {
+            const int r0 = __builtin_amdgcn_readfirstlane((int)items[i]);
+            const RowInfo it = p.rows[(int64_t)g * R + r0];
+            const int tpl = __builtin_amdgcn_readfirstlane(it.tpl);
+            const int nr = __builtin_amdgcn_readfirstlane(it.nr), part = __builtin_amdgcn_readfirstlane(it.part);
+            if (lane >= steps) continue;
+            const float2 z = sum_rows(wsum + (buf * sb + lane) * Rp + r0, nr);
+            if (PARTS && part >= 0) {
+                // one part of a template split over workgroups: its partial sum goes to the
+                // part's row; the parts are added before the mode's output
+                p.zpart[(int64_t)part * p.ld_part + sc.tb + t + lane] = z;
+            } else if (MODE == kModeSnr) {
+                p.snr[(int64_t)tpl * p.ld + p.obase + sc.tb + t + lane] = z.x * z.x + z.y * z.y;
+            } else if (MODE == kModeZ) {
+                p.z[(int64_t)tpl * p.ld + p.obase + sc.tb + t + lane] = z;
+            } else {
+                const float sn = z.x * z.x + z.y * z.y;
+                const unsigned long long key = ((unsigned long long)__float_as_uint(sn) << 32) |
+                                               (unsigned long long)(0xFFFFFFFFu - (uint32_t)tpl);
+                best = key > best ? key : best;
+            }
+        }
+        if (MODE == kModeKeys && best != 0ull) atomicMax(&kmax[buf * sb + lane], best);
+    };
 
     for (int64_t s0 = 0; s0 < n; s0 += p.nb) {
         const int nbs = (int)min((int64_t)p.nb, n - s0);
-        const float *xw = nullptr;
-        if (CARRY) {
-            xw = nullptr;
-        } else if (XLDS) {
-            __syncthreads();
-            const int cnt = gw + nbs;
-            const int64_t m0 = xbase + s0 - glo - gw;   // xs[i] = x[m0 + i]; m < 0 from the history
-            const int nneg = (int)min((int64_t)cnt, max((int64_t)0, -m0));
-            // a band's window may reach past the largest delay (glo + gw > max_delay):
-            // samples before the history (m < -max_delay) are read by no filter and
-            // staged as zeros, so the history is only read at indices >= 0
-            const int nz = (int)min((int64_t)nneg, max((int64_t)0, -(int64_t)p.dmax - m0));
-            if (p.hist) {
-                stage_range<true>(xs, nullptr, 0, 0, nz);
-                stage_range<false>(xs, p.hist, p.dmax + m0, nz, nneg);
-            } else {
-                stage_range<true>(xs, nullptr, 0, 0, nneg);
-            }
-            stage_range<false>(xs, p.x, m0, nneg, cnt);
+        const float *xw;
+        __syncthreads();
+        if (XLDS) {
+            stage_window(xs, p, xbase + s0, glo, gw, nbs);
             __syncthreads();
             xw = xs;
         } else {
             xw = p.xwin + (xbase + s0);
         }
-        if (!CARRY && wact) {
-            if (XLDS)
-                load_ahead<FL, TT, AH>(xv, xw, s, 0);
-            else
-                load_ahead_vec<FL, TT, AH>(xv, xw, s, 0);
-        }
+        if (wact && !plain) fill_ring<FL, true, !XLDS>(s, xv, xw, 0);
 
-        for (int t0 = 0; t0 < nbs; t0 += TT) {
-            const int steps = min(TT, nbs - t0);
-            const bool more = t0 + TT < nbs;
+        for (int b0 = 0; b0 < nbs; b0 += sb) {
+            const int bsteps = min(sb, nbs - b0);
             if (wact) {
-                if (steps == TT)
-                    compute_tile<FL, TT, true, CARRY, AH, !XLDS>(s, xv, xw, t0, steps, wt, lane, more);
-                else
-                    compute_tile<FL, TT, false, CARRY, AH, !XLDS>(s, xv, xw, t0, steps, wt, lane, more);
-                wave_lds_sync();
-                row_sums<TT>(wt, rsp, wsum + buf * TT * Rp, Rp, wave, lane);
-                if (XLDS && !CARRY && more) load_ahead<FL, TT, AH>(xv, xw, s, t0 + TT);
+                float2 *ws = wsum + buf * sb * Rp;
+                run_tiles<FL, true, !XLDS>(s, xv, xw, b0, b0 + bsteps, wt, lane, plain, [&](int t0, int steps) {
+                    if (t0 > b0) {
+                        row_add(rr, ws, Rp, wave, lane);
+                        ws += kFwdTile * Rp;
+                    }
+                    rr = row_reads(wt, lane);
+                    chunk_done += steps;
+                    if (chunk_done == p.L) {
+                        carry_correct<FL>(s, p.s, p.prec, plain, p.L, p.L);
+                        chunk_done = 0;
+                    }
+                });
+                row_add(rr, ws, Rp, wave, lane);
             }
             __syncthreads();
-            if (keys_out && pending && wave == 0 && lane < pend_steps) {
-                const int pb = buf ^ 1;
-                p.keys[(int64_t)g * p.ld + sc.tb + pend_t + lane] = kmax[pb * TT + lane];
-                kmax[pb * TT + lane] = 0ull;
-            }
-            if (leader && tl16 < steps) {
-                const float2 *ws = wsum + (buf * TT + tl16) * Rp + ri.r0;
-                float zr, zi;
-                if (ri.nr <= 8)
-                    sum_rows<8>(ws, ri.nr, zr, zi);
-                else if (ri.nr <= 16)
-                    sum_rows<16>(ws, ri.nr, zr, zi);
-                else
-                    sum_rows_loop(ws, ri.nr, zr, zi);
-                const int64_t tl = s0 + t0 + tl16;
-                if (PARTS && ri.part >= 0) {
-                    // one part of a template split over workgroups: its partial sum (the
-                    // segment's local sum, completed in place by the carry pass) goes to the
-                    // part's row; the parts are added before the mode's output
-                    float2 *zp = p.zpart + (int64_t)ri.part * p.ld_part + sc.tb + tl;
-                    if (sc.zl_in) {
-                        const float2 zl = *zp;
-                        zr += zl.x;
-                        zi += zl.y;
-                    }
-                    *zp = make_float2(zr, zi);
-                } else {
-                    if (sc.zl_in) {
-                        const float2 zl = sc.zl_in[(int64_t)ri.tpl * sc.ld_zl + tl];
-                        zr += zl.x;
-                        zi += zl.y;
-                    }
-                    if (sc.zl_out) {
-                        sc.zl_out[(int64_t)ri.tpl * sc.ld_zl + tl] = make_float2(zr, zi);
-                    } else if (MODE == kModeSnr) {
-                        p.snr[(int64_t)ri.tpl * p.ld + p.obase + sc.tb + tl] = zr * zr + zi * zi;
-                    } else if (MODE == kModeZ) {
-                        p.z[(int64_t)ri.tpl * p.ld + p.obase + sc.tb + tl] = make_float2(zr, zi);
-                    } else {
-                        const float sn = zr * zr + zi * zi;
-                        const unsigned long long key =
-                            ((unsigned long long)__float_as_uint(sn) << 32) |
-                            (unsigned long long)(0xFFFFFFFFu - (uint32_t)ri.tpl);
-                        atomicMax(&kmax[buf * TT + tl16], key);
-                    }
-                }
-            }
-            if (keys_out) {
-                pending = true;
-                pend_t = s0 + t0;
-                pend_steps = steps;
-            }
-            const int64_t tend = s0 + t0 + steps;
-            if (tend - chunk_start == p.L || tend == n) {
-                if (wact) carry_correct<FL>(s, p.s, p.prec, (int)(tend - chunk_start), p.L);
-                chunk_start = tend;
-            }
+            flush_keys(buf ^ 1);
+            emit(s0 + b0, bsteps);
+            pend_t = s0 + b0;
+            pend_steps = bsteps;
             buf ^= 1;
         }
     }
-    if (keys_out) {
+    if (wact && chunk_done) carry_correct<FL>(s, p.s, p.prec, plain, chunk_done, p.L);
+    if (MODE == kModeKeys) {
         __syncthreads();
-        if (pending && wave == 0 && lane < pend_steps) {
-            const int pb = buf ^ 1;
-            p.keys[(int64_t)g * p.ld + sc.tb + pend_t + lane] = kmax[pb * TT + lane];
-            kmax[pb * TT + lane] = 0ull;
+        flush_keys(buf ^ 1);
+    }
+    if (ract && sc.st_out) {
+#pragma unroll
+        for (int f = 0; f < FL; ++f)
+            sc.st_out[s.slot(f) - sc.out_off] = make_float4(s.yr[f], s.yi[f], s.l0r[f], s.l0i[f]);
+    }
+}
+
+// The states of workgroup g alone over launch samples [sc.tb, sc.tb + sc.tn):
+// no template sums, no output rows, no barrier but the window's.
+template <int FL, bool XLDS>
+__device__ void state_group(const FwdArgs &p, int g, unsigned char *smem, const SegCtx &sc, float4 *st_copy) {
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int glo = XLDS && p.group_lo ? p.group_lo[g] : 0;
+    const int gw = XLDS ? p.band_w : p.dmax;
+    float *xs = reinterpret_cast<float *>(smem);
+    const RowInfo ri = p.rows[(int64_t)g * 4 * p.wpg + wave * 4 + (lane >> 4)];
+    const bool ract = ri.tpl >= 0 && (p.only_tpl < 0 || ri.tpl == p.only_tpl);
+    const bool wact = __ballot(ract) != 0;
+    Lane<FL> s;
+    const bool plain = load_lane<FL>(s, p, g, wave, lane, ract, p.dmax - glo - gw, sc);
+    if (ract && st_copy) {
+#pragma unroll
+        for (int f = 0; f < FL; ++f)
+            st_copy[s.slot(f) - sc.out_off] = make_float4(s.yr[f], s.yi[f], s.l0r[f], s.l0i[f]);
+    }
+    const int64_t n = sc.tn, xbase = p.xbase + sc.tb;
+    int chunk_done = 0;
+    float xv[Ring<false, !XLDS>::value][FL];
+    for (int64_t s0 = 0; s0 < n; s0 += p.nb) {
+        const int nbs = (int)min((int64_t)p.nb, n - s0);
+        const float *xw;
+        if (XLDS) {
+            __syncthreads();
+            stage_window(xs, p, xbase + s0, glo, gw, nbs);
+            __syncthreads();
+            xw = xs;
+        } else {
+            xw = p.xwin + (xbase + s0);
+        }
+        if (!wact) continue;
+        if (!plain) fill_ring<FL, false, !XLDS>(s, xv, xw, 0);
+        for (int t0 = 0; t0 < nbs;) {   // whole stretches up to a chunk end
+            const int t1 = min(nbs, t0 + p.L - chunk_done);
+            run_tiles<FL, false, !XLDS>(s, xv, xw, t0, t1, nullptr, lane, plain, [](int, int) {});
+            chunk_done += t1 - t0;
+            t0 = t1;
+            if (chunk_done == p.L) {
+                carry_correct<FL>(s, p.s, p.prec, plain, p.L, p.L);
+                chunk_done = 0;
+            }
         }
     }
+    if (wact && chunk_done) carry_correct<FL>(s, p.s, p.prec, plain, chunk_done, p.L);
     if (ract && sc.st_out) {
 #pragma unroll
         for (int f = 0; f < FL; ++f)
@@ -533,9 +709,7 @@ __device__ __forceinline__ SegCtx whole_launch(const FwdArgs &p) {
     sc.st_out = p.state;
     sc.in_off = 0;
     sc.out_off = 0;
-    sc.zl_out = nullptr;
-    sc.zl_in = nullptr;
-    sc.ld_zl = 0;
+    sc.seg = 0;
     return sc;
 }
 
@@ -544,144 +718,160 @@ __device__ __forceinline__ void hist_copy_at(const HistCopy &hc, int i) {
     hc.new_h[i] = m >= 0 ? hc.x[m] : hc.old_h[hc.dmax + m];
 }
 
-template <int FL, int TT, int MODE, bool XLDS, bool PARTS>
+// A streaming call's last launch also writes the next call's history (hc.dmax >
+// 0); it reads old_h and x only, which the launch does not write.
+__device__ __forceinline__ void hist_copy_all(const HistCopy &hc) {
+    for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < hc.dmax; i += gridDim.x * blockDim.x) hist_copy_at(hc, i);
+}
+
+template <int FL, int MODE, bool XLDS, bool PARTS>
 __global__ void __launch_bounds__(512) fwd_kernel(FwdArgs p) {
     extern __shared__ __align__(16) unsigned char smem[];
-    if constexpr (MODE != kModeKeys) {
-        // a streaming call's last launch also writes the next call's history
-        // (hist_next.dmax > 0); it reads old_h and x only, which this launch
-        // does not write
-        for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < p.hist_next.dmax; i += gridDim.x * blockDim.x)
-            hist_copy_at(p.hist_next, i);
-    }
+    if constexpr (MODE != kModeKeys) hist_copy_all(p.hist_next);
     const SegCtx sc = whole_launch(p);
-    fwd_group<FL, TT, MODE, XLDS, false, PARTS>(p, p.gbase + blockIdx.x, smem, sc);
+    fwd_group<FL, MODE, XLDS, PARTS>(p, p.gbase + blockIdx.x, smem, sc);
 }
 
-// Time split, local pass: item (segment, group). Segment 0 starts from the
-// carried state and writes the mode's output; later segments start cold and
-// keep their local z. Every item stores its end state.
-template <int FL, int TT, int MODE, bool XLDS, bool PARTS>
-__device__ __forceinline__ void seg_item(const FwdArgs &p, unsigned bid, unsigned char *smem) {
-    const int g = p.gbase + bid % p.groups, seg = bid / p.groups;
+// Time split: the launch's samples in nseg segments that run in parallel.
+// Every segment but the last is first run for its states alone (segment 0
+// from the carried state, the others from rest), seg_chain_kernel composes the
+// segments' true start states in FP64, and then every segment runs in full
+// from its true start. The state pass costs 3.2 VALU operations per update; the
+// other way round (every segment in full from rest, then the free response of
+// the true starts added to stored template sums) cost about 6.5 and wrote and
+// read the sums. 64 x 1,000 filters, 16,384 samples, 16 segments: state pass
+// 107 us + full pass 241 us, against 296 + 172 us.
+__device__ __forceinline__ SegCtx segment(const FwdArgs &p, int seg) {
     SegCtx sc;
     sc.tb = (int64_t)seg * p.seg_len;
     sc.tn = min(p.seg_len, p.n - sc.tb);
-    sc.st_in = seg == 0 ? p.state : nullptr;
-    sc.st_out = p.seg_end + (int64_t)seg * p.seg_stride;
-    sc.in_off = 0;
-    sc.out_off = p.seg_slot0;
-    if (MODE == kModeZ) {  // the local z goes straight to the output rows; the carry pass adds to it
-        sc.zl_out = seg == 0 ? nullptr : p.z + p.obase + sc.tb;
-        sc.ld_zl = p.ld;
-    } else {
-        sc.zl_out = seg == 0 ? nullptr : p.zl + (int64_t)(seg - 1) * p.n_templates * p.seg_len;
-        sc.ld_zl = p.seg_len;
-    }
-    sc.zl_in = nullptr;
-    fwd_group<FL, TT, MODE, XLDS, false, PARTS>(p, g, smem, sc);
-}
-
-template <int FL, int TT, int MODE, bool XLDS, bool PARTS>
-__global__ void __launch_bounds__(512) fwd_seg_kernel(FwdArgs p) {
-    extern __shared__ __align__(16) unsigned char smem[];
-    seg_item<FL, TT, MODE, XLDS, PARTS>(p, blockIdx.x, smem);
-}
-
-// Time split, carry pass over segments 1..: free response of the true
-// segment-start state plus the local z, then the mode's output.
-template <int FL, int TT, int MODE, bool PARTS>
-__device__ __forceinline__ void carry_item(const FwdArgs &p, unsigned bid, unsigned char *smem) {
-    const int g = p.gbase + bid % p.groups, seg = 1 + bid / p.groups;
-    SegCtx sc;
-    sc.tb = (int64_t)seg * p.seg_len;
-    sc.tn = min(p.seg_len, p.n - sc.tb);
-    sc.st_in = p.seg_start + (int64_t)seg * p.seg_stride;
+    sc.st_in = nullptr;
     sc.st_out = nullptr;
     sc.in_off = p.seg_slot0;
     sc.out_off = 0;
-    sc.zl_out = nullptr;
-    if (MODE == kModeZ) {
-        sc.zl_in = p.z + p.obase + sc.tb;
-        sc.ld_zl = p.ld;
+    sc.seg = 0;
+    sc.stride = p.seg_stride;
+    sc.len = p.seg_len;
+    return sc;
+}
+
+template <int FL, bool XLDS>
+__device__ __forceinline__ void pre_item(const FwdArgs &p, unsigned bid, unsigned char *smem) {
+    const int g = p.gbase + bid % p.groups, seg = bid / p.groups;
+    SegCtx sc = segment(p, seg);
+    if (seg == 0) {
+        sc.st_in = p.state;
+        sc.in_off = 0;
+    }
+    sc.st_out = p.seg_end + (int64_t)seg * p.seg_stride;
+    sc.out_off = p.seg_slot0;
+    // the full pass overwrites p.state while it runs: its segment 0 starts from this copy
+    state_group<FL, XLDS>(p, g, smem, sc, seg == 0 && p.chain_inline ? p.seg_start : nullptr);
+}
+
+template <int FL, int MODE, bool XLDS, bool PARTS>
+__device__ __forceinline__ void seg_item(const FwdArgs &p, unsigned bid, unsigned char *smem) {
+    const int g = p.gbase + bid % p.groups, seg = bid / p.groups;
+    SegCtx sc = segment(p, seg);
+    if (p.chain_inline && seg > 0) {
+        sc.st_in = p.seg_end;
+        sc.seg = seg;
     } else {
-        sc.zl_in = p.zl + (int64_t)(seg - 1) * p.n_templates * p.seg_len;
-        sc.ld_zl = p.seg_len;
+        sc.st_in = p.seg_start + (int64_t)seg * p.seg_stride;
     }
-    fwd_group<FL, TT, MODE, false, true, PARTS>(p, g, smem, sc);
+    if (sc.tb + sc.tn == p.n) sc.st_out = p.state;
+    fwd_group<FL, MODE, XLDS, PARTS>(p, g, smem, sc);
 }
 
-template <int FL, int TT, int MODE, bool PARTS>
-__global__ void __launch_bounds__(512) fwd_carry_kernel(FwdArgs p) {
+template <int FL, bool XLDS>
+__global__ void __launch_bounds__(512) fwd_pre_kernel(FwdArgs p) {
     extern __shared__ __align__(16) unsigned char smem[];
-    carry_item<FL, TT, MODE, PARTS>(p, blockIdx.x, smem);
+    pre_item<FL, XLDS>(p, blockIdx.x, smem);
 }
 
-// Carries of one slot across the segments of a launch: c holds the true end
-// state of segment 0 on entry; for k >= 1 the true start of segment k is c,
-// then c <- a^{len_k} c + e_k (e_k = segment k's end state from rest), in
-// FP64. Full segments share one a^{seg_len}; the segment-end reads are issued
-// eight at a time ahead of the dependent chain.
-__device__ __forceinline__ void chain_segments(const float4 *seg_end, float4 *seg_start, int64_t nslots, int64_t sl,
-                                               double2 a, int nseg, int64_t seg_len, int64_t n, double &cr,
-                                               double &ci) {
-    const double2 a_full = cpow64(a, (int)seg_len);
-    for (int k0 = 1; k0 < nseg; k0 += 8) {
-        float4 eb[8];
+template <int FL, int MODE, bool XLDS, bool PARTS>
+__global__ void __launch_bounds__(512) fwd_seg_kernel(FwdArgs p) {
+    extern __shared__ __align__(16) unsigned char smem[];
+    if (p.chain_inline) hist_copy_all(p.hist_next);
+    seg_item<FL, MODE, XLDS, PARTS>(p, blockIdx.x, smem);
+}
+
+// True start states of one slot's segments: start[0] = the carried state, c_1 =
+// e_0 (segment 0 ran from the carried state), c_{k+1} = a^seg_len c_k + e_k in
+// FP64 (e_k: segment k's end state from rest; every segment but the last has
+// seg_len samples). A block takes 64 slots; its four waves take a quarter each
+// of up to 64 end states, compose it from rest, exchange the four results and
+// write the states from the true start of their quarter: one read latency and
+// half the dependent chain of a thread per slot (29.7 us for 64 segments).
+__device__ __forceinline__ void chain_segments(const float4 *seg_end, float4 *seg_start, int64_t stride, int64_t sl,
+                                               bool act, float4 state, double2 a, int nseg, int64_t seg_len) {
+    __shared__ double2 loc[4][64];
+    constexpr int kPer = 16;
+    const int lane = threadIdx.x & 63, q = threadIdx.x >> 6;
+    const double2 al = cpow64(a, (int)seg_len);
+    double2 c0 = make_double2(0.0, 0.0);   // true state before end state `base`
+    if (act && q == 0) seg_start[sl] = state;
+    for (int base = 0; base < nseg - 1; base += 4 * kPer) {
+        const int ne = min(4 * kPer, nseg - 1 - base), per = (ne + 3) / 4;
+        const int k0 = min(ne, q * per), cnt = min(ne, k0 + per) - k0;
+        float4 e[kPer];
 #pragma unroll
-        for (int u = 0; u < 8; ++u)
-            if (k0 + u < nseg) eb[u] = seg_end[(int64_t)(k0 + u) * nslots + sl];
+        for (int u = 0; u < kPer; ++u)
+            if (act && u < cnt) e[u] = seg_end[(int64_t)(base + k0 + u) * stride + sl];
+        double2 c = make_double2(0.0, 0.0);
 #pragma unroll
-        for (int u = 0; u < 8; ++u) {
-            const int k = k0 + u;
-            if (k >= nseg) break;
-            const float hr = (float)cr, hi = (float)ci;
-            seg_start[(int64_t)k * nslots + sl] =
-                make_float4(hr, hi, (float)(cr - (double)hr), (float)(ci - (double)hi));
-            const int64_t len = min(seg_len, n - (int64_t)k * seg_len);
-            const double2 al = len == seg_len ? a_full : cpow64(a, (int)len);
-            const float4 e = eb[u];
-            const double er = (double)e.x + (double)e.z, ei = (double)e.y + (double)e.w;
-            const double nr = al.x * cr - al.y * ci + er;
-            const double ni = al.x * ci + al.y * cr + ei;
-            cr = nr;
-            ci = ni;
+        for (int u = 0; u < kPer; ++u)
+            if (act && u < cnt) chain_step(c, al, e[u]);
+        __syncthreads();   // the exchange of the previous 64
+        loc[q][lane] = c;
+        __syncthreads();
+        const double2 ap = cpow64(al, per);
+        c = c0;
+        for (int k = 0; k < 4; ++k) {   // quarters before a non-empty one hold `per` end states
+            const double2 m = cmul64(ap, c0), t = loc[k][lane];
+            c0 = make_double2(m.x + t.x, m.y + t.y);
+            if (k + 1 == q) c = c0;
         }
+#pragma unroll
+        for (int u = 0; u < kPer; ++u)
+            if (act && u < cnt) {
+                chain_step(c, al, e[u]);
+                seg_start[(int64_t)(base + k0 + u + 1) * stride + sl] = hi_lo(c);
+            }
     }
 }
 
-// Time split, carry chain: c_{s+1} = a^len_s c_s + e_s in FP64 per slot, from
-// the true end of segment 0; writes every segment's true start state and the
-// launch's final state. Covers slots [seg_slot0, seg_slot0 + seg_stride) of
+// What a carried state is multiplied by per sample in the chain: a, or the
+// rounded coefficient in the all-FP32 mode.
+__device__ __forceinline__ double2 chain_coeff(const FwdArgs &p, int64_t sl) {
+    return p.prec == kPrecFp32 ? f64c(p.s.a32[sl]) : p.s.a64[sl];
+}
+
+// Time split, carry chain over slots [seg_slot0, seg_slot0 + seg_stride) of
 // the segment buffers; with only_tpl >= 0 only that template's slots (the
-// other slots' entries were not written by the segment pass).
+// other slots' entries were not written by the state pass).
 __device__ __forceinline__ void chain_item(const FwdArgs &p, int fl, int nseg, unsigned chain_blocks, unsigned bid) {
     if (bid >= chain_blocks) {   // the history copy (hist_next.dmax > 0), 256 samples per block
         const int i = (int)(bid - chain_blocks) * 256 + (int)threadIdx.x;
         if (i < p.hist_next.dmax) hist_copy_at(p.hist_next, i);
         return;
     }
-    const int64_t i = (int64_t)bid * blockDim.x + threadIdx.x;
-    if (i >= p.seg_stride) return;  // every slot, padding included (its states stay zero)
-    const int64_t sl = p.seg_slot0 + i;
-    if (p.only_tpl >= 0) {
+    const int64_t i = (int64_t)bid * 64 + (threadIdx.x & 63), sl = p.seg_slot0 + i;
+    bool act = i < p.seg_stride;  // every slot, padding included (its states stay zero)
+    if (act && p.only_tpl >= 0) {
         // slot = ((group * wpg + wave) * fl + f) * 64 + lane; row = 4 (group * wpg + wave) + lane / 16
-        const RowInfo ri = p.rows[((sl >> 6) / fl) * 4 + ((sl & 63) >> 4)];
-        if (ri.tpl != p.only_tpl) return;
+        act = p.rows[((sl >> 6) / fl) * 4 + ((sl & 63) >> 4)].tpl == p.only_tpl;
     }
-    const float4 e0 = p.seg_end[i];
-    double cr = (double)e0.x + (double)e0.z, ci = (double)e0.y + (double)e0.w;
-    double2 a = p.s.a64[sl];
-    if (p.prec == kPrecFp32) {  // the all-FP32 mode propagates with the rounded coefficient
-        const float2 r = p.s.a32[sl];
-        a = make_double2((double)r.x, (double)r.y);
+    float4 st = make_float4(0.f, 0.f, 0.f, 0.f);
+    double2 a = make_double2(0.0, 0.0);
+    if (act) {
+        st = p.state[sl];
+        a = chain_coeff(p, sl);
     }
-    chain_segments(p.seg_end, p.seg_start, p.seg_stride, i, a, nseg, p.seg_len, p.n, cr, ci);
-    const float hr = (float)cr, hi = (float)ci;
-    p.state[sl] = make_float4(hr, hi, (float)(cr - (double)hr), (float)(ci - (double)hi));
+    chain_segments(p.seg_end, p.seg_start, p.seg_stride, i, act, st, a, nseg, p.seg_len);
 }
 
-__global__ void seg_chain_kernel(FwdArgs p, int fl, int nseg, unsigned chain_blocks) {
+__global__ void __launch_bounds__(256) seg_chain_kernel(FwdArgs p, int fl, int nseg, unsigned chain_blocks) {
     chain_item(p, fl, nseg, chain_blocks, blockIdx.x);
 }
 
@@ -694,18 +884,18 @@ __device__ __forceinline__ int multi_bank(const int32_t *first, int count) {
     return b;
 }
 
-template <int FL, int TT, int MODE>
+template <int FL>
+__global__ void __launch_bounds__(512) fwd_pre_multi_kernel(MultiFwd m) {
+    extern __shared__ __align__(16) unsigned char smem[];
+    const int b = multi_bank(m.pre_first, m.count);
+    pre_item<FL, true>(m.a[b], blockIdx.x - (unsigned)m.pre_first[b], smem);
+}
+
+template <int FL, int MODE>
 __global__ void __launch_bounds__(512) fwd_seg_multi_kernel(MultiFwd m) {
     extern __shared__ __align__(16) unsigned char smem[];
     const int b = multi_bank(m.seg_first, m.count);
-    seg_item<FL, TT, MODE, true, false>(m.a[b], blockIdx.x - (unsigned)m.seg_first[b], smem);
-}
-
-template <int FL, int TT, int MODE>
-__global__ void __launch_bounds__(512) fwd_carry_multi_kernel(MultiFwd m) {
-    extern __shared__ __align__(16) unsigned char smem[];
-    const int b = multi_bank(m.carry_first, m.count);
-    carry_item<FL, TT, MODE, false>(m.a[b], blockIdx.x - (unsigned)m.carry_first[b], smem);
+    seg_item<FL, MODE, true, false>(m.a[b], blockIdx.x - (unsigned)m.seg_first[b], smem);
 }
 
 __global__ void __launch_bounds__(256) seg_chain_multi_kernel(MultiFwd m, int fl) {
@@ -715,7 +905,7 @@ __global__ void __launch_bounds__(256) seg_chain_multi_kernel(MultiFwd m, int fl
 
 // Persistent batch kernel: workgroups pop (stream, group) items until the list
 // is exhausted; every item is one block of one stream for one group.
-template <int FL, int TT>
+template <int FL>
 __global__ void __launch_bounds__(512) batch_kernel(const BatchStream *streams, const int2 *items,
                                                     int nitems, int *counter, const int64_t *pos,
                                                     int block_len) {
@@ -738,7 +928,7 @@ __global__ void __launch_bounds__(512) batch_kernel(const BatchStream *streams, 
         a.n = min((int64_t)block_len, len - p0);
         a.ld = block_len;
         const SegCtx sc = whole_launch(a);
-        fwd_group<FL, TT, kModeKeys, true, false>(a, g, smem, sc);
+        fwd_group<FL, kModeKeys, true, false>(a, g, smem, sc);
     }
 }
 
@@ -746,67 +936,44 @@ __global__ void __launch_bounds__(512) batch_kernel(const BatchStream *streams, 
 // live streams alone cannot fill the device). Items are (stream, group << 4 |
 // segment), one workgroup each; items of ended streams or of segments past the
 // block's end exit at once. Per-stream segment buffers hang off the stream's
-// FwdArgs (seg_end, seg_start, zl, seg_len).
+// FwdArgs (seg_end, seg_start, seg_len).
 __device__ __forceinline__ bool batch_item(const BatchStream *streams, const int2 *items, const int64_t *pos,
-                                           int block_len, int &sidx, int &g, int &seg, int64_t &p0,
-                                           int64_t &n) {
+                                           int block_len, FwdArgs &a, int &g, int &seg) {
     const int2 item = items[blockIdx.x];
-    sidx = __builtin_amdgcn_readfirstlane(item.x);
+    const int sidx = __builtin_amdgcn_readfirstlane(item.x);
     g = __builtin_amdgcn_readfirstlane(item.y >> 4);
     seg = __builtin_amdgcn_readfirstlane(item.y & 15);
-    p0 = pos[sidx];
-    const int64_t len = streams[sidx].len;
+    const int64_t p0 = pos[sidx], len = streams[sidx].len;
     if (p0 >= len) return false;
-    n = min((int64_t)block_len, len - p0);
-    return (int64_t)seg * streams[sidx].args.seg_len < n;
+    a = streams[sidx].args;
+    a.xbase = p0;
+    a.n = min((int64_t)block_len, len - p0);
+    a.ld = block_len;
+    a.gbase = 0;
+    a.seg_slot0 = 0;
+    a.seg_stride = a.nslots;
+    return (int64_t)seg * a.seg_len < a.n;
 }
 
-template <int FL, int TT>
+template <int FL>
+__global__ void __launch_bounds__(512) batch_pre_kernel(const BatchStream *streams, const int2 *items,
+                                                        const int64_t *pos, int block_len) {
+    extern __shared__ __align__(16) unsigned char smem[];
+    FwdArgs a;
+    int g, seg;
+    if (!batch_item(streams, items, pos, block_len, a, g, seg)) return;
+    if ((int64_t)(seg + 1) * a.seg_len >= a.n) return;   // the block's last segment needs no end state
+    pre_item<FL, true>(a, (unsigned)(seg * a.groups + g), smem);
+}
+
+template <int FL>
 __global__ void __launch_bounds__(512) batch_seg_kernel(const BatchStream *streams, const int2 *items,
                                                         const int64_t *pos, int block_len) {
     extern __shared__ __align__(16) unsigned char smem[];
-    int sidx, g, seg;
-    int64_t p0, n;
-    if (!batch_item(streams, items, pos, block_len, sidx, g, seg, p0, n)) return;
-    FwdArgs a = streams[sidx].args;
-    a.xbase = p0;
-    a.n = n;
-    a.ld = block_len;
-    SegCtx sc;
-    sc.tb = (int64_t)seg * a.seg_len;
-    sc.tn = min(a.seg_len, n - sc.tb);
-    sc.st_in = seg == 0 ? a.state : nullptr;
-    sc.st_out = a.seg_end + (int64_t)seg * a.nslots;
-    sc.in_off = 0;
-    sc.out_off = 0;
-    sc.zl_out = seg == 0 ? nullptr : a.zl + (int64_t)(seg - 1) * a.n_templates * a.seg_len;
-    sc.zl_in = nullptr;
-    sc.ld_zl = a.seg_len;
-    fwd_group<FL, TT, kModeKeys, true, false>(a, g, smem, sc);
-}
-
-template <int FL, int TT>
-__global__ void __launch_bounds__(512) batch_carry_kernel(const BatchStream *streams, const int2 *items,
-                                                          const int64_t *pos, int block_len) {
-    extern __shared__ __align__(16) unsigned char smem[];
-    int sidx, g, seg;
-    int64_t p0, n;
-    if (!batch_item(streams, items, pos, block_len, sidx, g, seg, p0, n)) return;
-    FwdArgs a = streams[sidx].args;
-    a.xbase = p0;
-    a.n = n;
-    a.ld = block_len;
-    SegCtx sc;
-    sc.tb = (int64_t)seg * a.seg_len;
-    sc.tn = min(a.seg_len, n - sc.tb);
-    sc.st_in = a.seg_start + (int64_t)seg * a.nslots;
-    sc.st_out = nullptr;
-    sc.in_off = 0;
-    sc.out_off = 0;
-    sc.zl_out = nullptr;
-    sc.zl_in = a.zl + (int64_t)(seg - 1) * a.n_templates * a.seg_len;
-    sc.ld_zl = a.seg_len;
-    fwd_group<FL, TT, kModeKeys, false, true>(a, g, smem, sc);
+    FwdArgs a;
+    int g, seg;
+    if (!batch_item(streams, items, pos, block_len, a, g, seg)) return;
+    seg_item<FL, kModeKeys, true, false>(a, (unsigned)(seg * a.groups + g), smem);
 }
 
 // FP64 carry chain of every live stream (grid.y = stream): the same
@@ -815,22 +982,19 @@ __global__ void __launch_bounds__(256) batch_chain_kernel(const BatchStream *str
                                                           int block_len) {
     const int sidx = blockIdx.y;
     const FwdArgs &a = streams[sidx].args;
-    const int64_t sl = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (sl >= a.nslots) return;
+    const int64_t sl = (int64_t)blockIdx.x * 64 + (threadIdx.x & 63);
     const int64_t p0 = pos[sidx], len = streams[sidx].len;
-    if (p0 >= len) return;
+    if (p0 >= len || (int64_t)blockIdx.x * 64 >= a.nslots) return;
     const int64_t n = min((int64_t)block_len, len - p0);
     const int nv = (int)((n + a.seg_len - 1) / a.seg_len);
-    const float4 e0 = a.seg_end[sl];
-    double cr = (double)e0.x + (double)e0.z, ci = (double)e0.y + (double)e0.w;
-    double2 av = a.s.a64[sl];
-    if (a.prec == kPrecFp32) {
-        const float2 r = a.s.a32[sl];
-        av = make_double2((double)r.x, (double)r.y);
+    const bool act = sl < a.nslots;   // whole waves: a bank's slot count is a multiple of 64
+    float4 st = make_float4(0.f, 0.f, 0.f, 0.f);
+    double2 av = make_double2(0.0, 0.0);
+    if (act) {
+        st = a.state[sl];
+        av = chain_coeff(a, sl);
     }
-    chain_segments(a.seg_end, a.seg_start, a.nslots, sl, av, nv, a.seg_len, n, cr, ci);
-    const float hr = (float)cr, hi = (float)ci;
-    a.state[sl] = make_float4(hr, hi, (float)(cr - (double)hr), (float)(ci - (double)hi));
+    chain_segments(a.seg_end, a.seg_start, a.nslots, sl, act, st, av, nv, a.seg_len);
 }
 
 // Max over workgroup partial keys: 16 samples x 16 group slices per block.
@@ -896,9 +1060,22 @@ __global__ void __launch_bounds__(256) combine_parts_kernel(const float2 *zpart,
     if (mode == kModeKeys) key_row[t] = kbest;
 }
 
-// Slot arrays from caller-order FP64 coefficients on the device (the same
-// values the host plan computes: fl32 roundings, a^L and a^L - fl32(a)^L in
-// FP64, the FP64-carry flag). Padding slots keep their zeros.
+// a^L minus what the FP32 recursion multiplies a carried state by over a chunk.
+__device__ __forceinline__ double2 chunk_drift(double2 a, float2 b, int L) {
+    const RotCoeffs r = rot_coeffs(a, b);
+    const double2 p = cpow64(a, L), q = rot_pow(r.a4, r.v, L);
+    return make_double2(p.x - q.x, p.y - q.y);
+}
+
+__global__ void __launch_bounds__(256) chunk_drift_kernel(const double2 *a64, const float2 *b32, int64_t nslots,
+                                                          int L, double2 *dL) {
+    const int64_t sl = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (sl < nslots) dL[sl] = chunk_drift(a64[sl], b32[sl], L);
+}
+
+// Slot arrays from caller-order FP64 coefficients on the device (fl32
+// roundings, a^L and the chunk drift in FP64, the FP64-carry flag). Padding
+// slots keep their zeros.
 __global__ void __launch_bounds__(256) set_coeffs_kernel(const double2 *a, const double2 *b,
                                                          const int32_t *slot_filter, int64_t nslots, int L,
                                                          float2 *a32, float2 *b32, double2 *aL, double2 *dL,
@@ -911,9 +1088,8 @@ __global__ void __launch_bounds__(256) set_coeffs_kernel(const double2 *a, const
     const float2 af = make_float2((float)av.x, (float)av.y);
     a32[sl] = af;
     b32[sl] = make_float2((float)bv.x, (float)bv.y);
-    const double2 p = cpow64(av, L), q = cpow64(make_double2((double)af.x, (double)af.y), L);
-    aL[sl] = p;
-    dL[sl] = make_double2(p.x - q.x, p.y - q.y);
+    aL[sl] = cpow64(av, L);
+    dL[sl] = chunk_drift(av, b32[sl], L);
     a64[sl] = av;
     flags[sl] = hypot(av.x, av.y) > 1.0 - 1e-5 ? 1 : 0;
 }
@@ -1414,90 +1590,86 @@ __global__ void batch_advance_kernel(int64_t *pos, const BatchStream *streams, i
     }
 }
 
-template <int FL, int TT, int MODE, bool XLDS>
+template <int FL, int MODE, bool XLDS>
 hipError_t launch_fwd_t(const FwdArgs &a, int groups, size_t lds, hipStream_t st, KernelEvents ev) {
     if (a.zpart)
-        hipExtLaunchKernelGGL((fwd_kernel<FL, TT, MODE, XLDS, true>), dim3(groups), dim3(a.wpg * 64), (uint32_t)lds,
+        hipExtLaunchKernelGGL((fwd_kernel<FL, MODE, XLDS, true>), dim3(groups), dim3(a.wpg * 64), (uint32_t)lds,
                               st, ev.start, ev.stop, 0u, a);
     else
-        hipExtLaunchKernelGGL((fwd_kernel<FL, TT, MODE, XLDS, false>), dim3(groups), dim3(a.wpg * 64), (uint32_t)lds,
+        hipExtLaunchKernelGGL((fwd_kernel<FL, MODE, XLDS, false>), dim3(groups), dim3(a.wpg * 64), (uint32_t)lds,
                               st, ev.start, ev.stop, 0u, a);
     return hipGetLastError();
 }
 
-template <int TT, int MODE, bool XLDS>
+template <int MODE, bool XLDS>
 hipError_t launch_fwd_m(const FwdArgs &a, int fl, int groups, size_t lds, hipStream_t st, KernelEvents ev) {
     switch (fl) {
-        case 1: return launch_fwd_t<1, TT, MODE, XLDS>(a, groups, lds, st, ev);
-        case 2: return launch_fwd_t<2, TT, MODE, XLDS>(a, groups, lds, st, ev);
-        case 3: return launch_fwd_t<3, TT, MODE, XLDS>(a, groups, lds, st, ev);
-        case 4: return launch_fwd_t<4, TT, MODE, XLDS>(a, groups, lds, st, ev);
+        case 1: return launch_fwd_t<1, MODE, XLDS>(a, groups, lds, st, ev);
+        case 2: return launch_fwd_t<2, MODE, XLDS>(a, groups, lds, st, ev);
+        case 3: return launch_fwd_t<3, MODE, XLDS>(a, groups, lds, st, ev);
+        case 4: return launch_fwd_t<4, MODE, XLDS>(a, groups, lds, st, ev);
         default: return hipErrorInvalidValue;
     }
 }
 
-template <int TT, bool XLDS>
+template <bool XLDS>
 hipError_t launch_fwd_x(const FwdArgs &a, int mode, int fl, int groups, size_t lds, hipStream_t st,
                         KernelEvents ev) {
     switch (mode) {
-        case kModeSnr: return launch_fwd_m<TT, kModeSnr, XLDS>(a, fl, groups, lds, st, ev);
-        case kModeKeys: return launch_fwd_m<TT, kModeKeys, XLDS>(a, fl, groups, lds, st, ev);
-        case kModeZ: return launch_fwd_m<TT, kModeZ, XLDS>(a, fl, groups, lds, st, ev);
+        case kModeSnr: return launch_fwd_m<kModeSnr, XLDS>(a, fl, groups, lds, st, ev);
+        case kModeKeys: return launch_fwd_m<kModeKeys, XLDS>(a, fl, groups, lds, st, ev);
+        case kModeZ: return launch_fwd_m<kModeZ, XLDS>(a, fl, groups, lds, st, ev);
         default: return hipErrorInvalidValue;
     }
 }
 
-template <int FL, int TT, int MODE, bool XLDS>
-hipError_t launch_split_t(const FwdArgs &a, int nseg, size_t lds, size_t lds_carry, const int32_t *slot_filter,
-                          hipStream_t st, KernelEvents ev) {
-    if (a.zpart)
-        hipExtLaunchKernelGGL((fwd_seg_kernel<FL, TT, MODE, XLDS, true>), dim3(a.groups * nseg), dim3(a.wpg * 64),
-                              (uint32_t)lds, st, ev.start, (hipEvent_t) nullptr, 0u, a);
-    else
-        hipExtLaunchKernelGGL((fwd_seg_kernel<FL, TT, MODE, XLDS, false>), dim3(a.groups * nseg), dim3(a.wpg * 64),
-                              (uint32_t)lds, st, ev.start, (hipEvent_t) nullptr, 0u, a);
+template <int FL, int MODE, bool XLDS>
+hipError_t launch_split_t(const FwdArgs &a, int nseg, size_t lds, size_t lds_pre, hipStream_t st, KernelEvents ev) {
+    hipExtLaunchKernelGGL((fwd_pre_kernel<FL, XLDS>), dim3(a.groups * (nseg - 1)), dim3(a.wpg * 64),
+                          (uint32_t)lds_pre, st, ev.start, (hipEvent_t) nullptr, 0u, a);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    const unsigned nb = (unsigned)((a.seg_stride + 255) / 256);
-    const unsigned hb = a.hist_next.dmax > 0 ? (unsigned)((a.hist_next.dmax + 255) / 256) : 0u;
-    (void)slot_filter;
-    hipLaunchKernelGGL(seg_chain_kernel, dim3(nb + hb), dim3(256), 0, st, a, FL, nseg, nb);
-    e = hipGetLastError();
-    if (e != hipSuccess) return e;
+    if (!a.chain_inline) {
+        const unsigned nb = (unsigned)((a.seg_stride + 63) / 64);
+        const unsigned hb = a.hist_next.dmax > 0 ? (unsigned)((a.hist_next.dmax + 255) / 256) : 0u;
+        hipLaunchKernelGGL(seg_chain_kernel, dim3(nb + hb), dim3(256), 0, st, a, FL, nseg, nb);
+        e = hipGetLastError();
+        if (e != hipSuccess) return e;
+    }
     if (a.zpart)
-        hipExtLaunchKernelGGL((fwd_carry_kernel<FL, TT, MODE, true>), dim3(a.groups * (nseg - 1)), dim3(a.wpg * 64),
-                              (uint32_t)lds_carry, st, (hipEvent_t) nullptr, ev.stop, 0u, a);
+        hipExtLaunchKernelGGL((fwd_seg_kernel<FL, MODE, XLDS, true>), dim3(a.groups * nseg), dim3(a.wpg * 64),
+                              (uint32_t)lds, st, (hipEvent_t) nullptr, ev.stop, 0u, a);
     else
-        hipExtLaunchKernelGGL((fwd_carry_kernel<FL, TT, MODE, false>), dim3(a.groups * (nseg - 1)), dim3(a.wpg * 64),
-                              (uint32_t)lds_carry, st, (hipEvent_t) nullptr, ev.stop, 0u, a);
+        hipExtLaunchKernelGGL((fwd_seg_kernel<FL, MODE, XLDS, false>), dim3(a.groups * nseg), dim3(a.wpg * 64),
+                              (uint32_t)lds, st, (hipEvent_t) nullptr, ev.stop, 0u, a);
     return hipGetLastError();
 }
 
-template <int TT, int MODE, bool XLDS>
-hipError_t launch_split_m(const FwdArgs &a, int fl, int nseg, size_t lds, size_t ldc, const int32_t *sf,
-                          hipStream_t st, KernelEvents ev) {
+template <int MODE, bool XLDS>
+hipError_t launch_split_m(const FwdArgs &a, int fl, int nseg, size_t lds, size_t ldp, hipStream_t st,
+                          KernelEvents ev) {
     switch (fl) {
-        case 1: return launch_split_t<1, TT, MODE, XLDS>(a, nseg, lds, ldc, sf, st, ev);
-        case 2: return launch_split_t<2, TT, MODE, XLDS>(a, nseg, lds, ldc, sf, st, ev);
-        case 3: return launch_split_t<3, TT, MODE, XLDS>(a, nseg, lds, ldc, sf, st, ev);
-        case 4: return launch_split_t<4, TT, MODE, XLDS>(a, nseg, lds, ldc, sf, st, ev);
+        case 1: return launch_split_t<1, MODE, XLDS>(a, nseg, lds, ldp, st, ev);
+        case 2: return launch_split_t<2, MODE, XLDS>(a, nseg, lds, ldp, st, ev);
+        case 3: return launch_split_t<3, MODE, XLDS>(a, nseg, lds, ldp, st, ev);
+        case 4: return launch_split_t<4, MODE, XLDS>(a, nseg, lds, ldp, st, ev);
         default: return hipErrorInvalidValue;
     }
 }
 
-template <int TT, bool XLDS>
-hipError_t launch_split_x(const FwdArgs &a, int mode, int fl, int nseg, size_t lds, size_t ldc, const int32_t *sf,
-                          hipStream_t st, KernelEvents ev) {
-    if (mode == kModeSnr) return launch_split_m<TT, kModeSnr, XLDS>(a, fl, nseg, lds, ldc, sf, st, ev);
-    if (mode == kModeKeys) return launch_split_m<TT, kModeKeys, XLDS>(a, fl, nseg, lds, ldc, sf, st, ev);
-    if (mode == kModeZ) return launch_split_m<TT, kModeZ, XLDS>(a, fl, nseg, lds, ldc, sf, st, ev);
+template <bool XLDS>
+hipError_t launch_split_x(const FwdArgs &a, int mode, int fl, int nseg, size_t lds, size_t ldp, hipStream_t st,
+                          KernelEvents ev) {
+    if (mode == kModeSnr) return launch_split_m<kModeSnr, XLDS>(a, fl, nseg, lds, ldp, st, ev);
+    if (mode == kModeKeys) return launch_split_m<kModeKeys, XLDS>(a, fl, nseg, lds, ldp, st, ev);
+    if (mode == kModeZ) return launch_split_m<kModeZ, XLDS>(a, fl, nseg, lds, ldp, st, ev);
     return hipErrorInvalidValue;
 }
 
-template <int FL, int TT>
+template <int FL>
 int occ_t(int wpg, size_t lds) {
     int nb = 0;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, fwd_kernel<FL, TT, kModeKeys, true, false>, wpg * 64, lds) !=
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, fwd_kernel<FL, kModeKeys, true, false>, wpg * 64, lds) !=
         hipSuccess)
         return 0;
     return nb;
@@ -1507,86 +1679,91 @@ inline unsigned nblocks(int64_t n, int bs) { return (unsigned)((n + bs - 1) / bs
 
 }  // namespace
 
-hipError_t launch_forward(const FwdArgs &a, int mode, int fl, int tt, bool x_in_lds, int groups,
-                          size_t lds, hipStream_t st, KernelEvents ev) {
+hipError_t launch_forward(const FwdArgs &a, int mode, int fl, bool x_in_lds, int groups, size_t lds, hipStream_t st,
+                          KernelEvents ev) {
     if (groups <= 0) return hipSuccess;
-    if (tt == 16)
-        return x_in_lds ? launch_fwd_x<16, true>(a, mode, fl, groups, lds, st, ev)
-                        : launch_fwd_x<16, false>(a, mode, fl, groups, lds, st, ev);
-    if (tt == 8)
-        return x_in_lds ? launch_fwd_x<8, true>(a, mode, fl, groups, lds, st, ev)
-                        : launch_fwd_x<8, false>(a, mode, fl, groups, lds, st, ev);
-    return hipErrorInvalidValue;
+    return x_in_lds ? launch_fwd_x<true>(a, mode, fl, groups, lds, st, ev)
+                    : launch_fwd_x<false>(a, mode, fl, groups, lds, st, ev);
 }
 
-hipError_t launch_forward_split(const FwdArgs &a, int mode, int fl, int tt, bool x_in_lds, int nseg, size_t lds,
-                                size_t lds_carry, const int32_t *slot_filter, hipStream_t st,
-                                KernelEvents ev) {
-    if (a.groups <= 0 || nseg < 2) return hipErrorInvalidValue;
-    if (tt == 16)
-        return x_in_lds ? launch_split_x<16, true>(a, mode, fl, nseg, lds, lds_carry, slot_filter, st, ev)
-                        : launch_split_x<16, false>(a, mode, fl, nseg, lds, lds_carry, slot_filter, st, ev);
-    if (tt == 8)
-        return x_in_lds ? launch_split_x<8, true>(a, mode, fl, nseg, lds, lds_carry, slot_filter, st, ev)
-                        : launch_split_x<8, false>(a, mode, fl, nseg, lds, lds_carry, slot_filter, st, ev);
-    return hipErrorInvalidValue;
+// The state pass needs the strain window only (so more workgroups share a compute unit).
+size_t state_pass_lds(const FwdArgs &a, bool x_in_lds) { return x_in_lds ? window_bytes(a.band_w, a.nb) : 0; }
+
+hipError_t launch_forward_split(const FwdArgs &args, int mode, int fl, bool x_in_lds, int nseg, size_t lds,
+                                hipStream_t st, KernelEvents ev) {
+    if (args.groups <= 0 || nseg < 2) return hipErrorInvalidValue;
+    FwdArgs a = args;
+    a.chain_inline = nseg <= kChainInline ? 1 : 0;
+    const size_t lds_pre = state_pass_lds(a, x_in_lds);
+    return x_in_lds ? launch_split_x<true>(a, mode, fl, nseg, lds, lds_pre, st, ev)
+                    : launch_split_x<false>(a, mode, fl, nseg, lds, lds_pre, st, ev);
 }
 
 namespace {
 
-template <int FL, int TT>
-hipError_t launch_multi_t(const MultiFwd &m, int wpg, size_t lds, size_t lds_carry, hipStream_t st) {
+template <int FL>
+hipError_t launch_multi_t(const MultiFwd &m, int wpg, size_t lds, size_t lds_pre, hipStream_t st) {
     const int n = m.count;
-    hipLaunchKernelGGL((fwd_seg_multi_kernel<FL, TT, kModeZ>), dim3((unsigned)m.seg_first[n]), dim3(wpg * 64), lds,
-                       st, m);
+    hipLaunchKernelGGL((fwd_pre_multi_kernel<FL>), dim3((unsigned)m.pre_first[n]), dim3(wpg * 64), lds_pre, st, m);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(seg_chain_multi_kernel, dim3((unsigned)m.chain_first[n]), dim3(256), 0, st, m, FL);
     e = hipGetLastError();
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL((fwd_carry_multi_kernel<FL, TT, kModeZ>), dim3((unsigned)m.carry_first[n]), dim3(wpg * 64),
-                       lds_carry, st, m);
+    hipLaunchKernelGGL((fwd_seg_multi_kernel<FL, kModeZ>), dim3((unsigned)m.seg_first[n]), dim3(wpg * 64), lds,
+                       st, m);
     return hipGetLastError();
-}
-
-template <int TT>
-hipError_t launch_multi_f(const MultiFwd &m, int fl, int wpg, size_t lds, size_t lds_carry, hipStream_t st) {
-    switch (fl) {
-        case 1: return launch_multi_t<1, TT>(m, wpg, lds, lds_carry, st);
-        case 2: return launch_multi_t<2, TT>(m, wpg, lds, lds_carry, st);
-        case 3: return launch_multi_t<3, TT>(m, wpg, lds, lds_carry, st);
-        case 4: return launch_multi_t<4, TT>(m, wpg, lds, lds_carry, st);
-        default: return hipErrorInvalidValue;
-    }
 }
 
 }  // namespace
 
-hipError_t launch_forward_split_multi(const MultiFwd &m, int fl, int tt, int wpg, size_t lds, size_t lds_carry,
-                                      hipStream_t st) {
+hipError_t launch_forward_split_multi(const MultiFwd &m, int fl, int wpg, size_t lds, hipStream_t st) {
     if (m.count < 1 || m.count > kMultiMax) return hipErrorInvalidValue;
-    if (tt == 16) return launch_multi_f<16>(m, fl, wpg, lds, lds_carry, st);
-    if (tt == 8) return launch_multi_f<8>(m, fl, wpg, lds, lds_carry, st);
-    return hipErrorInvalidValue;
+    size_t lds_pre = 0;
+    for (int b = 0; b < m.count; ++b) {
+        const size_t l = state_pass_lds(m.a[b], true);
+        lds_pre = l > lds_pre ? l : lds_pre;
+    }
+    switch (fl) {
+        case 1: return launch_multi_t<1>(m, wpg, lds, lds_pre, st);
+        case 2: return launch_multi_t<2>(m, wpg, lds, lds_pre, st);
+        case 3: return launch_multi_t<3>(m, wpg, lds, lds_pre, st);
+        case 4: return launch_multi_t<4>(m, wpg, lds, lds_pre, st);
+        default: return hipErrorInvalidValue;
+    }
 }
 
-int forward_occupancy(int fl, int tt, int wpg, size_t lds) {
-    if (tt == 16) {
-        switch (fl) {
-            case 1: return occ_t<1, 16>(wpg, lds);
-            case 2: return occ_t<2, 16>(wpg, lds);
-            case 3: return occ_t<3, 16>(wpg, lds);
-            case 4: return occ_t<4, 16>(wpg, lds);
-        }
-    } else {
-        switch (fl) {
-            case 1: return occ_t<1, 8>(wpg, lds);
-            case 2: return occ_t<2, 8>(wpg, lds);
-            case 3: return occ_t<3, 8>(wpg, lds);
-            case 4: return occ_t<4, 8>(wpg, lds);
-        }
+int forward_occupancy(int fl, int wpg, size_t lds) {
+    switch (fl) {
+        case 1: return occ_t<1>(wpg, lds);
+        case 2: return occ_t<2>(wpg, lds);
+        case 3: return occ_t<3>(wpg, lds);
+        case 4: return occ_t<4>(wpg, lds);
+        default: return 0;
     }
-    return 0;
+}
+
+namespace {
+
+template <int FL>
+int pre_occ_t(int wpg, size_t lds, bool x_in_lds) {
+    int nb = 0;
+    const hipError_t e = x_in_lds ? hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, fwd_pre_kernel<FL, true>, wpg * 64, lds)
+                                  : hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, fwd_pre_kernel<FL, false>, wpg * 64, lds);
+    return e == hipSuccess ? nb : 0;
+}
+
+}  // namespace
+
+int state_occupancy(int fl, int wpg, const FwdArgs &a, bool x_in_lds) {
+    const size_t lds = state_pass_lds(a, x_in_lds);
+    switch (fl) {
+        case 1: return pre_occ_t<1>(wpg, lds, x_in_lds);
+        case 2: return pre_occ_t<2>(wpg, lds, x_in_lds);
+        case 3: return pre_occ_t<3>(wpg, lds, x_in_lds);
+        case 4: return pre_occ_t<4>(wpg, lds, x_in_lds);
+        default: return 0;
+    }
 }
 
 hipError_t launch_finalize_keys(const uint64_t *keys, int groups, int64_t ld, int64_t n,
@@ -1620,6 +1797,13 @@ hipError_t launch_set_coeffs(const double *a, const double *b, const int32_t *sl
     return hipGetLastError();
 }
 
+hipError_t launch_chunk_drift(const double2 *a64, const float2 *b32, int64_t nslots, int L, double2 *dL,
+                              hipStream_t st) {
+    if (nslots <= 0) return hipSuccess;
+    hipLaunchKernelGGL(chunk_drift_kernel, dim3(nblocks(nslots, 256)), dim3(256), 0, st, a64, b32, nslots, L, dL);
+    return hipGetLastError();
+}
+
 hipError_t launch_rows_argmax(const float *snr, int T, int64_t ld, int64_t n, float *mx,
                               int32_t *am, hipStream_t st) {
     if (n <= 0) return hipSuccess;
@@ -1644,24 +1828,20 @@ hipError_t launch_window_fill(float *xwin, const float *hist, const float *x, in
     return hipGetLastError();
 }
 
-template <int FL, int TT>
+template <int FL>
 int bocc_t(int wpg, size_t lds) {
     int nb = 0;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, batch_kernel<FL, TT>, wpg * 64, lds) != hipSuccess)
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, batch_kernel<FL>, wpg * 64, lds) != hipSuccess)
         return 0;
     return nb;
 }
 
-int batch_occupancy(int fl, int tt, int wpg, size_t lds) {
-    switch (fl * 100 + tt) {
-        case 108: return bocc_t<1, 8>(wpg, lds);
-        case 208: return bocc_t<2, 8>(wpg, lds);
-        case 308: return bocc_t<3, 8>(wpg, lds);
-        case 408: return bocc_t<4, 8>(wpg, lds);
-        case 116: return bocc_t<1, 16>(wpg, lds);
-        case 216: return bocc_t<2, 16>(wpg, lds);
-        case 316: return bocc_t<3, 16>(wpg, lds);
-        case 416: return bocc_t<4, 16>(wpg, lds);
+int batch_occupancy(int fl, int wpg, size_t lds) {
+    switch (fl) {
+        case 1: return bocc_t<1>(wpg, lds);
+        case 2: return bocc_t<2>(wpg, lds);
+        case 3: return bocc_t<3>(wpg, lds);
+        case 4: return bocc_t<4>(wpg, lds);
         default: return 0;
     }
 }
@@ -1702,63 +1882,57 @@ hipError_t launch_backward(const BwdArgs &a, hipStream_t st) {
     return launch_backward_t(a, st);
 }
 
-template <int FL, int TT>
+template <int FL>
 hipError_t launch_batch_t(const BatchStream *streams, const int2 *items, int nitems, int *counter,
                           const int64_t *pos, int block_len, int grid, int wpg, size_t lds, hipStream_t st) {
-    hipLaunchKernelGGL((batch_kernel<FL, TT>), dim3(grid), dim3(wpg * 64), lds, st, streams, items, nitems,
+    hipLaunchKernelGGL((batch_kernel<FL>), dim3(grid), dim3(wpg * 64), lds, st, streams, items, nitems,
                        counter, pos, block_len);
     return hipGetLastError();
 }
 
 hipError_t launch_batch(const BatchStream *streams, const int2 *items, int nitems, int *counter,
-                        const int64_t *pos, int block_len, int fl, int tt, int grid, int wpg, size_t lds,
+                        const int64_t *pos, int block_len, int fl, int grid, int wpg, size_t lds,
                         hipStream_t st) {
-    switch (fl * 100 + tt) {
-        case 108: return launch_batch_t<1, 8>(streams, items, nitems, counter, pos, block_len, grid, wpg, lds, st);
-        case 208: return launch_batch_t<2, 8>(streams, items, nitems, counter, pos, block_len, grid, wpg, lds, st);
-        case 308: return launch_batch_t<3, 8>(streams, items, nitems, counter, pos, block_len, grid, wpg, lds, st);
-        case 408: return launch_batch_t<4, 8>(streams, items, nitems, counter, pos, block_len, grid, wpg, lds, st);
-        case 116: return launch_batch_t<1, 16>(streams, items, nitems, counter, pos, block_len, grid, wpg, lds, st);
-        case 216: return launch_batch_t<2, 16>(streams, items, nitems, counter, pos, block_len, grid, wpg, lds, st);
-        case 316: return launch_batch_t<3, 16>(streams, items, nitems, counter, pos, block_len, grid, wpg, lds, st);
-        case 416: return launch_batch_t<4, 16>(streams, items, nitems, counter, pos, block_len, grid, wpg, lds, st);
+    switch (fl) {
+        case 1: return launch_batch_t<1>(streams, items, nitems, counter, pos, block_len, grid, wpg, lds, st);
+        case 2: return launch_batch_t<2>(streams, items, nitems, counter, pos, block_len, grid, wpg, lds, st);
+        case 3: return launch_batch_t<3>(streams, items, nitems, counter, pos, block_len, grid, wpg, lds, st);
+        case 4: return launch_batch_t<4>(streams, items, nitems, counter, pos, block_len, grid, wpg, lds, st);
         default: return hipErrorInvalidValue;
     }
 }
 
-template <int FL, int TT>
-hipError_t launch_batch_split_t(const BatchStream *streams, const int2 *seg_items, int n_seg_items,
-                                const int2 *carry_items, int n_carry_items, const int64_t *pos, int block_len,
-                                int nstreams, int64_t max_slots, int wpg, size_t lds, size_t lds_carry,
-                                hipStream_t st) {
-    hipLaunchKernelGGL((batch_seg_kernel<FL, TT>), dim3(n_seg_items), dim3(wpg * 64), lds, st, streams, seg_items,
-                       pos, block_len);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(batch_chain_kernel, dim3(nblocks(max_slots, 256), nstreams), dim3(256), 0, st, streams, pos,
+template <int FL>
+hipError_t launch_batch_split_t(const BatchStream *streams, const int2 *pre_items, int n_pre_items,
+                                const int2 *seg_items, int n_seg_items, const int64_t *pos, int block_len,
+                                int nstreams, int64_t max_slots, int wpg, size_t lds, hipStream_t st) {
+    hipError_t e = hipSuccess;
+    if (n_pre_items > 0) {
+        hipLaunchKernelGGL((batch_pre_kernel<FL>), dim3(n_pre_items), dim3(wpg * 64), lds, st, streams, pre_items,
+                           pos, block_len);
+        e = hipGetLastError();
+        if (e != hipSuccess) return e;
+    }
+    hipLaunchKernelGGL(batch_chain_kernel, dim3(nblocks(max_slots, 64), nstreams), dim3(256), 0, st, streams, pos,
                        block_len);
     e = hipGetLastError();
-    if (e != hipSuccess || n_carry_items == 0) return e;
-    hipLaunchKernelGGL((batch_carry_kernel<FL, TT>), dim3(n_carry_items), dim3(wpg * 64), lds_carry, st, streams,
-                       carry_items, pos, block_len);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL((batch_seg_kernel<FL>), dim3(n_seg_items), dim3(wpg * 64), lds, st, streams, seg_items,
+                       pos, block_len);
     return hipGetLastError();
 }
 
-hipError_t launch_batch_split(const BatchStream *streams, const int2 *seg_items, int n_seg_items,
-                              const int2 *carry_items, int n_carry_items, const int64_t *pos, int block_len,
-                              int nstreams, int64_t max_slots, int fl, int tt, int wpg, size_t lds,
-                              size_t lds_carry, hipStream_t st) {
-#define SPIIR_SPLIT_ARGS streams, seg_items, n_seg_items, carry_items, n_carry_items, pos, block_len, nstreams, \
-                         max_slots, wpg, lds, lds_carry, st
-    switch (fl * 100 + tt) {
-        case 108: return launch_batch_split_t<1, 8>(SPIIR_SPLIT_ARGS);
-        case 208: return launch_batch_split_t<2, 8>(SPIIR_SPLIT_ARGS);
-        case 308: return launch_batch_split_t<3, 8>(SPIIR_SPLIT_ARGS);
-        case 408: return launch_batch_split_t<4, 8>(SPIIR_SPLIT_ARGS);
-        case 116: return launch_batch_split_t<1, 16>(SPIIR_SPLIT_ARGS);
-        case 216: return launch_batch_split_t<2, 16>(SPIIR_SPLIT_ARGS);
-        case 316: return launch_batch_split_t<3, 16>(SPIIR_SPLIT_ARGS);
-        case 416: return launch_batch_split_t<4, 16>(SPIIR_SPLIT_ARGS);
+hipError_t launch_batch_split(const BatchStream *streams, const int2 *pre_items, int n_pre_items,
+                              const int2 *seg_items, int n_seg_items, const int64_t *pos, int block_len,
+                              int nstreams, int64_t max_slots, int fl, int wpg, size_t lds,
+                              hipStream_t st) {
+#define SPIIR_SPLIT_ARGS streams, pre_items, n_pre_items, seg_items, n_seg_items, pos, block_len, nstreams, \
+                         max_slots, wpg, lds, st
+    switch (fl) {
+        case 1: return launch_batch_split_t<1>(SPIIR_SPLIT_ARGS);
+        case 2: return launch_batch_split_t<2>(SPIIR_SPLIT_ARGS);
+        case 3: return launch_batch_split_t<3>(SPIIR_SPLIT_ARGS);
+        case 4: return launch_batch_split_t<4>(SPIIR_SPLIT_ARGS);
         default: return hipErrorInvalidValue;
     }
 #undef SPIIR_SPLIT_ARGS

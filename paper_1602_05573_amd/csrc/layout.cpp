@@ -159,14 +159,15 @@ int choose_fl(int T, const int64_t *off, int n_cu) {
 }
 
 size_t fwd_lds_bytes(int wpg, int dmax, int nb, bool x_in_lds, int tt) {
-    const size_t win = x_in_lds ? (size_t)((dmax + nb + tt + 3) & ~3) * 4 : 0;
-    return win + (size_t)wpg * tt * 64 * 8 + ((size_t)2 * tt * (4 * wpg + 1) + 16) * 8 + (size_t)2 * tt * 8;
+    const size_t win = x_in_lds ? (size_t)((dmax + nb + kFwdTile + 3) & ~3) * 4 : 0;
+    const size_t sb = (size_t)sum_batch(tt);
+    return win + (size_t)wpg * kFwdTile * 64 * 8 + 2 * sb * (size_t)(4 * wpg + 1) * 8 + 2 * sb * 8 + 48;
 }
 
-// The strain window (max_delay + nb samples) in LDS when it fits, and 16-step
-// tiles when they fit beside it. The forward kernel closes a chunk (FP64
-// carry correction, tape entry) only at a tile end, so the tile length must
-// divide L: chunk lengths that are not a multiple of 16 take 8-step tiles.
+// The strain window (max_delay + nb samples) in LDS when it fits, and batches
+// of 64 steps when their row sums fit beside at least 2,048 samples of it. A
+// chunk ends at a tile end, so kFwdTile must divide L; chunk lengths that are not
+// a multiple of 16 take batches of 8.
 Geometry plan_geometry(int wpg, int dmax, int L, int max_block, size_t lds_cap) {
     Geometry best;
     bool have = false;
@@ -175,7 +176,7 @@ Geometry plan_geometry(int wpg, int dmax, int L, int max_block, size_t lds_cap) 
         Geometry g;
         g.tt = tt;
         const int64_t fixed = (int64_t)fwd_lds_bytes(wpg, 0, 0, false, tt);
-        int64_t nb = ((int64_t)lds_cap - fixed - 4 * (int64_t)(dmax + tt) - 64) / (4 * L) * L;
+        int64_t nb = ((int64_t)lds_cap - fixed - 4 * (int64_t)(dmax + kFwdTile) - 64) / (4 * L) * L;
         nb = std::min<int64_t>(nb, max_block);
         g.xlds = nb >= L;
         g.nb = g.xlds ? (int)nb : max_block;
@@ -183,7 +184,7 @@ Geometry plan_geometry(int wpg, int dmax, int L, int max_block, size_t lds_cap) 
         if (!have) {
             best = g;
             have = true;
-            if (!g.xlds || g.nb >= std::min(max_block, 2048)) return g;
+            if (g.xlds && g.nb >= std::min(max_block, 2048)) return g;
         } else if (g.xlds && (!best.xlds || g.nb > best.nb)) {
             return g;
         }

@@ -17,6 +17,7 @@ namespace spiir {
 
 constexpr int kMaxWaves = 8;    // 64-lane waves per workgroup (512 threads)
 constexpr int kRowLanes = 16;   // lanes per row; a row serves exactly one template
+constexpr int kFwdTile = 8;        // steps per tile of lane sums; divides every chunk length
 
 // Per 16-lane row of a workgroup: the template it serves (-1: none), the
 // first row of that template (or of its part) inside the workgroup, its number
@@ -60,7 +61,7 @@ struct Plan {
 
 // LDS plan of the forward kernel for one workgroup size.
 struct Geometry {
-    int tt = 16;         // steps per tile; always divides the chunk length
+    int tt = 16;         // batch class of the full pass (sum_batch); always divides the chunk length
     int nb = 0;          // samples per LDS window fill (a multiple of the chunk length)
     bool xlds = true;    // the strain window sits in LDS
     size_t lds = 0;      // LDS bytes per workgroup
@@ -93,7 +94,12 @@ int auto_wpg(int64_t total_rows, int max_nr, int n_cu);
 // compute unit; 1 for small banks.
 int choose_fl(int T, const int64_t *off, int n_cu);
 // LDS bytes of a forward workgroup: strain window (when in LDS), one tile of
-// lane partial sums per wave, double-buffered row sums and the key slots.
+// lane partial sums per wave, double-buffered row sums and key slots of one
+// batch, and the workgroup's templates.
+// Steps that a full pass runs between two barriers: 64 (one sample per lane in
+// the template sums), or 8 where the chunk length is no multiple of 16 or the
+// window needs the LDS that the larger row-sum buffer takes.
+inline int sum_batch(int tt) { return tt == 16 ? 64 : 8; }
 size_t fwd_lds_bytes(int wpg, int dmax, int nb, bool x_in_lds, int tt);
 Geometry plan_geometry(int wpg, int dmax, int L, int max_block, size_t lds_cap);
 

@@ -20,7 +20,7 @@ struct SlotArrays {
     const float2 *b32;    // fl32(b)
     const int32_t *xoff;  // max_delay - d: offset of x[m - d] inside the window
     const double2 *aL;    // a^L in FP64
-    const double2 *dL;    // a^L - fl32(a)^L in FP64
+    const double2 *dL;    // a^L minus what the FP32 recursion multiplies a carried state by over L steps, FP64
     const double2 *a64;   // a in FP64 (powers for ragged chunks)
     const int32_t *flags; // bit 0: |a| > 1 - 1e-5 (FP64 carry in hybrid mode)
 };
@@ -44,6 +44,7 @@ struct FwdArgs {
     int64_t n;            // samples in this launch
     int32_t dmax, L, nb, prec, wpg, only_tpl;
     int32_t gbase;        // group of blockIdx.x == 0
+    int32_t sumb;         // steps per batch of the full pass (at most 64, whole tiles)
     int32_t band_w;       // LDS window: delays of a group lie in [lo, lo + band_w]; max_delay without bands
     const int32_t *group_lo;  // [groups] lowest delay of each group's band (null: no bands, lo = 0)
     const RowInfo *rows;  // [groups * wpg * 4]
@@ -59,13 +60,14 @@ struct FwdArgs {
     int32_t groups;       // workgroups of the bank (item = segment * groups + group)
     int32_t n_templates;
     int64_t seg_len;
-    float4 *seg_end;      // [nseg][nslots] state at each segment end (local from zero for segments > 0)
-    float4 *seg_start;    // [nseg][nslots] true state at each segment start (segments > 0)
-    float2 *zl;           // [nseg - 1][T][seg_len] local z of segments > 0
+    float4 *seg_end;      // [nseg][nslots] state at each segment end but the last (from rest for segments > 0)
+    float4 *seg_start;    // [nseg][nslots] true state at each segment start
     HistCopy hist_next;   // time split: history copy done by the chain launch (dmax 0: none)
     // seg_end / seg_start hold slots [seg_slot0, seg_slot0 + seg_stride) of every segment
     // (entry [seg][slot - seg_slot0]); the whole bank: 0 and nslots
     int64_t seg_slot0, seg_stride;
+    int32_t chain_inline;   // time split without a chain launch: the full pass composes its start states
+    int32_t pad0;
 };
 
 struct BwdArgs {
@@ -88,14 +90,14 @@ struct BwdArgs {
 
 // Time-split streaming z calls of several banks (each on its own strain) in
 // one launch per pass: pass workgroups [first[b], first[b + 1]) belong to
-// bank b (segment pass: groups x nseg; chain: chain_blocks plus the history
-// copy's blocks; carry pass: groups x (nseg - 1)).
+// bank b (state pass: groups x (nseg - 1); chain: chain_blocks plus the
+// history copy's blocks; full pass: groups x nseg).
 constexpr int kMultiMax = 8;
 struct MultiFwd {
     FwdArgs a[kMultiMax];
-    int32_t seg_first[kMultiMax + 1];
+    int32_t pre_first[kMultiMax + 1];
     int32_t chain_first[kMultiMax + 1];
-    int32_t carry_first[kMultiMax + 1];
+    int32_t seg_first[kMultiMax + 1];
     int32_t nseg[kMultiMax];
     int32_t chain_blocks[kMultiMax];
     int32_t count;
@@ -120,18 +122,17 @@ struct KernelEvents {
     hipEvent_t stop = nullptr;
 };
 
-hipError_t launch_forward(const FwdArgs &a, int mode, int fl, int tt, bool x_in_lds, int groups,
-                          size_t lds, hipStream_t stream, KernelEvents ev = KernelEvents());
-// Time-split launch (modes kModeSnr / kModeKeys / kModeZ): local pass over every
-// segment, FP64 carry chain, carry-only pass with the local z added.
-hipError_t launch_forward_split(const FwdArgs &a, int mode, int fl, int tt, bool x_in_lds, int nseg,
-                                size_t lds, size_t lds_carry, const int32_t *slot_filter,
-                                hipStream_t stream, KernelEvents ev = KernelEvents());
+hipError_t launch_forward(const FwdArgs &a, int mode, int fl, bool x_in_lds, int groups, size_t lds,
+                          hipStream_t stream, KernelEvents ev = KernelEvents());
+// Time-split launch (modes kModeSnr / kModeKeys / kModeZ): state pass over every
+// segment but the last, FP64 carry chain, full pass over every segment.
+hipError_t launch_forward_split(const FwdArgs &a, int mode, int fl, bool x_in_lds, int nseg,
+                                size_t lds, hipStream_t stream, KernelEvents ev = KernelEvents());
 // The three passes of a MultiFwd (z mode, strain windows in LDS); every bank
-// shares fl, tt and the workgroup size wpg * 64.
-hipError_t launch_forward_split_multi(const MultiFwd &m, int fl, int tt, int wpg, size_t lds, size_t lds_carry,
-                                      hipStream_t stream);
-int forward_occupancy(int fl, int tt, int wpg, size_t lds);
+// shares fl and the workgroup size wpg * 64.
+hipError_t launch_forward_split_multi(const MultiFwd &m, int fl, int wpg, size_t lds, hipStream_t stream);
+int forward_occupancy(int fl, int wpg, size_t lds);
+int state_occupancy(int fl, int wpg, const FwdArgs &a, bool x_in_lds);
 // Adjoint over nseg time segments: segment-local (lambda, nu) scan, FP64 chain,
 // per-segment backward, FP64 reduction of the per-segment gradients.
 hipError_t launch_backward(const BwdArgs &a, hipStream_t stream);
@@ -148,23 +149,26 @@ hipError_t launch_combine_parts(const float2 *zpart, int64_t ld_part, const int3
 hipError_t launch_set_coeffs(const double *a, const double *b, const int32_t *slot_filter, int64_t nslots, int L,
                              float2 *a32, float2 *b32, double2 *aL, double2 *dL, double2 *a64, int32_t *flags,
                              hipStream_t stream);
+// dL of every slot from its a64 and b32.
+hipError_t launch_chunk_drift(const double2 *a64, const float2 *b32, int64_t nslots, int L, double2 *dL,
+                              hipStream_t stream);
 hipError_t launch_rows_argmax(const float *snr, int T, int64_t ld, int64_t n, float *mx,
                               int32_t *am, hipStream_t stream);
 hipError_t launch_hist_update(const float *old_h, float *new_h, const float *x, int64_t n,
                               int dmax, hipStream_t stream);
 hipError_t launch_window_fill(float *xwin, const float *hist, const float *x, int64_t n,
                               int dmax, hipStream_t stream);
-int batch_occupancy(int fl, int tt, int wpg, size_t lds);
+int batch_occupancy(int fl, int wpg, size_t lds);
 hipError_t launch_fill_zero(void *p, size_t bytes, hipStream_t stream);
 hipError_t launch_batch(const BatchStream *streams, const int2 *items, int nitems,
-                        int *counter, const int64_t *pos, int block_len, int fl, int tt, int grid,
+                        int *counter, const int64_t *pos, int block_len, int fl, int grid,
                         int wpg, size_t lds, hipStream_t stream);
-// Time-split batch step: local pass over (stream, group << 4 | segment) items,
-// per-stream FP64 carry chain, carry-only pass over the items of segments >= 1.
-hipError_t launch_batch_split(const BatchStream *streams, const int2 *seg_items, int n_seg_items,
-                              const int2 *carry_items, int n_carry_items, const int64_t *pos, int block_len,
-                              int nstreams, int64_t max_slots, int fl, int tt, int wpg, size_t lds,
-                              size_t lds_carry, hipStream_t stream);
+// Time-split batch step: state pass over the (stream, group << 4 | segment)
+// items of all segments but the last, per-stream FP64 carry chain, full pass.
+hipError_t launch_batch_split(const BatchStream *streams, const int2 *pre_items, int n_pre_items,
+                              const int2 *seg_items, int n_seg_items, const int64_t *pos, int block_len,
+                              int nstreams, int64_t max_slots, int fl, int wpg, size_t lds,
+                              hipStream_t stream);
 hipError_t launch_batch_finalize(const BatchStream *streams, int nstreams, const uint64_t *keys,
                                  int64_t key_stride, const int64_t *pos, int block_len,
                                  int max_groups, hipStream_t stream);
