@@ -420,7 +420,7 @@ __device__ __forceinline__ float4 hi_lo(double2 c) {
 // start state (at most 7 reads per slot); beyond it a launch of its own does.
 // The launch costs about 6 us with its gaps: 21.7 -> 15.1 us per 512-sample
 // call of a 4 x 128-filter bank.
-constexpr int kChainInline = 8;
+constexpr int kChainInline = 16;
 
 // Coefficients and initial states of a lane's slots; true if the wave runs
 // the plain recursion. The block powers are formed here in FP64 (full rate on
@@ -534,19 +534,22 @@ __device__ void fwd_group(const FwdArgs &p, int g, unsigned char *smem, const Se
     const int sb = p.sumb;
     float2 *wsum = tiles + W * kFwdTile * 64;   // [2][sb][Rp]
     unsigned long long *kmax = reinterpret_cast<unsigned long long *>(wsum + 2 * sb * Rp);  // [2][sb]
-    int *nitems = reinterpret_cast<int *>(kmax + 2 * sb);
-    unsigned char *items = reinterpret_cast<unsigned char *>(nitems + 1);   // [R]: first rows of the templates here
 
     const RowInfo ri = p.rows[(int64_t)g * R + wave * 4 + (lane >> 4)];
     const bool ract = ri.tpl >= 0 && (p.only_tpl < 0 || ri.tpl == p.only_tpl);
     const bool wact = __ballot(ract) != 0;
-    if (wave == 0) {
-        RowInfo it = {-1, 0, 0, -1};
-        if (lane < R) it = p.rows[(int64_t)g * R + lane];
-        const bool first = it.tpl >= 0 && it.r0 == lane && (p.only_tpl < 0 || it.tpl == p.only_tpl);
-        const unsigned long long m = __ballot(first);
-        if (first) items[__popcll(m & ((1ull << lane) - 1))] = (unsigned char)lane;
-        if (lane == 0) *nitems = __popcll(m);
+    // the workgroup's templates: lane i of every wave holds the first row of template i
+    RowInfo it = {-1, 0, 0, -1};
+    if (lane < R) it = p.rows[(int64_t)g * R + lane];
+    unsigned long long first = __ballot(it.tpl >= 0 && it.r0 == lane && (p.only_tpl < 0 || it.tpl == p.only_tpl));
+    const int ni = __popcll(first);
+    {
+        int from = lane;   // the lane holding the first row of template `lane`
+        for (int i = 0; i < ni; ++i) {
+            if (lane == i) from = __ffsll(first) - 1;
+            first &= first - 1;
+        }
+        it = RowInfo{__shfl(it.tpl, from), __shfl(it.r0, from), __shfl(it.nr, from), __shfl(it.part, from)};
     }
     if (MODE == kModeKeys)
         for (int i = tid; i < 2 * sb; i += W * 64) kmax[i] = 0ull;
@@ -570,13 +573,10 @@ __device__ void fwd_group(const FwdArgs &p, int g, unsigned char *smem, const Se
     };
     // template sums and outputs of one batch: launch samples sc.tb + t + [0, steps)
     auto emit = [&](int64_t t, int steps) {
-        const int ni = *nitems;
         unsigned long long best = 0ull;
         for (int i = wave; i < ni; i += W) {
-            const int r0 = __builtin_amdgcn_readfirstlane((int)items[i]);
-            const RowInfo it = p.rows[(int64_t)g * R + r0];
-            const int tpl = __builtin_amdgcn_readfirstlane(it.tpl);
-            const int nr = __builtin_amdgcn_readfirstlane(it.nr), part = __builtin_amdgcn_readfirstlane(it.part);
+            const int r0 = __builtin_amdgcn_readlane(it.r0, i), nr = __builtin_amdgcn_readlane(it.nr, i);
+            const int tpl = __builtin_amdgcn_readlane(it.tpl, i), part = __builtin_amdgcn_readlane(it.part, i);
             if (lane >= steps) continue;
             const float2 z = sum_rows(wsum + (buf * sb + lane) * Rp + r0, nr);
             if (PARTS && part >= 0) {
@@ -720,9 +720,11 @@ __device__ __forceinline__ void hist_copy_at(const HistCopy &hc, int i) {
 
 // A streaming call's last launch also writes the next call's history (hc.dmax >
 // 0); it reads old_h and x only, which the launch does not write.
-__device__ __forceinline__ void hist_copy_all(const HistCopy &hc) {
-    for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < hc.dmax; i += gridDim.x * blockDim.x) hist_copy_at(hc, i);
+__device__ __forceinline__ void hist_copy_part(const HistCopy &hc, int block, int blocks) {
+    for (int i = block * blockDim.x + threadIdx.x; i < hc.dmax; i += blocks * blockDim.x) hist_copy_at(hc, i);
 }
+
+__device__ __forceinline__ void hist_copy_all(const HistCopy &hc) { hist_copy_part(hc, blockIdx.x, gridDim.x); }
 
 template <int FL, int MODE, bool XLDS, bool PARTS>
 __global__ void __launch_bounds__(512) fwd_kernel(FwdArgs p) {
@@ -895,6 +897,8 @@ template <int FL, int MODE>
 __global__ void __launch_bounds__(512) fwd_seg_multi_kernel(MultiFwd m) {
     extern __shared__ __align__(16) unsigned char smem[];
     const int b = multi_bank(m.seg_first, m.count);
+    if (m.a[b].chain_inline)
+        hist_copy_part(m.a[b].hist_next, blockIdx.x - (unsigned)m.seg_first[b], m.seg_first[b + 1] - m.seg_first[b]);
     seg_item<FL, MODE, true, false>(m.a[b], blockIdx.x - (unsigned)m.seg_first[b], smem);
 }
 
@@ -1702,14 +1706,23 @@ hipError_t launch_forward_split(const FwdArgs &args, int mode, int fl, bool x_in
 namespace {
 
 template <int FL>
-hipError_t launch_multi_t(const MultiFwd &m, int wpg, size_t lds, size_t lds_pre, hipStream_t st) {
-    const int n = m.count;
+hipError_t launch_multi_t(const MultiFwd &args, int wpg, size_t lds, size_t lds_pre, hipStream_t st) {
+    const int n = args.count;
+    MultiFwd m = args;
+    bool chain = false;
+    for (int b = 0; b < n; ++b) {
+        m.a[b].chain_inline = m.nseg[b] <= kChainInline ? 1 : 0;
+        chain = chain || !m.a[b].chain_inline;
+    }
+    for (int b = 0; b < n && chain; ++b) m.a[b].chain_inline = 0;   // one bank too many: the launch serves all
     hipLaunchKernelGGL((fwd_pre_multi_kernel<FL>), dim3((unsigned)m.pre_first[n]), dim3(wpg * 64), lds_pre, st, m);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(seg_chain_multi_kernel, dim3((unsigned)m.chain_first[n]), dim3(256), 0, st, m, FL);
-    e = hipGetLastError();
-    if (e != hipSuccess) return e;
+    if (chain) {
+        hipLaunchKernelGGL(seg_chain_multi_kernel, dim3((unsigned)m.chain_first[n]), dim3(256), 0, st, m, FL);
+        e = hipGetLastError();
+        if (e != hipSuccess) return e;
+    }
     hipLaunchKernelGGL((fwd_seg_multi_kernel<FL, kModeZ>), dim3((unsigned)m.seg_first[n]), dim3(wpg * 64), lds,
                        st, m);
     return hipGetLastError();

@@ -161,7 +161,7 @@ int choose_fl(int T, const int64_t *off, int n_cu) {
 size_t fwd_lds_bytes(int wpg, int dmax, int nb, bool x_in_lds, int tt) {
     const size_t win = x_in_lds ? (size_t)((dmax + nb + kFwdTile + 3) & ~3) * 4 : 0;
     const size_t sb = (size_t)sum_batch(tt);
-    return win + (size_t)wpg * kFwdTile * 64 * 8 + 2 * sb * (size_t)(4 * wpg + 1) * 8 + 2 * sb * 8 + 48;
+    return win + (size_t)wpg * kFwdTile * 64 * 8 + 2 * sb * (size_t)(4 * wpg + 1) * 8 + 2 * sb * 8;
 }
 
 // The strain window (max_delay + nb samples) in LDS when it fits, and batches

@@ -95,7 +95,7 @@ int auto_wpg(int64_t total_rows, int max_nr, int n_cu);
 int choose_fl(int T, const int64_t *off, int n_cu);
 // LDS bytes of a forward workgroup: strain window (when in LDS), one tile of
 // lane partial sums per wave, double-buffered row sums and key slots of one
-// batch, and the workgroup's templates.
+// batch.
 // Steps that a full pass runs between two barriers: 64 (one sample per lane in
 // the template sums), or 8 where the chunk length is no multiple of 16 or the
 // window needs the LDS that the larger row-sum buffer takes.
