@@ -117,6 +117,8 @@ struct spiir_bank {
     int32_t *split_tpl = nullptr, *split_off = nullptr;
     int n_split = 0;
     int band = 0;                  // delay band width (0: none); group_lo [groups] on the device
+    bool band_auto = false;        // chosen by the library, not by opts.delay_band
+    std::vector<int> part_group;   // workgroup of every part
     int32_t *group_lo = nullptr;
     int nseg = 1;                 // most time segments per streaming launch
     bool seg_auto = false;        // the call chooses their number and length (plan_segments)
@@ -358,6 +360,8 @@ int scratch_setup(int dev, unsigned char **out) {
     return SPIIR_OK;
 }
 
+constexpr int kAutoBand = 16384;   // delay bands of large banks whose window does not fit LDS
+
 // seg_cap: most time segments the automatic time split may choose.
 int create_bank(spiir_bank **out, int32_t T, const int64_t *off, const double *a, const double *b,
                 const int32_t *d, const spiir_bank_opts &o, int seg_cap = 64) {
@@ -382,15 +386,30 @@ int create_bank(spiir_bank **out, int32_t T, const int64_t *off, const double *a
     const int L = o.chunk_len ? o.chunk_len : 256;
     int max_block = o.max_block ? o.max_block : 16384;
     max_block = std::max(L, (max_block / L) * L);
-    // Delay bands (an option): every workgroup takes filters of one band of delays and stages
-    // only that band's window in LDS. Not chosen automatically: on the chirp-fit bank (delays
-    // up to 65,535) the best banded layout only matched the strain window in global memory.
+    // Delay bands: every workgroup takes filters of one band of delays and stages only that
+    // band's window in LDS (an option, and the automatic choice below for large banks).
     const bool global_window = !plan_geometry(1, dmax, L, max_block, df.lds_cap).xlds;
     int band = 0;
     if (o.delay_band > 0) {
         band = o.delay_band;
         if (!plan_geometry(1, band - 1, L, max_block, df.lds_cap).xlds)
             return fail(SPIIR_EINVAL, "delay_band %d: its strain window does not fit LDS", band);
+    }
+    // A bank of more than 128 filters per compute unit whose delays do not fit LDS takes
+    // bands of 16,384 samples, 4 filters per lane and 8-wave workgroups when the layout is
+    // left to the library, unless cutting its templates by delay costs over a quarter more
+    // workgroups. Chirp-fit bank (256 x 400 filters, delays up to 65,535), forward over
+    // 65,536 samples: 2.86 ms, against 5.33 ms with the window in global memory (its reads,
+    // a cache line per lane and 16 bytes, bound that kernel); 2.85 ms with bands of 10,240,
+    // 3.03 with 8,192, 3.55 with 6,144.
+    bool band_auto = false;
+    if (global_window && o.delay_band == 0 && o.filters_per_lane == 0 && o.waves_per_group == 0 &&
+        o.time_split == 0 && max_block >= 2048 && off[T] > 128 * (int64_t)df.n_cu &&
+        plan_geometry(kMaxWaves, kAutoBand - 1, L, max_block, df.lds_cap).xlds) {
+        Layout whole, cut;
+        band_auto = !build_layout(T, off, d, 4, kMaxWaves, 0, whole) &&
+                    !build_layout(T, off, d, 4, kMaxWaves, kAutoBand, cut) && 4 * cut.groups <= 5 * whole.groups;
+        if (band_auto) band = kAutoBand;
     }
     const int win_delay = band ? band - 1 : dmax;   // delays one workgroup's window covers
     // a banded window is refilled every band samples (at most), so that several workgroups
@@ -410,6 +429,7 @@ int create_bank(spiir_bank **out, int32_t T, const int64_t *off, const double *a
         const Plan pw = plan_rows(T, off, choose_fl(T, off, df.n_cu));
         seg_layout = p4.max_nr <= 4 * kMaxWaves && (pw.total_rows + 3) / 4 < (int64_t)7 * df.n_cu;
     }
+    if (band_auto) seg_layout = true;
     if (seg_layout) seg_cap = std::min(seg_cap, 16);
     int fl = o.filters_per_lane;
     if (fl == 0 && seg_layout) fl = 4;
@@ -458,6 +478,10 @@ int create_bank(spiir_bank **out, int32_t T, const int64_t *off, const double *a
         return rc;
     }
     bk->band = band;
+    bk->band_auto = band_auto;
+    bk->part_group.assign((size_t)bk->lay.n_parts, 0);
+    for (size_t r = 0; r < bk->lay.rows.size(); ++r)
+        if (bk->lay.rows[r].part >= 0) bk->part_group[(size_t)bk->lay.rows[r].part] = (int)(r / (4 * (size_t)wpg));
     const Geometry gm = plan_geometry(wpg, win_delay, L, nb_cap, df.lds_cap);
     if (L % gm.tt) {   // chunk ends are detected at tile ends only
         delete bk;
@@ -1056,7 +1080,7 @@ int spiir_trigger_max_per_template(spiir_bank *bk, const float *x, int64_t n, fl
     if (n < 0) return fail(SPIIR_EINVAL, "n must be >= 0");
     if (n == 0) return SPIIR_OK;
     if (!x || !mx || !am || !snr) return fail(SPIIR_EINVAL, "null device pointer");
-    if (bk->n_split)
+    if (bk->n_split && !bk->band_auto)
         return fail(SPIIR_EINVAL, "the per-template comparator needs every template inside one workgroup");
     DeviceGuard guard(bk->device);
     hipStream_t st = as_stream(stream);
@@ -1092,29 +1116,47 @@ int spiir_trigger_max_per_template(spiir_bank *bk, const float *x, int64_t n, fl
     for (int64_t P = 0; P < n; P += bk->max_block) {
         const int64_t np = std::min<int64_t>(bk->max_block, n - P);
         const int nseg = (int)((np + L - 1) / L);
+        // (template, workgroup) launches: one per template, or one per workgroup that holds
+        // parts of it where the library cut templates by delay
+        int split = 0;
         for (int j = 0; j < bk->T; ++j) {
-            FwdArgs a = bk->base_args();
-            a.state = bk->state;
-            a.x = x;
-            a.hist = hist;
-            a.xwin = bk->xwin;
-            a.xbase = P;
-            a.n = np;
-            a.obase = P;
-            a.snr = snr;
-            a.ld = n;
-            a.only_tpl = j;
-            a.gbase = bk->lay.tpl_group[j];
-            a.groups = 1;
-            if (nseg >= 2) {
-                a.seg_len = L;
-                a.seg_end = bk->pl_seg_end;
-                a.seg_start = bk->pl_seg_start;
-                a.seg_slot0 = (int64_t)a.gbase * gslots;
-                a.seg_stride = gslots;
-                HIPCHK(launch_forward_split(a, kModeSnr, bk->lay.fl, false, nseg, bk->lds_tile, st));
-            } else {
-                HIPCHK(launch_forward(a, kModeSnr, bk->lay.fl, false, 1, bk->lds_tile, st));
+            const bool cut = split < bk->n_split && bk->lay.split_tpl[(size_t)split] == j;
+            std::vector<int> where(1, bk->lay.tpl_group[j]);
+            if (cut) {
+                where.assign(bk->part_group.begin() + bk->lay.split_off[(size_t)split],
+                             bk->part_group.begin() + bk->lay.split_off[(size_t)split + 1]);
+                std::sort(where.begin(), where.end());
+                where.erase(std::unique(where.begin(), where.end()), where.end());
+            }
+            for (int g : where) {
+                FwdArgs a = bk->base_args();
+                a.state = bk->state;
+                a.x = x;
+                a.hist = hist;
+                a.xwin = bk->xwin;
+                a.xbase = P;
+                a.n = np;
+                a.obase = P;
+                a.snr = snr;
+                a.ld = n;
+                a.only_tpl = j;
+                a.gbase = g;
+                a.groups = 1;
+                if (nseg >= 2) {
+                    a.seg_len = L;
+                    a.seg_end = bk->pl_seg_end;
+                    a.seg_start = bk->pl_seg_start;
+                    a.seg_slot0 = (int64_t)a.gbase * gslots;
+                    a.seg_stride = gslots;
+                    HIPCHK(launch_forward_split(a, kModeSnr, bk->lay.fl, false, nseg, bk->lds_tile, st));
+                } else {
+                    HIPCHK(launch_forward(a, kModeSnr, bk->lay.fl, false, 1, bk->lds_tile, st));
+                }
+            }
+            if (cut) {
+                HIPCHK(launch_combine_parts(bk->zpart, bk->max_block, bk->split_tpl + split, bk->split_off + split, 1,
+                                            np, kModeSnr, snr, nullptr, n, P, nullptr, st));
+                ++split;
             }
         }
     }
@@ -1283,7 +1325,8 @@ int spiir_batch_create(spiir_batch **out, int32_t ns, spiir_bank *const *banks, 
         if (banks[s]->lay.fl != banks[0]->lay.fl || banks[s]->lay.wpg != banks[0]->lay.wpg ||
             banks[s]->tt != banks[0]->tt)
             return fail(SPIIR_EINVAL, "banks must share filters_per_lane, waves_per_group and tile length");
-        if (!banks[s]->xlds) return fail(SPIIR_EINVAL, "bank %d keeps its strain window outside LDS", s);
+        if (!banks[s]->xlds || banks[s]->band_auto)
+            return fail(SPIIR_EINVAL, "bank %d keeps its strain window outside LDS", s);
         if (banks[s]->n_split)
             return fail(SPIIR_EINVAL, "bank %d has templates split over workgroups; a batch takes none", s);
         for (int t = 0; t < s; ++t)

@@ -21,6 +21,8 @@
 //     max/argmax encoded as a 64-bit key (SNR bits << 32 | ~template).
 #include <hip/hip_ext.h>
 
+#include <algorithm>
+
 #include "spiir_internal.h"
 
 namespace spiir {
@@ -1032,9 +1034,11 @@ __global__ void __launch_bounds__(256) finalize_keys_kernel(const uint64_t *keys
 
 // Templates split over workgroups: z_j = the sum of its parts' partial sums
 // (in part order) for samples [0, n) of a piece, then the mode's output for
-// those templates: SNR rows, z rows, or (keys) the per-sample maximum key over
-// the split templates into key_row, which the key finalisation takes as one
-// more workgroup.
+// those templates: SNR rows, z rows (grid.y over the templates: one block per
+// template and 256 samples, since 64 blocks alone took 45 us for 256 templates
+// of 16,384 samples), or (keys, grid.y = 1) the per-sample maximum key over the
+// split templates into key_row, which the key finalisation takes as one more
+// workgroup.
 __global__ void __launch_bounds__(256) combine_parts_kernel(const float2 *zpart, int64_t ld_part,
                                                             const int32_t *split_tpl, const int32_t *split_off,
                                                             int n_split, int64_t n, int mode, float *snr, float2 *z,
@@ -1042,7 +1046,7 @@ __global__ void __launch_bounds__(256) combine_parts_kernel(const float2 *zpart,
     const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (t >= n) return;
     unsigned long long kbest = 0ull;
-    for (int i = 0; i < n_split; ++i) {
+    for (int i = blockIdx.y; i < n_split; i += gridDim.y) {
         float zr = 0.f, zi = 0.f;
         for (int q = split_off[i]; q < split_off[i + 1]; ++q) {
             const float2 v = zpart[(int64_t)q * ld_part + t];
@@ -1185,26 +1189,6 @@ __device__ __forceinline__ void fetch_x(const float *p, int ql, float (&v)[kSub]
     } else {
 #pragma unroll
         for (int t = 0; t < kSub; ++t) v[t] = t < ql ? p[t] : 0.f;
-    }
-}
-
-__device__ __forceinline__ void fetch_g(const float2 *p, int ql, float (&gr)[kSub], float (&gi)[kSub]) {
-    if (ql == kSub) {
-#pragma unroll
-        for (int i = 0; i < kSub / 2; ++i) {
-            const f4u q = *reinterpret_cast<const f4u *>(p + 2 * i);
-            gr[2 * i] = q.x;
-            gi[2 * i] = q.y;
-            gr[2 * i + 1] = q.z;
-            gi[2 * i + 1] = q.w;
-        }
-    } else {
-#pragma unroll
-        for (int t = 0; t < kSub; ++t) {
-            const float2 g = t < ql ? p[t] : make_float2(0.f, 0.f);
-            gr[t] = g.x;
-            gi[t] = g.y;
-        }
     }
 }
 
@@ -1795,7 +1779,8 @@ hipError_t launch_combine_parts(const float2 *zpart, int64_t ld_part, const int3
                                 const int32_t *split_off, int n_split, int64_t n, int mode, float *snr, float2 *z,
                                 int64_t ld, int64_t obase, uint64_t *key_row, hipStream_t st) {
     if (n <= 0 || n_split <= 0) return hipSuccess;
-    hipLaunchKernelGGL(combine_parts_kernel, dim3(nblocks(n, 256)), dim3(256), 0, st, zpart, ld_part, split_tpl,
+    const unsigned by = mode == kModeKeys ? 1u : (unsigned)std::min(n_split, 65535);
+    hipLaunchKernelGGL(combine_parts_kernel, dim3(nblocks(n, 256), by), dim3(256), 0, st, zpart, ld_part, split_tpl,
                        split_off, n_split, n, mode, snr, z, ld, obase, key_row);
     return hipGetLastError();
 }

@@ -87,3 +87,58 @@ def test_automatic_segments(n, every):
     s, mx, am, _ = run_rows(bank, x, [0, n, 2 * n, 3 * n])
     assert snr_err(s, ref)[0] <= SNR_TOL
     check_argmax(mx, am, ref)
+
+
+@pytest.fixture(scope="module")
+def long_delays():
+    # above 128 filters per compute unit of a 256-unit device, delays of four bands
+    bank = random_bank(94, 0, 84, 380, 420, 0.99, 1 - 1e-5, 60000)
+    x = strain(5000, 94)
+    return bank, x, oracle.snr(bank, x, nthreads=oracle.max_threads())
+
+
+def test_automatic_delay_bands(long_delays):
+    """A large bank whose delays do not fit LDS is cut by delay; streaming calls,
+    the per-template comparator and the allocation-free call against the oracle."""
+    from paper_1602_05573_amd import SpiirBank, SpiirBatch, SpiirError
+    bank, x, ref = long_delays
+    print("[case] automatic delay bands", flush=True)
+    s, mx, am, info = run_rows(bank, x, [0, 1000, 1003, 5000])
+    assert info["delay_band"] > 0 and info["x_in_lds"] == 1 and info["n_parts"] > 0
+    assert snr_err(s, ref)[0] <= SNR_TOL
+    check_argmax(mx, am, ref)
+    xd = torch.from_numpy(x).cuda()
+    with SpiirBank.from_bank(bank) as bk:
+        outs = [bk.trigger_max_per_template(xd[a:b].contiguous()) for a, b in ((0, 700), (700, 5000))]
+        check_argmax(torch.cat([o[0] for o in outs]).cpu().numpy(), torch.cat([o[1] for o in outs]).cpu().numpy(), ref)
+        bk.reset()
+        m = torch.empty(5000, dtype=torch.float32, device="cuda")
+        j = torch.empty(5000, dtype=torch.int32, device="cuda")
+        bk.trigger_max_noalloc(xd, out=(m, j))
+        check_argmax(m.cpu().numpy(), j.cpu().numpy(), ref)
+        with pytest.raises(SpiirError, match="outside LDS"):
+            SpiirBatch([bk], [xd], block_len=4096)
+
+
+@pytest.mark.parametrize("n,L,K", [(1, 256, 64), (15, 256, 65), (16, 8, 1), (17, 24, 63), (300, 256, 128), (1000, 64, 200)])
+def test_backward_edges(n, L, K):
+    """Gradients where sub-chunks, chunks and waves of the backward are partly
+    filled; the gate is the one of the adjoint tests (per-template norm)."""
+    from paper_1602_05573_amd import SpiirBank
+    bank = random_bank(95, K, 5, K, K, 0.95, 0.9999, 90)
+    x = strain(n, 95)
+    zr = oracle.z(bank, x)
+    rng = np.random.default_rng(95)
+    G = (rng.standard_normal(zr.shape) + 1j * rng.standard_normal(zr.shape)).astype(np.complex64)
+    ga_ref, gb_ref = oracle.backward(bank, x, G.astype(np.complex128))
+    print("[case] backward n %d L %d K %d" % (n, L, K), flush=True)
+    for ts in (1, 3):
+        with SpiirBank.from_bank(bank, chunk_len=L, time_split=ts) as bk:
+            z, tape = bk.forward_z(torch.from_numpy(x).cuda(), want_tape=True)
+            ga, gb = bk.backward(tape, torch.from_numpy(G).cuda())
+            tape.close()
+            ga, gb = ga.cpu().numpy(), gb.cpu().numpy()
+        for g, r in ((ga, ga_ref), (gb, gb_ref)):
+            for j in range(bank.n_templates):
+                sl = slice(int(bank.offsets[j]), int(bank.offsets[j + 1]))
+                assert np.linalg.norm(g[sl] - r[sl]) <= 1e-3 * np.linalg.norm(r[sl])
