@@ -209,16 +209,28 @@ int mr_key_chunks(int T);
 hipError_t launch_mr_copy_out(float *mx, const float *mxo, int32_t *am, const int32_t *amo, int64_t n,
                               hipStream_t stream);
 
-// Whitening front end: frame FFTs (PSD or whitening mode), PSD average,
-// 1/sqrt(S) from a given PSD, overlap-add with history and pending half-frame.
-hipError_t launch_wh_frames(bool psd, const float *hist, int64_t hlen, const float *x, const float *wtab,
-                            const float2 *tw, int n, int logn, const float *inv, float *y, float *pw,
-                            int64_t frames, hipStream_t stream);
-hipError_t launch_wh_psd_reduce(const float *pw, int64_t frames, int H, double wsum2, double *S, float *inv,
+// Whitening front end: the hops of a call, the power of the training frames (a
+// row per pair of frames), the PSD from those rows, 1/sqrt(S) from a given PSD,
+// and a copy of up to two arrays.
+struct WhitenHops {
+    const float *hist = nullptr;   // [H] samples before x
+    const float *x = nullptr;      // [nf H]
+    int64_t nf = 0;
+    const float *wtab = nullptr;
+    const float2 *tw = nullptr;
+    const float *inv = nullptr;
+    const float *pend = nullptr;   // [H] second half of the frame before the call's first
+    float *pend_new = nullptr, *hist_new = nullptr;
+    float *out = nullptr;          // [nf H], apart from x
+};
+hipError_t launch_wh_hops(const WhitenHops &a, int logn, hipStream_t stream);
+hipError_t launch_wh_power(const float *x, int64_t frames, const float *wtab, const float2 *tw, int logn, float *pw,
+                           hipStream_t stream);
+hipError_t launch_wh_psd_reduce(const float *pw, int64_t frames, int logn, double wsum2, double *S, float *inv,
                                 hipStream_t stream);
-hipError_t launch_wh_inv(const double *S, int H, float *inv, hipStream_t stream);
-hipError_t launch_wh_ola(const float *y, int64_t nf, int n, const float *pend, float *pend_new, const float *x,
-                         int64_t nx, float *hist_new, float *out, hipStream_t stream);
+hipError_t launch_wh_inv(const double *S, int logn, float *inv, hipStream_t stream);
+hipError_t launch_wh_copy(const float *a, float *b, int64_t n, const float *c, float *d, int64_t m,
+                          hipStream_t stream);
 
 // Trigger clustering over a max/argmax series (block maxima, window test,
 // ordered compaction); the workspace holds the block maxima, masks and counts.

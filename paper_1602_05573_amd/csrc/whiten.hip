@@ -5,227 +5,402 @@
 //   PSD estimate : S[f] = mean over frames of |DFT(w . s_k)[f]|^2 / sum_t w[t]^2, f = 0..N/2
 //   whitening    : y_k = IDFT(DFT(w . x_k) / sqrt(S)), overlap-added at hop H
 // The stream is whitened with a delay of H samples (H zeros precede it).
-// Each frame is one workgroup of 1,024 threads: a radix-2 FFT of N complex
-// points in LDS (bit-reversed load, in-place butterflies taken two stages per
-// pass, a bank swizzle on the frame buffer; the FP64-computed twiddle table
-// is staged in LDS once per frame, so no stage waits on global memory); the
-// inverse transform is the forward one applied to the conjugate.
+//
+// Two neighbouring frames share one complex transform (the earlier one in the
+// real part, the later one in the imaginary part): 1 / sqrt(S) is real and
+// even, so whitening acts on both parts alone, and the hop that the two frames
+// overlap in is the sum of one half of each, so a hop is written by the one
+// group of threads that transforms its two frames and no frame output goes
+// through memory. The first hop takes the stored half of the frame before the
+// call instead of that frame, and one more group transforms the last frame
+// alone for the half that the next call takes: neither depends on samples
+// outside its frames, and the stored half keeps the PSD it was made with.
+//
+// What bounds it is the latency of one transform on one compute unit (4,096
+// samples are 3 workgroups): FP32 issue of the butterflies and the exchanges
+// through LDS. Hence radix 8 with 8 elements per thread (3 exchanges each way
+// at N = 4,096, where radix 4 had 12 passes through LDS and two more for the
+// bit reversal), the frequencies left in digit-reversed order between the two
+// transforms (1 / sqrt(S) is stored in that order), and every twiddle factor
+// loaded once into registers, from tables in the order of use, and used by
+// both transforms. A call of 4,096 samples at N = 4,096: one launch of 6.5 us,
+// where one real frame per workgroup, radix 4 over bit-reversed input and a
+// launch for the overlap-add took 16.8 + 3.3 us; 262,144 samples after a PSD of
+// 131,072: 108 -> 22 us.
 #include "spiir_internal.h"
 
-#include <atomic>
+#include <algorithm>
 
 namespace spiir {
 namespace {
 
-constexpr int kThreads = 256;      // overlap-add and PSD launches
-constexpr int kFftThreads = 1024;  // one frame per workgroup
+constexpr int kThreads = 256;
 
-__device__ inline int bitrev(int i, int logn) { return (int)(__brev((unsigned)i) >> (32 - logn)); }
-
-// LDS position of frame element i: inside each aligned block of 16 elements,
-// bits 4-5 of i are XORed into bits 0-1 and 2-3. The first two radix-2^2
-// passes have 16 lanes touching elements 4 (s = 0) or 16 (s = 2) apart, which
-// land on 4 bank groups unswizzled (4-way conflicts) and on 16 swizzled; the
-// later passes touch 16 consecutive elements either way. A bijection on
-// [0, n), applied to every access of the frame buffer.
-__device__ inline int sw(int i) {
-    const int m = (i >> 4) & 3;
-    return i ^ (m | (m << 2));
-}
-
-__device__ inline float2 cmul(float2 a, float2 b) {
+__device__ __forceinline__ float2 cmul(float2 a, float2 b) {
     return make_float2(a.x * b.x - a.y * b.y, a.x * b.y + a.y * b.x);
 }
+__device__ __forceinline__ float2 cmulc(float2 a, float2 b) {   // a * conj(b)
+    return make_float2(a.x * b.x + a.y * b.y, a.y * b.x - a.x * b.y);
+}
+__device__ __forceinline__ float2 cadd(float2 a, float2 b) { return make_float2(a.x + b.x, a.y + b.y); }
+__device__ __forceinline__ float2 csub(float2 a, float2 b) { return make_float2(a.x - b.x, a.y - b.y); }
+// a * (-i) forward, a * i inverse
+template <bool INV>
+__device__ __forceinline__ float2 rot90(float2 a) {
+    return INV ? make_float2(-a.y, a.x) : make_float2(a.y, -a.x);
+}
 
-// In-place radix-2 decimation-in-time over bit-reversed input, two stages per
-// pass: stage s combines pairs h = 2^s apart with exp(-2 pi i pos / 2h), stage
-// s+1 pairs 2h apart with exp(-2 pi i pos' / 4h). The four elements
-// b, b+h, b+2h, b+3h of a group (b = its 4h-block start + pos, pos < h) are
-// closed under both stages, so each thread takes whole groups through both in
-// registers: one LDS exchange and one barrier per two stages. An odd stage
-// count ends with one plain radix-2 stage.
-__device__ void fft_stages(float2 *buf, const float2 *tw, int n, int logn) {
-    int s = 0;
-    for (; s + 1 < logn; s += 2) {
-        const int h = 1 << s;
-        const int st1 = n >> (s + 1), st2 = n >> (s + 2);
-        for (int q = threadIdx.x; q < n / 4; q += kFftThreads) {
-            const int pos = q & (h - 1);
-            const int b = ((q >> s) << (s + 2)) + pos;
-            const float2 w1 = tw[pos * st1];
-            const float2 w2a = tw[pos * st2], w2b = tw[(pos + h) * st2];
-            const int e0 = sw(b), e1 = sw(b + h), e2 = sw(b + 2 * h), e3 = sw(b + 3 * h);
-            const float2 a0 = buf[e0], a1 = cmul(buf[e1], w1), a2 = buf[e2], a3 = cmul(buf[e3], w1);
-            const float2 b0 = make_float2(a0.x + a1.x, a0.y + a1.y), b1 = make_float2(a0.x - a1.x, a0.y - a1.y);
-            const float2 c2 = cmul(make_float2(a2.x + a3.x, a2.y + a3.y), w2a);
-            const float2 c3 = cmul(make_float2(a2.x - a3.x, a2.y - a3.y), w2b);
-            buf[e0] = make_float2(b0.x + c2.x, b0.y + c2.y);
-            buf[e2] = make_float2(b0.x - c2.x, b0.y - c2.y);
-            buf[e1] = make_float2(b1.x + c3.x, b1.y + c3.y);
-            buf[e3] = make_float2(b1.x - c3.x, b1.y - c3.y);
-        }
-        __syncthreads();
+// Frequency digits: position p of the transformed frame holds frequency f when
+// the base-8 digits of f, lowest first, are those of p, highest first (the last
+// digit has the remaining 1 to 3 bits).
+__device__ __forceinline__ int pos_of(int f, int logn) {
+    int p = 0, left = logn;
+    while (left > 3) {
+        left -= 3;
+        p |= (f & 7) << left;
+        f >>= 3;
     }
-    if (s < logn) {
-        const int h = 1 << s;
-        const int step = n >> (s + 1);
-        for (int q = threadIdx.x; q < n / 2; q += kFftThreads) {
-            const int pos = q & (h - 1);
-            const int i0 = ((q >> s) << (s + 1)) + pos;
-            const int p0 = sw(i0), p1 = sw(i0 + h);
-            const float2 u = buf[p0], v = cmul(buf[p1], tw[pos * step]);
-            buf[p0] = make_float2(u.x + v.x, u.y + v.y);
-            buf[p1] = make_float2(u.x - v.x, u.y - v.y);
+    return p | f;
+}
+
+// LDS position of frame element p: bits 3-7 are XORed into bits 0-4, so that
+// the strided accesses of every pass (elements 1, 8 and 64 apart over the lanes)
+// take the 32 pairs of banks once per half wave. Linear over bits: a sum of
+// parts with disjoint bits maps to the XOR of their images.
+__device__ __forceinline__ constexpr int sw(int p) { return p ^ ((p >> 3) & 31); }
+
+template <bool INV>
+__device__ __forceinline__ void dft4(float2 &c0, float2 &c1, float2 &c2, float2 &c3) {
+    const float2 s0 = cadd(c0, c2), s1 = csub(c0, c2), s2 = cadd(c1, c3), s3 = rot90<INV>(csub(c1, c3));
+    c0 = cadd(s0, s2);
+    c1 = cadd(s1, s3);
+    c2 = csub(s0, s2);
+    c3 = csub(s1, s3);
+}
+
+template <bool INV>
+__device__ __forceinline__ void dft8(float2 (&v)[8]) {
+    constexpr float r = 0.70710678118654752440f;
+    float2 a0 = cadd(v[0], v[4]), a1 = cadd(v[1], v[5]), a2 = cadd(v[2], v[6]), a3 = cadd(v[3], v[7]);
+    float2 b0 = csub(v[0], v[4]), b1 = csub(v[1], v[5]), b2 = csub(v[2], v[6]), b3 = csub(v[3], v[7]);
+    // times exp(-+ i pi k / 4)
+    const float2 q1 = rot90<INV>(b1), q3 = rot90<INV>(b3);
+    b1 = make_float2((b1.x + q1.x) * r, (b1.y + q1.y) * r);
+    b2 = rot90<INV>(b2);
+    b3 = make_float2((q3.x - b3.x) * r, (q3.y - b3.y) * r);
+    dft4<INV>(a0, a1, a2, a3);
+    dft4<INV>(b0, b1, b2, b3);
+    v[0] = a0;
+    v[1] = b0;
+    v[2] = a1;
+    v[3] = b1;
+    v[4] = a2;
+    v[5] = b2;
+    v[6] = a3;
+    v[7] = b3;
+}
+
+// N-point transform of one group of N/8 threads, 8 elements each. Pass s of
+// the kPasses radix-8 passes takes blocks of N >> 3s elements; the last pass
+// takes each thread's 8 consecutive elements in transforms of kLast.
+template <int LOGN>
+struct Fft {
+    static constexpr int N = 1 << LOGN;
+    static constexpr int T = N / 8;
+    static constexpr int kPasses = (LOGN + 2) / 3 - 1;
+    static constexpr int kLast = N >> (3 * kPasses);
+    static constexpr int kGroup = T < 64 ? 64 : T;   // threads per workgroup
+
+    float2 v[8];
+    float2 w[kPasses][7];
+
+    static constexpr int span(int s) { return N >> (3 * (s + 1)); }
+    static __device__ __forceinline__ int base(int s, int t) {
+        const int m = span(s);
+        return (t / m) * (8 * m) + (t & (m - 1));
+    }
+    // table of pass s: exp(-2 pi i q pos / (8 span)), q = 1..7 by pos
+    __device__ __forceinline__ void twiddles(const float2 *__restrict__ tw, int t) {
+#pragma unroll
+        for (int s = 0; s < kPasses; ++s) {
+            const int m = span(s);
+#pragma unroll
+            for (int q = 1; q < 8; ++q) w[s][q - 1] = tw[(q - 1) * m + (t & (m - 1))];
+            tw += 7 * m;
         }
-        __syncthreads();
+    }
+    __device__ __forceinline__ void put(float2 *buf, int b, int m) {
+        b = sw(b);
+#pragma unroll
+        for (int k = 0; k < 8; ++k) buf[b ^ sw(k * m)] = v[k];
+    }
+    __device__ __forceinline__ void get(const float2 *buf, int b, int m) {
+        b = sw(b);
+#pragma unroll
+        for (int k = 0; k < 8; ++k) v[k] = buf[b ^ sw(k * m)];
+    }
+    template <bool INV>
+    __device__ __forceinline__ void last() {
+        if constexpr (kLast == 8) {
+            dft8<INV>(v);
+        } else if constexpr (kLast == 4) {
+            dft4<INV>(v[0], v[1], v[2], v[3]);
+            dft4<INV>(v[4], v[5], v[6], v[7]);
+        } else {
+#pragma unroll
+            for (int k = 0; k < 8; k += 2) {
+                const float2 u = v[k];
+                v[k] = cadd(u, v[k + 1]);
+                v[k + 1] = csub(u, v[k + 1]);
+            }
+        }
+    }
+    // v[k] = element t + k T in; position 8 t + k out. Each pass stores where it
+    // loaded, so one barrier per exchange is enough.
+    __device__ __forceinline__ void forward(float2 *buf, int t) {
+#pragma unroll
+        for (int s = 0; s < kPasses; ++s) {
+            dft8<false>(v);
+#pragma unroll
+            for (int q = 1; q < 8; ++q) v[q] = cmul(v[q], w[s][q - 1]);
+            put(buf, base(s, t), span(s));
+            __syncthreads();
+            if (s + 1 < kPasses)
+                get(buf, base(s + 1, t), span(s + 1));
+            else
+                get(buf, 8 * t, 1);
+        }
+        last<false>();
+    }
+    // the transposed steps: position 8 t + k in, element t + k T out
+    __device__ __forceinline__ void inverse(float2 *buf, int t) {
+        last<true>();
+        put(buf, 8 * t, 1);
+#pragma unroll
+        for (int s = kPasses - 1; s >= 0; --s) {
+            __syncthreads();
+            get(buf, base(s, t), span(s));
+#pragma unroll
+            for (int q = 1; q < 8; ++q) v[q] = cmulc(v[q], w[s][q - 1]);
+            dft8<true>(v);
+            if (s > 0) put(buf, base(s, t), span(s));
+        }
+    }
+};
+
+// Hop j = 0..nf (group j of the grid; nf is the stored half for the next call).
+// Half frame b of the stream is hist for b = 0 and x + (b - 1) H after it;
+// frame j has the half frames j and j + 1.
+template <int LOGN>
+__global__ void __launch_bounds__(Fft<LOGN>::kGroup)
+    wh_hops_kernel(const float *__restrict__ hist, const float *__restrict__ x, int64_t nf,
+                   const float *__restrict__ wtab, const float2 *__restrict__ tw, const float *__restrict__ inv,
+                   const float *__restrict__ pend, float *__restrict__ pend_new, float *__restrict__ hist_new,
+                   float *__restrict__ out) {
+    using F = Fft<LOGN>;
+    constexpr int T = F::T, H = F::N / 2, kPer = F::kGroup / T;
+    __shared__ float2 lds[F::kGroup * 8];
+    const int t = threadIdx.x & (T - 1);
+    float2 *buf = lds + (threadIdx.x / T) * F::N;
+    const int64_t j = (int64_t)blockIdx.x * kPer + threadIdx.x / T;
+    const bool live = j <= nf, prev = live && j > 0, next = j < nf;
+    // half frames j - 1, j, j + 1
+    const float *h0 = j <= 1 ? hist : x + (j - 2) * H, *h1 = j == 0 ? hist : x + (j - 1) * H, *h2 = x + j * H;
+    F f;
+    float s[12];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        s[k] = prev ? h0[t + k * T] : 0.f;
+        s[4 + k] = live ? h1[t + k * T] : 0.f;
+        s[8 + k] = next ? h2[t + k * T] : 0.f;
+    }
+    float win[8];
+#pragma unroll
+    for (int k = 0; k < 8; ++k) win[k] = wtab[t + k * T];
+    f.twiddles(tw, t);
+    const float4 i0 = *reinterpret_cast<const float4 *>(inv + 8 * t);
+    const float4 i1 = *reinterpret_cast<const float4 *>(inv + 8 * t + 4);
+#pragma unroll
+    for (int k = 0; k < 8; ++k)
+        f.v[k] = make_float2(prev ? win[k] * s[k] : 0.f, next ? win[k] * s[4 + k] : 0.f);
+    f.forward(buf, t);
+    const float g[8] = {i0.x, i0.y, i0.z, i0.w, i1.x, i1.y, i1.z, i1.w};
+#pragma unroll
+    for (int k = 0; k < 8; ++k) f.v[k] = make_float2(f.v[k].x * g[k], f.v[k].y * g[k]);
+    f.inverse(buf, t);
+    constexpr float scale = 1.0f / (float)F::N;
+    if (!live) return;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        const int i = t + k * T;
+        const float before = prev ? f.v[k + 4].x * scale : pend[i];
+        if (next) {
+            out[j * H + i] = f.v[k].y * scale + before;
+        } else {
+            pend_new[i] = before;
+            hist_new[i] = s[4 + k];
+        }
     }
 }
 
-// Frame j covers samples jH .. jH + N - 1 of the concatenation hist[0..hlen) ++ x.
-// PSD mode: pw[j][f] = |X_j[f]|^2 for f = 0..H. Whitening mode: y[j][t] = the
-// inverse DFT of X_j[f] * inv[min(f, N - f)], t = 0..N-1.
-template <bool PSD>
-__global__ __launch_bounds__(kFftThreads) void wh_frames_kernel(const float *__restrict__ hist, int64_t hlen,
-                                                                const float *__restrict__ x,
-                                                                const float *__restrict__ wtab,
-                                                                const float2 *__restrict__ tw_g, int n, int logn,
-                                                                const float *__restrict__ inv,
-                                                                float *__restrict__ y, float *__restrict__ pw) {
-    extern __shared__ float2 buf[];   // [n] data, then [n/2] twiddles
-    float2 *tw = buf + n;
-    const int H = n / 2;
-    const int64_t base = (int64_t)blockIdx.x * H;
-    for (int k = threadIdx.x; k < H; k += kFftThreads) tw[k] = tw_g[k];
-    for (int i = threadIdx.x; i < n; i += kFftThreads) {
-        const int64_t gi = base + i;
-        const float v = gi < hlen ? hist[gi] : x[gi - hlen];
-        buf[sw(bitrev(i, logn))] = make_float2(wtab[i] * v, 0.0f);
-    }
+// Power of the training frames 2j and 2j + 1 in one transform Z of the two:
+// |X_2j[f]|^2 + |X_2j+1[f]|^2 = (|Z[f]|^2 + |Z[N - f]|^2) / 2, f = 0..H.
+template <int LOGN>
+__global__ void __launch_bounds__(Fft<LOGN>::kGroup)
+    wh_power_kernel(const float *__restrict__ x, int64_t frames, const float *__restrict__ wtab,
+                    const float2 *__restrict__ tw, float *__restrict__ pw) {
+    using F = Fft<LOGN>;
+    constexpr int T = F::T, H = F::N / 2, kPer = F::kGroup / T;
+    __shared__ float2 lds[F::kGroup * 8];
+    const int t = threadIdx.x & (T - 1);
+    float2 *buf = lds + (threadIdx.x / T) * F::N;
+    const int64_t j = (int64_t)blockIdx.x * kPer + threadIdx.x / T;
+    const bool first = 2 * j < frames, second = 2 * j + 1 < frames;
+    const float *h = x + 2 * j * H;
+    F f;
+    float s[12];
+#pragma unroll
+    for (int k = 0; k < 12; ++k) s[k] = (k < 8 ? first : second) ? h[t + k * T] : 0.f;
+    float win[8];
+#pragma unroll
+    for (int k = 0; k < 8; ++k) win[k] = wtab[t + k * T];
+    f.twiddles(tw, t);
+#pragma unroll
+    for (int k = 0; k < 8; ++k) f.v[k] = make_float2(win[k] * s[k], second ? win[k] * s[4 + k] : 0.f);
+    f.forward(buf, t);
+    f.put(buf, 8 * t, 1);
     __syncthreads();
-    fft_stages(buf, tw, n, logn);
-    if (PSD) {
-        for (int f = threadIdx.x; f <= H; f += kFftThreads) {
-            const float2 X = buf[sw(f)];
-            pw[(int64_t)blockIdx.x * (H + 1) + f] = X.x * X.x + X.y * X.y;
-        }
-        return;
+    if (!first) return;
+#pragma unroll
+    for (int k = 0; k < 5; ++k) {
+        const int q = t + k * T;
+        if (q > H) break;
+        const float2 a = buf[sw(pos_of(q, LOGN))], b = buf[sw(pos_of((F::N - q) & (F::N - 1), LOGN))];
+        pw[j * (H + 1) + q] = (float)(0.5 * ((double)a.x * a.x + (double)a.y * a.y + (double)b.x * b.x +
+                                             (double)b.y * b.y));
     }
-    // conj(X * inv), then bit-reversed order for the second forward transform
-    for (int f = threadIdx.x; f < n; f += kFftThreads) {
-        const float s = inv[min(f, n - f)];
-        const float2 X = buf[sw(f)];
-        buf[sw(f)] = make_float2(X.x * s, -X.y * s);
-    }
-    __syncthreads();
-    for (int i = threadIdx.x; i < n; i += kFftThreads) {
-        const int r = bitrev(i, logn);
-        if (i < r) {
-            const int pi = sw(i), pr = sw(r);
-            const float2 t = buf[pi];
-            buf[pi] = buf[pr];
-            buf[pr] = t;
-        }
-    }
-    __syncthreads();
-    fft_stages(buf, tw, n, logn);
-    const float scale = 1.0f / (float)n;
-    for (int t = threadIdx.x; t < n; t += kFftThreads) y[(int64_t)blockIdx.x * n + t] = buf[sw(t)].x * scale;
 }
 
-// S[f] = sum_j pw[j][f] / (frames * wsum2) in FP64; inv[f] = 1 / sqrt(S[f]), 0 where S <= 0.
-__global__ void wh_psd_reduce_kernel(const float *__restrict__ pw, int64_t frames, int H, double wsum2,
-                                     double *__restrict__ S, float *__restrict__ inv) {
-    const int f = blockIdx.x * blockDim.x + threadIdx.x;
-    if (f > H) return;
+__device__ __forceinline__ void put_inv(double v, int f, int logn, float *inv) {
+    const float s = v > 0.0 ? (float)(1.0 / sqrt(v)) : 0.0f;
+    inv[pos_of(f, logn)] = s;
+    inv[pos_of(((1 << logn) - f) & ((1 << logn) - 1), logn)] = s;
+}
+
+// S[f] = sum_j pw[j][f] / (frames * wsum2) in FP64 over the rows of the frame
+// pairs; inv[position of f and of N - f] = 1 / sqrt(S[f]), 0 where S <= 0. A
+// workgroup takes 32 frequencies and every thread every 8th row: with one
+// thread per frequency the serial loads of 63 rows took 17 us; 2.9 us now.
+__global__ void __launch_bounds__(kThreads)
+    wh_psd_reduce_kernel(const float *__restrict__ pw, int64_t rows, int64_t frames, int logn, double wsum2,
+                         double *__restrict__ S, float *__restrict__ inv) {
+    const int H = 1 << (logn - 1);
+    const int f = blockIdx.x * 32 + (threadIdx.x & 31);
+    const int r = threadIdx.x >> 5;
+    __shared__ double part[8][32];
     double acc = 0.0;
-    for (int64_t j = 0; j < frames; ++j) acc += (double)pw[j * (H + 1) + f];
+    if (f <= H) {
+#pragma unroll 4
+        for (int64_t j = r; j < rows; j += 8) acc += (double)pw[j * (H + 1) + f];
+    }
+    part[r][threadIdx.x & 31] = acc;
+    __syncthreads();
+    if (r > 0 || f > H) return;
+    acc = 0.0;
+#pragma unroll
+    for (int q = 0; q < 8; ++q) acc += part[q][threadIdx.x];
     const double v = acc / ((double)frames * wsum2);
     S[f] = v;
-    inv[f] = v > 0.0 ? (float)(1.0 / sqrt(v)) : 0.0f;
+    put_inv(v, f, logn, inv);
 }
 
-// inv[f] from a given S (host-set PSD).
-__global__ void wh_inv_kernel(const double *__restrict__ S, int H, float *__restrict__ inv) {
+// inv from a given S (host-set PSD).
+__global__ void wh_inv_kernel(const double *__restrict__ S, int logn, float *__restrict__ inv) {
     const int f = blockIdx.x * blockDim.x + threadIdx.x;
-    if (f > H) return;
-    const double v = S[f];
-    inv[f] = v > 0.0 ? (float)(1.0 / sqrt(v)) : 0.0f;
+    if (f <= 1 << (logn - 1)) put_inv(S[f], f, logn, inv);
 }
 
-// out[jH + t] = y[j][t] + (j == 0 ? pend[t] : y[j - 1][H + t]) for the nf frames;
-// block 0 also stores the last frame's second half (pending for the next call)
-// and the last H input samples (the next call's history).
-__global__ __launch_bounds__(kThreads) void wh_ola_kernel(const float *__restrict__ y, int64_t nf, int n,
-                                                          const float *__restrict__ pend,
-                                                          float *__restrict__ pend_new,
-                                                          const float *__restrict__ x, int64_t nx,
-                                                          float *__restrict__ hist_new, float *__restrict__ out) {
-    const int H = n / 2;
-    const int64_t m = (int64_t)blockIdx.x * kThreads + threadIdx.x;
-    if (m < nf * H) {
-        const int64_t j = m / H;
-        const int t = (int)(m - j * H);
-        const float prev = j == 0 ? pend[t] : y[(j - 1) * n + H + t];
-        out[m] = y[j * n + t] + prev;
-    }
-    if (blockIdx.x == 0)
-        for (int t = threadIdx.x; t < H; t += kThreads) {
-            pend_new[t] = y[(nf - 1) * n + H + t];
-            hist_new[t] = x[nx - H + t];
-        }
+__global__ void wh_copy_kernel(const float *a, float *b, int64_t n, const float *c, float *d, int64_t m) {
+    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (i < n) b[i] = a[i];
+    if (i < m) d[i] = c[i];
+}
+
+template <int LOGN>
+hipError_t hops(const WhitenHops &a, hipStream_t st) {
+    using F = Fft<LOGN>;
+    constexpr int per = F::kGroup / F::T;
+    hipLaunchKernelGGL(wh_hops_kernel<LOGN>, dim3((unsigned)(a.nf / per + 1)), dim3(F::kGroup), 0, st, a.hist, a.x,
+                       a.nf, a.wtab, a.tw, a.inv, a.pend, a.pend_new, a.hist_new, a.out);
+    return hipGetLastError();
+}
+
+template <int LOGN>
+hipError_t power(const float *x, int64_t frames, const float *wtab, const float2 *tw, float *pw, hipStream_t st) {
+    using F = Fft<LOGN>;
+    constexpr int per = F::kGroup / F::T;
+    const int64_t pairs = (frames + 1) / 2;
+    hipLaunchKernelGGL(wh_power_kernel<LOGN>, dim3((unsigned)((pairs + per - 1) / per)), dim3(F::kGroup), 0, st, x,
+                       frames, wtab, tw, pw);
+    return hipGetLastError();
 }
 
 }  // namespace
 
-hipError_t launch_wh_frames(bool psd, const float *hist, int64_t hlen, const float *x, const float *wtab,
-                            const float2 *tw, int n, int logn, const float *inv, float *y, float *pw,
-                            int64_t frames, hipStream_t st) {
-    if (frames <= 0) return hipSuccess;
-    const size_t lds = (size_t)n * sizeof(float2) + (size_t)(n / 2) * sizeof(float2);   // at most 96 KB
-    // the frame kernels may use more than the default 64 KB of dynamic LDS:
-    // raise their limit once per device
-    static std::atomic<uint64_t> attr_done{0};
-    int dev = 0;
-    hipError_t e = hipGetDevice(&dev);
-    if (e != hipSuccess) return e;
-    const uint64_t bit = 1ull << (dev & 63);
-    if (!(attr_done.load() & bit)) {
-        e = hipFuncSetAttribute(reinterpret_cast<const void *>(&wh_frames_kernel<true>),
-                                hipFuncAttributeMaxDynamicSharedMemorySize, 96 * 1024);
-        if (e == hipSuccess)
-            e = hipFuncSetAttribute(reinterpret_cast<const void *>(&wh_frames_kernel<false>),
-                                    hipFuncAttributeMaxDynamicSharedMemorySize, 96 * 1024);
-        if (e != hipSuccess) return e;
-        attr_done.fetch_or(bit);
+hipError_t launch_wh_hops(const WhitenHops &a, int logn, hipStream_t st) {
+    if (a.nf <= 0) return hipSuccess;
+    switch (logn) {
+        case 4: return hops<4>(a, st);
+        case 5: return hops<5>(a, st);
+        case 6: return hops<6>(a, st);
+        case 7: return hops<7>(a, st);
+        case 8: return hops<8>(a, st);
+        case 9: return hops<9>(a, st);
+        case 10: return hops<10>(a, st);
+        case 11: return hops<11>(a, st);
+        case 12: return hops<12>(a, st);
+        case 13: return hops<13>(a, st);
     }
-    if (psd)
-        hipLaunchKernelGGL(wh_frames_kernel<true>, dim3((unsigned)frames), dim3(kFftThreads), lds, st, hist, hlen,
-                           x, wtab, tw, n, logn, inv, y, pw);
-    else
-        hipLaunchKernelGGL(wh_frames_kernel<false>, dim3((unsigned)frames), dim3(kFftThreads), lds, st, hist, hlen,
-                           x, wtab, tw, n, logn, inv, y, pw);
-    return hipGetLastError();
+    return hipErrorInvalidValue;
 }
 
-hipError_t launch_wh_psd_reduce(const float *pw, int64_t frames, int H, double wsum2, double *S, float *inv,
+hipError_t launch_wh_power(const float *x, int64_t frames, const float *wtab, const float2 *tw, int logn, float *pw,
+                           hipStream_t st) {
+    if (frames <= 0) return hipSuccess;
+    switch (logn) {
+        case 4: return power<4>(x, frames, wtab, tw, pw, st);
+        case 5: return power<5>(x, frames, wtab, tw, pw, st);
+        case 6: return power<6>(x, frames, wtab, tw, pw, st);
+        case 7: return power<7>(x, frames, wtab, tw, pw, st);
+        case 8: return power<8>(x, frames, wtab, tw, pw, st);
+        case 9: return power<9>(x, frames, wtab, tw, pw, st);
+        case 10: return power<10>(x, frames, wtab, tw, pw, st);
+        case 11: return power<11>(x, frames, wtab, tw, pw, st);
+        case 12: return power<12>(x, frames, wtab, tw, pw, st);
+        case 13: return power<13>(x, frames, wtab, tw, pw, st);
+    }
+    return hipErrorInvalidValue;
+}
+
+hipError_t launch_wh_psd_reduce(const float *pw, int64_t frames, int logn, double wsum2, double *S, float *inv,
                                 hipStream_t st) {
-    hipLaunchKernelGGL(wh_psd_reduce_kernel, dim3((unsigned)((H + 1 + kThreads - 1) / kThreads)), dim3(kThreads), 0,
-                       st, pw, frames, H, wsum2, S, inv);
+    const int H = 1 << (logn - 1);
+    hipLaunchKernelGGL(wh_psd_reduce_kernel, dim3((unsigned)(H / 32 + 1)), dim3(kThreads), 0, st, pw,
+                       (frames + 1) / 2, frames, logn, wsum2, S, inv);
     return hipGetLastError();
 }
 
-hipError_t launch_wh_inv(const double *S, int H, float *inv, hipStream_t st) {
-    hipLaunchKernelGGL(wh_inv_kernel, dim3((unsigned)((H + 1 + kThreads - 1) / kThreads)), dim3(kThreads), 0, st, S,
-                       H, inv);
+hipError_t launch_wh_inv(const double *S, int logn, float *inv, hipStream_t st) {
+    const int H = 1 << (logn - 1);
+    hipLaunchKernelGGL(wh_inv_kernel, dim3((unsigned)(H / kThreads + 1)), dim3(kThreads), 0, st, S, logn, inv);
     return hipGetLastError();
 }
 
-hipError_t launch_wh_ola(const float *y, int64_t nf, int n, const float *pend, float *pend_new, const float *x,
-                         int64_t nx, float *hist_new, float *out, hipStream_t st) {
-    const int64_t total = nf * (n / 2);
-    const int64_t blocks = std::max<int64_t>(1, (total + kThreads - 1) / kThreads);
-    hipLaunchKernelGGL(wh_ola_kernel, dim3((unsigned)blocks), dim3(kThreads), 0, st, y, nf, n, pend, pend_new, x, nx,
-                       hist_new, out);
+hipError_t launch_wh_copy(const float *a, float *b, int64_t n, const float *c, float *d, int64_t m, hipStream_t st) {
+    const int64_t most = std::max(n, m);
+    if (most <= 0) return hipSuccess;
+    hipLaunchKernelGGL(wh_copy_kernel, dim3((unsigned)((most + kThreads - 1) / kThreads)), dim3(kThreads), 0, st, a, b,
+                       n, c, d, m);
     return hipGetLastError();
 }
 

@@ -18,14 +18,14 @@ struct spiir_whitener {
     int64_t B = 0;                 // most samples per piece (a multiple of H)
     double wsum2 = 0.0;            // sum of the squared window
     float *wtab = nullptr;         // [N] periodic Hann window
-    float2 *tw = nullptr;          // [N/2] exp(-2 pi i k / N)
+    float2 *tw = nullptr;          // twiddle factors of each radix-8 pass, in the order of use
     double *S = nullptr;           // [H+1] PSD
-    float *inv = nullptr;          // [H+1] 1 / sqrt(S)
+    float *inv = nullptr;          // [N] 1 / sqrt(S) in the transform's order of frequencies
     float *hist[2] = {nullptr, nullptr};  // last H input samples (double-buffered)
     float *pend[2] = {nullptr, nullptr};  // second half of the last frame's output
     int cur = 0;
-    float *y = nullptr;            // [B/H][N] frame outputs
-    float *pw = nullptr;           // [frames][H+1] power spectra of the PSD training frames
+    float *stage = nullptr;        // [B] copy of a piece whose output overlaps its input
+    float *pw = nullptr;           // [frame pairs][H+1] power spectra of the PSD training frames
     int64_t pw_frames = 0;
     bool has_psd = false;
 };
@@ -41,7 +41,7 @@ void wh_free(spiir_whitener *wh) {
         dfree(wh->hist[c]);
         dfree(wh->pend[c]);
     }
-    dfree(wh->y);
+    dfree(wh->stage);
     dfree(wh->pw);
 }
 
@@ -83,27 +83,31 @@ int spiir_whitener_create(spiir_whitener **out, int32_t frame_len, int32_t max_b
         delete wh;
         return code;
     };
+    std::vector<float2> tw;
+    for (int m = frame_len / 8; ; m /= 8) {   // blocks of 8 m elements: q = 1..7 by position
+        for (int q = 1; q < 8; ++q)
+            for (int p = 0; p < m; ++p) {
+                const double ang = -2.0 * M_PI * q * p / (8.0 * m);
+                tw.push_back(make_float2((float)std::cos(ang), (float)std::sin(ang)));
+            }
+        if (m <= 8) break;
+    }
     hipError_t e = dalloc(&wh->wtab, (size_t)frame_len);
-    if (e == hipSuccess) e = dalloc(&wh->tw, (size_t)H);
+    if (e == hipSuccess) e = dalloc(&wh->tw, tw.size());
     if (e == hipSuccess) e = dalloc(&wh->S, (size_t)H + 1);
-    if (e == hipSuccess) e = dalloc(&wh->inv, (size_t)H + 1);
+    if (e == hipSuccess) e = dalloc(&wh->inv, (size_t)frame_len);
     for (int c = 0; c < 2 && e == hipSuccess; ++c) {
         e = dalloc(&wh->hist[c], (size_t)H);
         if (e == hipSuccess) e = dalloc(&wh->pend[c], (size_t)H);
     }
-    if (e == hipSuccess) e = dalloc(&wh->y, (size_t)(B / H) * (size_t)frame_len);
+    if (e == hipSuccess) e = dalloc(&wh->stage, (size_t)B);
     if (e != hipSuccess) return bail(fail(SPIIR_ENOMEM, "device allocation failed: %s", hipGetErrorString(e)));
     std::vector<float> w(frame_len);
-    std::vector<float2> tw(H);
     double ws = 0.0;
     for (int t = 0; t < frame_len; ++t) {
         const double s1 = std::sin(M_PI * t / frame_len);
         w[t] = (float)(s1 * s1);
         ws += (s1 * s1) * (s1 * s1);
-    }
-    for (int k = 0; k < H; ++k) {
-        const double ang = -2.0 * M_PI * k / frame_len;
-        tw[k] = make_float2((float)std::cos(ang), (float)std::sin(ang));
     }
     wh->wsum2 = ws;
     e = hipMemcpy(wh->wtab, w.data(), w.size() * sizeof(float), hipMemcpyHostToDevice);
@@ -144,13 +148,12 @@ int spiir_whitener_estimate_psd(spiir_whitener *wh, const float *train, int64_t 
         HIPCHK(hipStreamSynchronize(st));
         dfree(wh->pw);
         wh->pw_frames = 0;
-        hipError_t e = dalloc(&wh->pw, (size_t)K * (size_t)(wh->H + 1));
+        hipError_t e = dalloc(&wh->pw, (size_t)((K + 1) / 2) * (size_t)(wh->H + 1));
         if (e != hipSuccess) return fail(SPIIR_ENOMEM, "device allocation failed: %s", hipGetErrorString(e));
         wh->pw_frames = K;
     }
-    HIPCHK(launch_wh_frames(true, nullptr, 0, train, wh->wtab, wh->tw, wh->N, wh->logN, nullptr, nullptr, wh->pw, K,
-                            st));
-    HIPCHK(launch_wh_psd_reduce(wh->pw, K, wh->H, wh->wsum2, wh->S, wh->inv, st));
+    HIPCHK(launch_wh_power(train, K, wh->wtab, wh->tw, wh->logN, wh->pw, st));
+    HIPCHK(launch_wh_psd_reduce(wh->pw, K, wh->logN, wh->wsum2, wh->S, wh->inv, st));
     wh->has_psd = true;
     return SPIIR_OK;
 }
@@ -162,7 +165,7 @@ int spiir_whitener_set_psd(spiir_whitener *wh, const double *psd) {
     DeviceGuard guard(wh->device);
     HIPCHK(hipDeviceSynchronize());
     HIPCHK(hipMemcpy(wh->S, psd, (size_t)(wh->H + 1) * sizeof(double), hipMemcpyHostToDevice));
-    HIPCHK(launch_wh_inv(wh->S, wh->H, wh->inv, nullptr));
+    HIPCHK(launch_wh_inv(wh->S, wh->logN, wh->inv, nullptr));
     HIPCHK(hipDeviceSynchronize());
     wh->has_psd = true;
     return SPIIR_OK;
@@ -198,13 +201,39 @@ int spiir_whitener_process(spiir_whitener *wh, const float *x, int64_t n, float 
     if (!x || !out) return fail(SPIIR_EINVAL, "null device pointer");
     DeviceGuard guard(wh->device);
     hipStream_t st = as_stream(stream);
-    for (int64_t P = 0; P < n; P += wh->B) {
-        const int64_t np = std::min<int64_t>(wh->B, n - P);
-        const int64_t nf = np / wh->H;
+    auto hops = [&](const float *in, int64_t np, float *to) {
         const int c = wh->cur;
-        HIPCHK(launch_wh_frames(false, wh->hist[c], wh->H, x + P, wh->wtab, wh->tw, wh->N, wh->logN, wh->inv, wh->y,
-                                nullptr, nf, st));
-        HIPCHK(launch_wh_ola(wh->y, nf, wh->N, wh->pend[c], wh->pend[c ^ 1], x + P, np, wh->hist[c ^ 1], out + P, st));
+        WhitenHops a;
+        a.hist = wh->hist[c];
+        a.x = in;
+        a.nf = np / wh->H;
+        a.wtab = wh->wtab;
+        a.tw = wh->tw;
+        a.inv = wh->inv;
+        a.pend = wh->pend[c];
+        a.pend_new = wh->pend[c ^ 1];
+        a.hist_new = wh->hist[c ^ 1];
+        a.out = to;
+        wh->cur ^= 1;
+        return launch_wh_hops(a, wh->logN, st);
+    };
+    const uintptr_t xi = (uintptr_t)x, oi = (uintptr_t)out, len = (uintptr_t)n * sizeof(float);
+    if (xi < oi + len && oi < xi + len) {   // a hop's group reads samples that another's writes: take a copy
+        for (int64_t P = 0; P < n; P += wh->B) {
+            const int64_t np = std::min<int64_t>(wh->B, n - P);
+            HIPCHK(launch_wh_copy(x + P, wh->stage, np, nullptr, nullptr, 0, st));
+            HIPCHK(hops(wh->stage, np, out + P));
+        }
+        return SPIIR_OK;
+    }
+    // One launch for the call, however long (262,144 samples in 4 pieces of 65,536 left most
+    // compute units without a frame). The stored halves still change places once per piece of
+    // max_block, so that a captured call of an even number of pieces leaves them where its
+    // replay takes them from.
+    HIPCHK(hops(x, n, out));
+    if ((n + wh->B - 1) / wh->B % 2 == 0) {
+        const int c = wh->cur;
+        HIPCHK(launch_wh_copy(wh->hist[c], wh->hist[c ^ 1], wh->H, wh->pend[c], wh->pend[c ^ 1], wh->H, st));
         wh->cur ^= 1;
     }
     return SPIIR_OK;
