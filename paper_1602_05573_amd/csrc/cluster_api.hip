@@ -25,7 +25,8 @@ constexpr int64_t kMaxClusterN = (int64_t)1 << 40;
 // last W samples before the new final_end. The window sits at offset off of
 // buffer cur: a step only moves off past the dropped samples, and the next
 // push with data writes the kept samples and the new block into the other
-// buffer in one launch (ping-pong buffers).
+// buffer (ping-pong buffers), in the clustering launch itself where the window
+// is short, else in one launch before it.
 struct spiir_trigger_stream {
     int device = 0;
     float thr = 0.0f;
@@ -50,12 +51,17 @@ void ts_free(spiir_trigger_stream *ts) {
     ts->ws = nullptr;
 }
 
-// Clusters the window with candidates [final_end, new_end) and slides it.
-int ts_step(spiir_trigger_stream *ts, int64_t new_end, int64_t *idx, int32_t *tpl, float *val, int64_t cap,
-            int64_t *count, hipStream_t st) {
+// Clusters the window with candidates [final_end, new_end) and slides it; with
+// src the window is joined by the same launch.
+int ts_step(spiir_trigger_stream *ts, int64_t new_end, const ClusterSrc *src, int64_t *idx, int32_t *tpl, float *val,
+            int64_t cap, int64_t *count, hipStream_t st) {
     const int c = ts->cur;
-    HIPCHK(launch_cluster(ts->wm[c] + ts->off, ts->wj[c] + ts->off, ts->len, ts->thr, ts->W, ts->ws, cap, idx, tpl,
-                          val, count, st, ts->final_end - ts->base, new_end - ts->base, ts->base));
+    if (src)
+        HIPCHK(launch_cluster_small(*src, ts->thr, ts->W, cap, idx, tpl, val, count, st, ts->final_end - ts->base,
+                                    new_end - ts->base, ts->base));
+    else
+        HIPCHK(launch_cluster(ts->wm[c] + ts->off, ts->wj[c] + ts->off, ts->len, ts->thr, ts->W, ts->ws, cap, idx,
+                              tpl, val, count, st, ts->final_end - ts->base, new_end - ts->base, ts->base));
     ts->final_end = new_end;
     const int64_t keep_from = std::max(ts->base, ts->final_end - ts->W) - ts->base;
     ts->off += keep_from;
@@ -141,7 +147,22 @@ int spiir_trigger_stream_push(spiir_trigger_stream *ts, const float *max_dev, co
     DeviceGuard guard(ts->device);
     hipStream_t st = as_stream(stream);
     const int c = ts->cur;
-    if (n > 0 && ts->off > 0) {   // kept samples and the block into the other buffer
+    ClusterSrc src;
+    const bool small = n > 0 && ts->len + n <= kClusterSmall;
+    if (small) {                  // the clustering launch joins them
+        src.m0 = ts->wm[c] + ts->off;
+        src.j0 = ts->wj[c] + ts->off;
+        src.keep = ts->len;
+        src.m1 = max_dev;
+        src.j1 = argmax_dev;
+        src.n = n;
+        const int to = ts->off > 0 ? c ^ 1 : c;
+        src.copy_from = ts->off > 0 ? 0 : ts->len;
+        src.dm = ts->wm[to];
+        src.dj = ts->wj[to];
+        ts->cur = to;
+        ts->off = 0;
+    } else if (n > 0 && ts->off > 0) {   // kept samples and the block into the other buffer
         HIPCHK(launch_ts_compose(ts->wm[c] + ts->off, ts->wj[c] + ts->off, ts->len, max_dev, argmax_dev, n,
                                  ts->wm[c ^ 1], ts->wj[c ^ 1], st));
         ts->cur = c ^ 1;
@@ -153,7 +174,7 @@ int spiir_trigger_stream_push(spiir_trigger_stream *ts, const float *max_dev, co
     ts->len += n;
     ts->total += n;
     const int64_t new_end = std::max(ts->final_end, ts->total - ts->W);
-    return ts_step(ts, new_end, index_dev, template_dev, snr_dev, capacity, count_dev, st);
+    return ts_step(ts, new_end, small ? &src : nullptr, index_dev, template_dev, snr_dev, capacity, count_dev, st);
 }
 
 int spiir_trigger_stream_flush(spiir_trigger_stream *ts, int64_t *index_dev, int32_t *template_dev, float *snr_dev,
@@ -162,7 +183,7 @@ int spiir_trigger_stream_flush(spiir_trigger_stream *ts, int64_t *index_dev, int
     int rc = ts_check_out(index_dev, template_dev, snr_dev, capacity, count_dev);
     if (rc) return rc;
     DeviceGuard guard(ts->device);
-    return ts_step(ts, ts->total, index_dev, template_dev, snr_dev, capacity, count_dev, as_stream(stream));
+    return ts_step(ts, ts->total, nullptr, index_dev, template_dev, snr_dev, capacity, count_dev, as_stream(stream));
 }
 
 int spiir_cluster_workspace_size(int64_t n, size_t *nbytes) {
