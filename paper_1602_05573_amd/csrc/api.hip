@@ -122,6 +122,7 @@ struct spiir_bank {
     int32_t *group_lo = nullptr;
     int nseg = 1;                 // most time segments per streaming launch
     bool seg_auto = false;        // the call chooses their number and length (plan_segments)
+    bool lone_wg = false;         // one workgroup of the full pass per compute unit
     int64_t slots_main = 1, slots_pre = 1;   // resident workgroups of the full / the state pass
     size_t lds_tile = 0;          // LDS of a full pass whose window stays in global memory
     float4 *seg_end = nullptr, *seg_start = nullptr;
@@ -505,6 +506,7 @@ int create_bank(spiir_bank **out, int32_t T, const int64_t *off, const double *a
         bk->lds = gs.lds;
         bk->slots_main = (int64_t)df.n_cu * std::max(1, forward_occupancy(fl, wpg, gs.lds));
     }
+    bk->lone_wg = bk->slots_main == df.n_cu;
     bk->slots_pre = (int64_t)df.n_cu * std::max(1, state_occupancy(fl, wpg, bk->base_args(), bk->xlds));
     if (o.time_split >= 2) {
         bk->nseg = std::min<int>(o.time_split, std::max(1, max_block / L));
@@ -609,9 +611,10 @@ struct CallScratch {
 };
 
 // Shared driver of the streaming calls (snr rows or fused keys). cs = null:
-// the bank's own buffers (the global strain window grown on demand).
+// the bank's own buffers (the global strain window grown on demand). group_plan:
+// the segments of a bank in a group (its results are then those of the group).
 int stream_call(spiir_bank *bk, const float *x, int64_t n, int mode, float *snr, int64_t ld,
-                float *mx, int32_t *am, hipStream_t st, const CallScratch *cs = nullptr) {
+                float *mx, int32_t *am, hipStream_t st, const CallScratch *cs = nullptr, bool group_plan = false) {
     DeviceGuard guard(bk->device);
     const float *hist = bk->hist[bk->hist_cur];
     float *xwin = bk->xwin;
@@ -652,7 +655,8 @@ int stream_call(spiir_bank *bk, const float *x, int64_t n, int mode, float *snr,
             a.keys = keys;
             a.ld = keys_ld;
         }
-        const SegPlan sp = plan_segments(bk, np, (cs && cs->nseg > 0) ? cs->nseg : bk->nseg);
+        const SegPlan sp = group_plan ? plan_group_segments(bk, np)
+                                      : plan_segments(bk, np, (cs && cs->nseg > 0) ? cs->nseg : bk->nseg);
         const int nseg = sp.nseg;
         a.seg_len = sp.len;
         // the next call's history is written by a launch that follows every
@@ -691,8 +695,8 @@ int stream_call(spiir_bank *bk, const float *x, int64_t n, int mode, float *snr,
 namespace spiir {
 namespace host {
 
-int bank_stream_z(spiir_bank *bk, const float *x, int64_t n, float *z, int64_t ld, hipStream_t st) {
-    return stream_call(bk, x, n, kModeZ, z, ld, nullptr, nullptr, st);
+int bank_stream_z(spiir_bank *bk, const float *x, int64_t n, float *z, int64_t ld, hipStream_t st, bool group_plan) {
+    return stream_call(bk, x, n, kModeZ, z, ld, nullptr, nullptr, st, nullptr, group_plan);
 }
 
 int bank_create_capped(spiir_bank **out, int32_t T, const int64_t *off, const double *a, const double *b,
@@ -702,16 +706,20 @@ int bank_create_capped(spiir_bank **out, int32_t T, const int64_t *off, const do
 
 int bank_wpg(const spiir_bank *bk) { return bk->lay.wpg; }
 
+bool bank_fills_device(const spiir_bank *bk, int64_t n) {
+    const int64_t g = bk->lay.groups, slots = bk->slots_main;
+    return bk->lone_wg && plan_segments(bk, n, bk->nseg).nseg == 1 && 8 * g >= 7 * ((g + slots - 1) / slots * slots);
+}
+
 bool banks_multi_ok(spiir_bank *const *bks, int nb, const int64_t *n) {
     if (nb < 1 || nb > kMultiMax) return false;
     const spiir_bank *b0 = bks[0];
     for (int b = 0; b < nb; ++b) {
         const spiir_bank *bk = bks[b];
-        if (!bk || !bk->xlds || bk->n_split || bk->nseg < 2 || !bk->tev0.empty()) return false;
+        if (!bk || !bk->xlds || bk->n_split) return false;
         if (bk->device != b0->device || bk->lay.fl != b0->lay.fl || bk->lay.wpg != b0->lay.wpg)
             return false;
         if (n[b] <= 0 || n[b] > bk->max_block) return false;
-        if (plan_group_segments(bk, n[b]).nseg < 2) return false;   // the call would not be time-split
     }
     return true;
 }

@@ -55,18 +55,24 @@ int resolve_device(int32_t device, int &dev);
 inline hipStream_t as_stream(void *s) { return reinterpret_cast<hipStream_t>(s); }
 
 // Bank operations used by the multi-rate bank (the bank stays opaque here).
-int bank_stream_z(spiir_bank *bk, const float *x, int64_t n, float *z, int64_t ld, hipStream_t st);
+int bank_stream_z(spiir_bank *bk, const float *x, int64_t n, float *z, int64_t ld, hipStream_t st,
+                  bool group_plan = false);
 int bank_create_capped(spiir_bank **out, int32_t T, const int64_t *off, const double *a, const double *b,
                        const int32_t *d, const spiir_bank_opts &o, int seg_cap);
 int bank_hist_cur(const spiir_bank *bk);
 void bank_set_hist_cur(spiir_bank *bk, int v);
 bool bank_timing_on(const spiir_bank *bk);
 int bank_wpg(const spiir_bank *bk);
+// Whether a call of n samples leaves no room for other work: not cut in time,
+// one workgroup per compute unit, on at least 7/8 of them in every round.
+bool bank_fills_device(const spiir_bank *bk, int64_t n);
 // Whether banks bks[0..nb) can take streaming z calls of n[b] samples through
-// banks_stream_z_multi: each call one time-split piece (at most max_block
-// samples, two segments or more) with the strain window in LDS, no split
-// templates, no kernel timing, one device, and the same filters per lane,
-// tile length and workgroup size.
+// banks_stream_z_multi: each call one piece (at most max_block samples, of one
+// segment or more) with the strain window in LDS, no split templates, one
+// device, and the same filters per lane and workgroup size. Calls too short to
+// be cut are taken too: 16 templates on 5 levels took 187 us for 512 samples
+// and 181 us for 4,096 with a launch and two events per level (the host's
+// time), 39 and 47 us as a group.
 bool banks_multi_ok(spiir_bank *const *bks, int nb, const int64_t *n);
 // Streaming z calls of several banks, bank b on x[b][0..n[b]) into z[b] (row
 // stride ld[b]), as one launch per time-split pass for all of them; the same

@@ -777,7 +777,9 @@ template <int FL, int MODE, bool XLDS, bool PARTS>
 __device__ __forceinline__ void seg_item(const FwdArgs &p, unsigned bid, unsigned char *smem) {
     const int g = p.gbase + bid % p.groups, seg = bid / p.groups;
     SegCtx sc = segment(p, seg);
-    if (p.chain_inline && seg > 0) {
+    if (sc.tn == p.n) {   // the one segment of a bank in a group
+        sc.st_in = p.state;
+    } else if (p.chain_inline && seg > 0) {
         sc.st_in = p.seg_end;
         sc.seg = seg;
     } else {
@@ -860,6 +862,7 @@ __device__ __forceinline__ void chain_item(const FwdArgs &p, int fl, int nseg, u
         if (i < p.hist_next.dmax) hist_copy_at(p.hist_next, i);
         return;
     }
+    if (nseg < 2) return;
     const int64_t i = (int64_t)bid * 64 + (threadIdx.x & 63), sl = p.seg_slot0 + i;
     bool act = i < p.seg_stride;  // every slot, padding included (its states stay zero)
     if (act && p.only_tpl >= 0) {
@@ -1699,9 +1702,12 @@ hipError_t launch_multi_t(const MultiFwd &args, int wpg, size_t lds, size_t lds_
         chain = chain || !m.a[b].chain_inline;
     }
     for (int b = 0; b < n && chain; ++b) m.a[b].chain_inline = 0;   // one bank too many: the launch serves all
-    hipLaunchKernelGGL((fwd_pre_multi_kernel<FL>), dim3((unsigned)m.pre_first[n]), dim3(wpg * 64), lds_pre, st, m);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
+    hipError_t e = hipSuccess;
+    if (m.pre_first[n] > 0) {
+        hipLaunchKernelGGL((fwd_pre_multi_kernel<FL>), dim3((unsigned)m.pre_first[n]), dim3(wpg * 64), lds_pre, st, m);
+        e = hipGetLastError();
+        if (e != hipSuccess) return e;
+    }
     if (chain) {
         hipLaunchKernelGGL(seg_chain_multi_kernel, dim3((unsigned)m.chain_first[n]), dim3(256), 0, st, m, FL);
         e = hipGetLastError();

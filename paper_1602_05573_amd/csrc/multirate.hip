@@ -46,19 +46,36 @@ __global__ __launch_bounds__(kThreads) void mr_decimate_kernel(const float *__re
 }
 
 constexpr int kMaxTaps = 64;
+typedef float f4v __attribute__((ext_vector_type(4)));
 
 // Output pairs (2m, 2m + 1) read the same W samples:
 // out(2m) += sum_k g[2k] W(m - k), out(2m + 1) += sum_k g[2k + 1] W(m - k),
 // with s[sb + m[u] - k] the staged W(m - k). Each of the NU pairs of a lane
 // accumulates its taps in ascending order, as the plain per-output sum does,
-// so both forms give the same values.
+// so both forms give the same values. Two tap pairs per step: their taps are
+// one 16-byte read and their samples neighbours.
 template <int NU>
-__device__ __forceinline__ void interp_pairs(const float2 *s, int sb, const float *sg, int lg, const int (&m)[NU],
-                                             float2 (&ev)[NU], float2 (&od)[NU]) {
-    // whole (even, odd) tap pairs, then an odd tap count's last even tap: the
-    // loop body has no per-tap condition
-    const int kp = lg >> 1;
-    for (int k = 0; k < kp; ++k) {
+__device__ __forceinline__ void interp_pairs(const float2 *s, int sb, const float *sg, int lg, const int *m,
+                                             float2 *ev, float2 *od) {
+    const int kp = lg >> 1;   // whole (even, odd) tap pairs
+    int k = 0;
+    for (; k + 2 <= kp; k += 2) {
+        const f4v g = *reinterpret_cast<const f4v *>(sg + 2 * k);
+#pragma unroll
+        for (int u = 0; u < NU; ++u) {
+            const float2 *p = s + (sb + m[u] - k - 1);
+            const float2 x = p[1], y = p[0];
+            ev[u].x = fmaf(g.x, x.x, ev[u].x);
+            ev[u].y = fmaf(g.x, x.y, ev[u].y);
+            od[u].x = fmaf(g.y, x.x, od[u].x);
+            od[u].y = fmaf(g.y, x.y, od[u].y);
+            ev[u].x = fmaf(g.z, y.x, ev[u].x);
+            ev[u].y = fmaf(g.z, y.y, ev[u].y);
+            od[u].x = fmaf(g.w, y.x, od[u].x);
+            od[u].y = fmaf(g.w, y.y, od[u].y);
+        }
+    }
+    if (k < kp) {
         const float ge = sg[2 * k], go = sg[2 * k + 1];
 #pragma unroll
         for (int u = 0; u < NU; ++u) {
@@ -69,7 +86,7 @@ __device__ __forceinline__ void interp_pairs(const float2 *s, int sb, const floa
             od[u].y = fmaf(go, x.y, od[u].y);
         }
     }
-    if (lg & 1) {
+    if (lg & 1) {   // an odd tap count's last even tap
         const float ge = sg[2 * kp];
 #pragma unroll
         for (int u = 0; u < NU; ++u) {
@@ -169,28 +186,58 @@ __global__ __launch_bounds__(kPyrThreads) void mr_pyramid_kernel(const float *__
 // taps; each output adds its taps in ascending order onto Z_r, as the plain
 // per-output sum does. The last tile writes every level's next history (the
 // last hh samples of W_r) to whist_new.
+//
+// Bound by LDS reads and FP32 issue about equally (1,024 templates, 5 levels,
+// 4,096 samples, 24 taps: 33.5 MB written at 1.7 TB/s in 20 us; 25 us before).
+// Hence two tap pairs per step, as many pairs per lane as the level's window
+// has, one 16-byte store and load per pair, every level's z loaded while the
+// level above is formed, and no barrier between levels, whose windows belong
+// to one wave.
 constexpr int kKeyChunk = 16;
 constexpr int kChainThreads = kKeyChunk * 64;
 constexpr int kTile = 512;
+// pairs per lane of a level's window: at most (kTile + kMaxTaps + 1) / 2 + 1 samples at
+// level 1 and fewer above, from an odd index on
+constexpr int kWinPairs = ((kTile + kMaxTaps + 1) / 2 + 3 + 127) / 128;
 constexpr int kChainLdsMax = 60 * 1024;   // dynamic LDS of mr_chain_kernel (static part: 384 bytes)
 
 __device__ __forceinline__ int floor_half(int v) { return v >= 0 ? v / 2 : -((-v + 1) / 2); }
 
-__device__ __forceinline__ float2 z_at(const float2 *zj, int q, int n) {
-    return zj && q < n ? zj[q] : make_float2(0.0f, 0.0f);
+// Pairs (2m, 2m + 1) of a level's z for m = m0 + 64 u + lane, 0 from n on or
+// without a row. A row starts at a multiple of its stride in its buffer, so an
+// even stride makes every pair one aligned 16-byte load.
+template <int NU>
+__device__ __forceinline__ void load_pairs(const float2 *zj, int64_t ld, int m0, int lane, int n, float2 (&ev)[NU],
+                                           float2 (&od)[NU]) {
+#pragma unroll
+    for (int u = 0; u < NU; ++u) ev[u] = od[u] = make_float2(0.0f, 0.0f);
+    if (!zj) return;
+    const bool pairs = (ld & 1) == 0;
+#pragma unroll
+    for (int u = 0; u < NU; ++u) {
+        const int q = 2 * (m0 + u * 64 + lane);
+        if (pairs && q + 1 < n) {
+            const f4v z = *reinterpret_cast<const f4v *>(zj + q);
+            ev[u] = make_float2(z.x, z.y);
+            od[u] = make_float2(z.z, z.w);
+        } else {
+            if (q < n) ev[u] = zj[q];
+            if (q + 1 < n) od[u] = zj[q + 1];
+        }
+    }
 }
 
 // Indices inside a piece fit int32 (a piece has at most max_block samples).
 template <bool KEYS>
-__global__ __launch_bounds__(kChainThreads) void mr_chain_kernel(MrChain c, int top, int hh,
+__global__ __launch_bounds__(kChainThreads, 8) void mr_chain_kernel(MrChain c, int top, int hh,
                                                                  const float *__restrict__ g, int lg, int n_out,
                                                                  int T, int capA, int capB, uint64_t *__restrict__ keys,
                                                                  int64_t ld_keys, float2 *__restrict__ out,
                                                                  int64_t ld_out, int tiles) {
     extern __shared__ __align__(16) float2 wbuf[];   // per wave: capA then capB samples
-    __shared__ float sg[kMaxTaps];
+    __shared__ __align__(16) float sg[kMaxTaps];
     __shared__ int slo[kMaxLevels], shi[kMaxLevels];
-    const int wv = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    const int wv = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6), lane = threadIdx.x & 63;
     const int chunk = (int)blockIdx.x / tiles;
     const int tile = (int)blockIdx.x % tiles;
     const bool last = tile == tiles - 1;
@@ -212,77 +259,79 @@ __global__ __launch_bounds__(kChainThreads) void mr_chain_kernel(MrChain c, int 
     }
     if (threadIdx.x < lg) sg[threadIdx.x] = g[threadIdx.x];
     __syncthreads();
+    // the rows of every level in one load, lane = level
+    int rows = -1;
+    if (live && lane <= top && c.z[lane]) rows = c.zrow[lane][j];
     auto zrow_of = [&](int r) -> const float2 * {
-        if (!live || !c.z[r]) return nullptr;
-        const int zr = c.zrow[r][j];
+        const int zr = __builtin_amdgcn_readlane(rows, r);
         return zr >= 0 ? c.z[r] + (int64_t)zr * c.ld_z[r] : nullptr;
     };
+    auto even = [](int lo) { return lo & ~1; };   // windows begin at an even index
     auto write_hist = [&](int r, const float2 *win) {
         // the last hh samples of W_r lie inside the last tile's window of level r
-        if (live && last && lane < hh) c.whist_new[r][j * hh + lane] = win[(n_out >> r) - hh + lane - slo[r]];
+        if (live && last && lane < hh) c.whist_new[r][j * hh + lane] = win[(n_out >> r) - hh + lane - even(slo[r])];
     };
-    if (top > 0) {
-        // top level: W_top = z_top, history below index 0
-        float2 *win = (top & 1) ? bufA : bufB;
-        const int lo = slo[top], hi = shi[top], nr = n_out >> top;
-        const float2 *zj = zrow_of(top);
-        if (live)
-            for (int q = lo + lane; q <= hi; q += 64)
-                win[q - lo] = q >= 0 ? z_at(zj, q, nr) : c.whist[top][j * hh + hh + q];
-        __syncthreads();
-        write_hist(top, win);
-    }
-    for (int r = top - 1; r >= 1; --r) {
+    // a level's z, loaded while the level above is formed; pair m0 + 64 u + lane
+    constexpr int NU = kTile / 2 / 64;
+    static_assert(kWinPairs == 3 && kWinPairs <= NU, "a level's window in one load");
+    float2 ev[NU], od[NU];
+    auto load = [&](int r) {
+        load_pairs<NU>(zrow_of(r), c.ld_z[r], max(slo[r], 0) / 2, lane, min(n_out >> r, shi[r] + 1), ev, od);
+    };
+    load(top);
+    for (int r = top; r >= 1; --r) {
         float2 *win = (r & 1) ? bufA : bufB;
         const float2 *src = (r & 1) ? bufB : bufA;   // W_{r+1}
-        const int lo = slo[r], hi = shi[r], nr = n_out >> r, lo_src = slo[r + 1];
-        const int qa = max(lo, 0);
-        if (live) {
-            for (int q = lo + lane; q < qa; q += 64) win[q - lo] = c.whist[r][j * hh + hh + q];
-            const float2 *zj = zrow_of(r);
-            const int mlo = qa / 2, mhi = hi / 2;
-            for (int m0 = mlo; m0 <= mhi; m0 += 128) {
-                int m[2];
-                float2 ev[2], od[2];
+        const int lo = slo[r], lb = even(lo), qa = max(lo, 0), mlo = qa / 2, np = shi[r] / 2 - mlo + 1;
+        float2 e[kWinPairs], o[kWinPairs];
+        int mw[kWinPairs];
 #pragma unroll
-                for (int u = 0; u < 2; ++u) {
-                    const int mm = min(m0 + u * 64 + lane, mhi);   // past mhi: a repeat, not written
-                    m[u] = mm - mlo;
-                    ev[u] = z_at(zj, 2 * mm, nr);
-                    od[u] = z_at(zj, 2 * mm + 1, nr);
-                }
-                interp_pairs<2>(src, mlo - lo_src, sg, lg, m, ev, od);
-#pragma unroll
-                for (int u = 0; u < 2; ++u) {
-                    const int mm = m0 + u * 64 + lane;
-                    if (mm > mhi) continue;
-                    if (2 * mm >= qa) win[2 * mm - lo] = ev[u];
-                    if (2 * mm + 1 <= hi) win[2 * mm + 1 - lo] = od[u];
-                }
-            }
+        for (int u = 0; u < kWinPairs; ++u) {
+            e[u] = ev[u];
+            o[u] = od[u];
+            mw[u] = min(u * 64 + lane, np - 1);   // past the window: a repeat, not written
         }
-        __syncthreads();
+        load(r - 1);
+        if (live) {
+            for (int q = lo + lane; q < qa; q += 64) win[q - lb] = c.whist[r][j * hh + hh + q];
+            if (r < top) {
+                const int sb = mlo - even(slo[r + 1]);
+                if (np > 128)
+                    interp_pairs<3>(src, sb, sg, lg, mw, e, o);
+                else if (np > 64)
+                    interp_pairs<2>(src, sb, sg, lg, mw, e, o);
+                else
+                    interp_pairs<1>(src, sb, sg, lg, mw, e, o);
+            }
+            // whole pairs: what one holds outside the window is not read
+            f4v *w4 = reinterpret_cast<f4v *>(win + (2 * mlo - lb));
+#pragma unroll
+            for (int u = 0; u < kWinPairs; ++u)
+                if (u * 64 + lane < np) w4[u * 64 + lane] = f4v{e[u].x, e[u].y, o[u].x, o[u].y};
+        }
+        // the buffers are the wave's own: its reads follow its writes in order
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
         write_hist(r, win);
     }
-    constexpr int NU = kTile / 2 / 64;
-    float2 ev[NU], od[NU];
+    int m[NU];
+#pragma unroll
+    for (int u = 0; u < NU; ++u) m[u] = u * 64 + lane;   // tile offsets 2m, 2m + 1
     if (live) {
-        const float2 *zj = zrow_of(0);
-        int m[NU];
-#pragma unroll
-        for (int u = 0; u < NU; ++u) {
-            m[u] = u * 64 + lane;   // pair m: tile offsets 2m, 2m + 1
-            const int p = p0 + 2 * m[u];
-            ev[u] = z_at(zj, p, n_out);
-            od[u] = z_at(zj, p + 1, n_out);
-        }
-        if (top > 0) interp_pairs<NU>(bufA, p0 / 2 - slo[1], sg, lg, m, ev, od);
+        if (top > 0) interp_pairs<NU>(bufA, p0 / 2 - even(slo[1]), sg, lg, m, ev, od);
         if (!KEYS) {
+            float2 *oj = out + j * ld_out + p0;
+            if (((uintptr_t)oj & 15) == 0 && p0 + kTile <= n_out) {
+                f4v *o4 = reinterpret_cast<f4v *>(oj);
 #pragma unroll
-            for (int u = 0; u < NU; ++u) {
-                const int p = p0 + 2 * m[u];
-                if (p < n_out) out[j * ld_out + p] = ev[u];
-                if (p + 1 < n_out) out[j * ld_out + p + 1] = od[u];
+                for (int u = 0; u < NU; ++u) o4[m[u]] = f4v{ev[u].x, ev[u].y, od[u].x, od[u].y};
+            } else {
+#pragma unroll
+                for (int u = 0; u < NU; ++u) {
+                    const int p = p0 + 2 * m[u];
+                    if (p < n_out) oj[2 * m[u]] = ev[u];
+                    if (p + 1 < n_out) oj[2 * m[u] + 1] = od[u];
+                }
             }
         }
     }
@@ -295,8 +344,8 @@ __global__ __launch_bounds__(kChainThreads) void mr_chain_kernel(MrChain c, int 
 #pragma unroll
             for (int u = 0; u < NU; ++u) {
                 const int t = 2 * (u * 64 + lane);
-                sq[t] = ev[u].x * ev[u].x + ev[u].y * ev[u].y;
-                sq[t + 1] = od[u].x * od[u].x + od[u].y * od[u].y;
+                *reinterpret_cast<float2 *>(sq + t) = make_float2(ev[u].x * ev[u].x + ev[u].y * ev[u].y,
+                                                                  od[u].x * od[u].x + od[u].y * od[u].y);
             }
         }
         __syncthreads();
@@ -357,7 +406,7 @@ void mr_chain_caps(int top, int lg, int *capA, int *capB) {
     for (int r = 1; r <= top; ++r) {
         cap = (cap + lg + 1) / 2 + 1;
         int &slot = (r & 1) ? *capA : *capB;
-        slot = std::max(slot, cap);
+        slot = std::max(slot, (cap + 3) & ~1);   // from an even index to an odd one
     }
 }
 
@@ -373,7 +422,7 @@ hipError_t launch_mr_chain(const MrChain &c, int top, int hh, const float *g, in
     int capA = 0, capB = 0;
     mr_chain_caps(top, lg, &capA, &capB);
     const size_t lds = mr_chain_lds(top, lg);
-    // at most 59,776 bytes (64 taps), within the default 64 KB with the static part
+    // at most 60,416 bytes (64 taps), within the default 64 KB with the static part
     if (lds > (size_t)kChainLdsMax) return hipErrorInvalidValue;
     if (n_out > INT32_MAX - kTile) return hipErrorInvalidValue;   // tile-local indices are int32
     const int tiles = (int)nblk(n_out, kTile);

@@ -31,6 +31,7 @@ struct spiir_multirate {
     float *h = nullptr, *g = nullptr;
     // the level banks run concurrently: each on its own stream, forked from the
     // caller's stream after the decimation and joined before the interpolation
+    std::vector<int64_t> nfilt;    // filters per level
     std::vector<hipStream_t> lstream;
     std::vector<hipEvent_t> lfork, ldone;
     // trigger calls in pieces of exactly B samples replay a captured graph of
@@ -95,18 +96,25 @@ int mr_clear_history(spiir_multirate *mr, hipStream_t st) {
     return SPIIR_OK;
 }
 
+bool mr_timing_on(const spiir_multirate *mr) {
+    for (auto *bk : mr->bank)
+        if (bk && bank_timing_on(bk)) return true;
+    return false;
+}
+
 // One piece (np <= B samples) of the multi-rate bank: decimation, the level
 // banks forked onto their streams, then one launch that interpolates every
 // level back to the full rate and writes the full-rate z (out0, row stride
 // ld0) or the per-sample keys for the max / argmax (mx, am).
 int mr_piece(spiir_multirate *mr, const float *x0, int64_t np, float2 *out0, int64_t ld0, float *mx, int32_t *am,
-             hipStream_t st) {
+             hipStream_t st, bool captured = false) {
     const int top = mr->top;
     const int c = mr->cur;
-    // the small levels' banks as one group of time-split launches, on the
-    // stream of the group's first level once the group's last input exists
+    // the small levels' banks as one group of time-split launches, once the
+    // group's last input exists
     bool grouped[kMaxLevels] = {};
-    int g0 = -1, g1 = -1;
+    int g0 = -1;
+    bool can_group = false;
     std::vector<spiir_bank *> gb;
     std::vector<const float *> gx;
     std::vector<int64_t> gn, gld;
@@ -119,34 +127,47 @@ int mr_piece(spiir_multirate *mr, const float *x0, int64_t np, float2 *out0, int
             gz.push_back(reinterpret_cast<float *>(mr->z[r]));
             gld.push_back(mr->B >> r);
         }
-        if (banks_multi_ok(gb.data(), (int)gb.size(), gn.data())) {
+        can_group = banks_multi_ok(gb.data(), (int)gb.size(), gn.data());
+        if (can_group && !mr_timing_on(mr)) {
             for (int r : mr->multi) grouped[r] = true;
             g0 = mr->multi.front();
-            g1 = mr->multi.back();
         }
     }
-    // each level's bank is forked onto its stream as soon as its input exists
-    auto fork = [&](int r, const float *xr) -> int {
-        if (!mr->bank[r]) return SPIIR_OK;
-        if (grouped[r]) {
-            if (r != g1) return SPIIR_OK;
-            HIPCHK(hipEventRecord(mr->lfork[g0], st));
-            HIPCHK(hipStreamWaitEvent(mr->lstream[g0], mr->lfork[g0], 0));
-            const int rc = banks_stream_z_multi(gb.data(), (int)gb.size(), gx.data(), gn.data(), gz.data(),
-                                                gld.data(), mr->lstream[g0]);
-            if (rc) return rc;
-            HIPCHK(hipEventRecord(mr->ldone[g0], mr->lstream[g0]));
-            return SPIIR_OK;
-        }
+    // one of them runs on st itself, after the forks of the others: it waits for no other
+    // queue before its first launch, and if it ends last nothing waits for it (each such
+    // wait was 12 to 16 us of idle device). It is the group, else the level with the most
+    // work; in a graph, where a branch costs no such wait, only the group. 1,024 templates
+    // of 100 to 400 filters, 4 levels, 4,096 samples: 173 us with every bank forked, 144
+    // with all of them on st (the large level leaves room beside it), 136 so. Captured:
+    // 139, 156, 131.
+    int home = g0;
+    if (home < 0 && !captured)
+        for (int r = 0; r <= top; ++r)
+            if (mr->bank[r] && (home < 0 || mr->nfilt[r] * (np >> r) > mr->nfilt[home] * (np >> home))) home = r;
+    // a bank that leaves no room beside it follows on st too: 230 workgroups of one per
+    // compute unit beside the group took 92 us, one after the other 82
+    bool forked[kMaxLevels] = {};
+    for (int r = 0; r <= top; ++r)
+        forked[r] = mr->bank[r] && r != home && !grouped[r] && !(home >= 0 && bank_fills_device(mr->bank[r], np >> r));
+    // timed banks run one by one, with the segments that they have in the group
+    auto as_group = [&](int r) {
+        return can_group && std::find(mr->multi.begin(), mr->multi.end(), r) != mr->multi.end();
+    };
+    auto run_bank = [&](int r, hipStream_t on) {
+        return bank_stream_z(mr->bank[r], r == 0 ? x0 : mr->xbuf[r], np >> r, reinterpret_cast<float *>(mr->z[r]),
+                             mr->B >> r, on, as_group(r));
+    };
+    // each forked bank starts as soon as its input exists
+    auto fork = [&](int r) -> int {
+        if (!forked[r]) return SPIIR_OK;
         HIPCHK(hipEventRecord(mr->lfork[r], st));
         HIPCHK(hipStreamWaitEvent(mr->lstream[r], mr->lfork[r], 0));
-        const int rc = bank_stream_z(mr->bank[r], xr, np >> r, reinterpret_cast<float *>(mr->z[r]), mr->B >> r,
-                                     mr->lstream[r]);
+        const int rc = run_bank(r, mr->lstream[r]);
         if (rc) return rc;
         HIPCHK(hipEventRecord(mr->ldone[r], mr->lstream[r]));
         return SPIIR_OK;
     };
-    int rc = fork(0, x0);
+    int rc = fork(0);
     if (rc) return rc;
     if (top > 0 && mr->pyramid) {
         MrPyramid pm;
@@ -158,16 +179,21 @@ int mr_piece(spiir_multirate *mr, const float *x0, int64_t np, float2 *out0, int
         }
         HIPCHK(launch_mr_pyramid(x0, np, top, pm, mr->h, mr->lh, mr->B, st));
         for (int r = 1; r <= top; ++r)
-            if ((rc = fork(r, mr->xbuf[r]))) return rc;
+            if ((rc = fork(r))) return rc;
     } else {
         for (int r = 1; r <= top; ++r) {
             HIPCHK(launch_mr_decimate(r == 1 ? x0 : mr->xbuf[r - 1], np >> (r - 1), mr->dh[c][r], mr->dh[c ^ 1][r],
                                       mr->h, mr->lh, mr->xbuf[r], st));
-            if ((rc = fork(r, mr->xbuf[r]))) return rc;
+            if ((rc = fork(r))) return rc;
         }
     }
+    if (g0 >= 0 &&
+        (rc = banks_stream_z_multi(gb.data(), (int)gb.size(), gx.data(), gn.data(), gz.data(), gld.data(), st)))
+        return rc;
     for (int r = 0; r <= top; ++r)
-        if (mr->bank[r] && (!grouped[r] || r == g0)) HIPCHK(hipStreamWaitEvent(st, mr->ldone[r], 0));
+        if (mr->bank[r] && !grouped[r] && !forked[r] && (rc = run_bank(r, st))) return rc;
+    for (int r = 0; r <= top; ++r)
+        if (forked[r]) HIPCHK(hipStreamWaitEvent(st, mr->ldone[r], 0));
     MrChain ch;
     std::memset(&ch, 0, sizeof ch);
     for (int r = 0; r <= top; ++r) {
@@ -188,12 +214,6 @@ int mr_piece(spiir_multirate *mr, const float *x0, int64_t np, float2 *out0, int
     }
     mr->cur ^= 1;
     return SPIIR_OK;
-}
-
-bool mr_timing_on(const spiir_multirate *mr) {
-    for (auto *bk : mr->bank)
-        if (bk && bank_timing_on(bk)) return true;
-    return false;
 }
 
 // Captures a trigger piece of B samples for each history parity. The host-side
@@ -228,7 +248,7 @@ int mr_build_graphs(spiir_multirate *mr) {
             restore();
             return fail(SPIIR_EHIP, "graph capture: %s", hipGetErrorString(e));
         }
-        const int rc = mr_piece(mr, mr->xin, mr->B, nullptr, 0, mr->mxo, mr->amo, mr->cap);
+        const int rc = mr_piece(mr, mr->xin, mr->B, nullptr, 0, mr->mxo, mr->amo, mr->cap, true);
         e = hipStreamEndCapture(mr->cap, &g);
         if (rc == SPIIR_OK && e == hipSuccess) e = hipGraphInstantiate(&mr->gexec[parity], g, nullptr, nullptr, 0);
         if (g) (void)hipGraphDestroy(g);
@@ -370,6 +390,7 @@ int spiir_multirate_create(spiir_multirate **out, int32_t n_levels, int32_t n_te
     int n_small = 0;
     for (int r = 0; r <= R; ++r) {
         const int64_t nf = filter_offsets[r][T];
+        mr->nfilt.push_back(nf);
         small[r] = nf > 0 && o.time_split == 0 && nf <= 128 * (int64_t)df.n_cu;
         n_small += small[r] ? 1 : 0;
     }
