@@ -97,14 +97,25 @@ __device__ __forceinline__ void interp_pairs(const float2 *s, int sb, const floa
     }
 }
 
-// Every decimation level of a piece in one launch: one workgroup, each level's
-// samples kept in LDS (after the lh - 1 history samples of that level) as the
-// input of the next; the full-rate input is staged in chunks. Level r
-// (1 <= r <= top) is formed from level r - 1 with the taps in the same order
-// as mr_decimate_kernel, so the values are those of the per-level launches;
-// so are the histories written to hist_new.
-constexpr int kPyrThreads = 1024;
-constexpr int kPyrChunk = 1024;   // level-1 outputs per staged chunk of the input
+// Every decimation level of a piece in one launch. A workgroup takes slice
+// samples of the input and forms its part of every level, each level's samples
+// kept in LDS as the input of the next; what the taps reach before its part is
+// formed again by the workgroup itself (22 * 15 samples of the input for 24
+// taps and 4 levels). Taps are added in the same order as in
+// mr_decimate_kernel, so the values are those of the per-level launches; so are
+// the histories, which the last workgroup writes to hist_new. Bound by latency:
+// one workgroup for the whole piece took 8 us for 4,096 samples and 22 us for
+// 16,384 (24 taps, 4 levels), slices of 512 take 5 us for both.
+constexpr int kPyrThreads = 512;
+constexpr int kPyrSlice = 512;
+
+// Samples of level r that a slice's part of the levels above reaches back to
+// before its own part.
+int pyr_reach(int r, int top, int lh) {
+    int reach = 0;
+    for (int q = top - 1; q >= r; --q) reach = std::max(0, 2 * reach + lh - 2);
+    return reach;
+}
 
 // acc = sum_{i < lh} h[i] v(m0 - i), v(m0 - i) = s[-i], taps ascending.
 __device__ __forceinline__ float fir_down(const float *sh, const float *s, int lh) {
@@ -118,55 +129,43 @@ __device__ __forceinline__ float fir_down(const float *sh, const float *s, int l
     return acc;
 }
 
-__global__ __launch_bounds__(kPyrThreads) void mr_pyramid_kernel(const float *__restrict__ x, int64_t n, int top,
+__global__ __launch_bounds__(kPyrThreads) void mr_pyramid_kernel(const float *__restrict__ x, int n, int top,
                                                                  MrPyramid pm, const float *__restrict__ h, int lh,
-                                                                 int cap0, int cap1) {
-    // dynamic LDS: [cap0] level r < top with r odd, [cap1] r even (history, then
-    // samples), [2 kPyrChunk + lh - 1] the staged chunk of the full-rate input
+                                                                 int slice, int cap0) {
+    // dynamic LDS: [cap0] levels r < top with r even, then those with r odd
     extern __shared__ float pbuf[];
     __shared__ float sh[kMaxTaps];
+    __shared__ int slo[kMaxLevels];   // first sample of each level in LDS (below 0: history)
     const int hl = lh - 1;
-    float *xs = pbuf + cap0 + cap1;
-    if (threadIdx.x < lh) sh[threadIdx.x] = h[threadIdx.x];
-    for (int r = 1; r <= top; ++r) {
-        const int64_t ns = n >> (r - 1);
-        const int64_t nq = ns / 2;
-        const float *hist = pm.hist[r];
-        float *ldst = r < top ? pbuf + ((r - 1) & 1) * cap0 : nullptr;
-        if (ldst)
-            for (int i = threadIdx.x; i < hl; i += kPyrThreads) ldst[i] = pm.hist[r + 1][i];
-        if (r == 1) {
-            // chunks of kPyrChunk outputs: inputs 2 q0 + 1 - hl .. 2 q0 + 2 kPyrChunk - 1
-            for (int64_t q0 = 0; q0 < nq; q0 += kPyrChunk) {
-                const int64_t m0 = 2 * q0 + 1 - hl;
-                const int cnt = (int)min((int64_t)(2 * kPyrChunk + hl), ns - m0);
-                __syncthreads();   // the previous chunk's reads are done
-                for (int k = threadIdx.x; k < cnt; k += kPyrThreads) {
-                    const int64_t m = m0 + k;
-                    xs[k] = m >= 0 ? x[m] : hist[hl + m];
-                }
-                __syncthreads();
-                const int64_t q = q0 + threadIdx.x;
-                if (threadIdx.x < kPyrChunk && q < nq) {
-                    const float acc = fir_down(sh, xs + (2 * q + 1 - m0), lh);
-                    pm.dst[1][q] = acc;
-                    if (ldst) ldst[hl + q] = acc;
-                }
-            }
-            for (int i = threadIdx.x; i < hl; i += kPyrThreads) {
-                const int64_t m = ns - hl + i;
-                pm.hist_new[1][i] = m >= 0 ? x[m] : hist[hl + m];
-            }
-        } else {
-            const float *lsrc = pbuf + ((r - 2) & 1) * cap0;   // level r - 1: lsrc[hl + m] = sample m
-            for (int64_t q = threadIdx.x; q < nq; q += kPyrThreads) {
-                const float acc = fir_down(sh, lsrc + hl + 2 * q + 1, lh);
-                pm.dst[r][q] = acc;
-                if (ldst) ldst[hl + q] = acc;
-            }
-            for (int i = threadIdx.x; i < hl; i += kPyrThreads) pm.hist_new[r][i] = lsrc[hl + ns - hl + i];
+    const int first = (int)blockIdx.x * slice, end = min(n, first + slice);
+    if (threadIdx.x == 0) {
+        int lo = first >> top;
+        for (int r = top - 1; r >= 0; --r) {
+            lo = min(first >> r, 2 * max(lo, 0) + 1 - hl);
+            slo[r] = lo;
         }
+    }
+    if (threadIdx.x < lh) sh[threadIdx.x] = h[threadIdx.x];
+    __syncthreads();
+    for (int m = slo[0] + (int)threadIdx.x; m < end; m += kPyrThreads)
+        pbuf[m - slo[0]] = m >= 0 ? x[m] : pm.hist[1][hl + m];
+    for (int r = 1; r <= top; ++r) {
         __syncthreads();
+        const float *lsrc = pbuf + ((r - 1) & 1) * cap0;   // sample m of level r - 1: lsrc[m - lo]
+        float *ldst = pbuf + (r & 1) * cap0;
+        const int lo = slo[r - 1], own = first >> r, qe = end >> r, q0 = r < top ? slo[r] : own;
+        for (int q = q0 + (int)threadIdx.x; q < qe; q += kPyrThreads) {
+            float acc;
+            if (q >= 0) {
+                acc = fir_down(sh, lsrc + (2 * q + 1 - lo), lh);
+                if (q >= own) pm.dst[r][q] = acc;
+            } else {
+                acc = pm.hist[r + 1][hl + q];
+            }
+            if (r < top) ldst[q - q0] = acc;
+        }
+        if (end == n)
+            for (int i = threadIdx.x; i < hl; i += kPyrThreads) pm.hist_new[r][i] = lsrc[(n >> (r - 1)) - hl + i - lo];
     }
 }
 
@@ -437,19 +436,17 @@ hipError_t launch_mr_chain(const MrChain &c, int top, int hh, const float *g, in
     return hipGetLastError();
 }
 
-size_t mr_pyramid_lds(int64_t B, int top, int lh) {
-    // level buffers (levels 1..top-1) and the staged input chunk
-    const int64_t hl = lh - 1;
-    const int64_t cap0 = top >= 2 ? hl + (B >> 1) : 0, cap1 = top >= 3 ? hl + (B >> 2) : 0;
-    return (size_t)(cap0 + cap1 + 2 * kPyrChunk + hl) * sizeof(float);
+size_t mr_pyramid_lds(int top, int lh) {
+    const int cap0 = kPyrSlice + pyr_reach(0, top, lh), cap1 = top >= 2 ? kPyrSlice / 2 + pyr_reach(1, top, lh) : 0;
+    return (size_t)(cap0 + cap1) * sizeof(float);
 }
 
 hipError_t launch_mr_pyramid(const float *x, int64_t n, int top, const MrPyramid &pm, const float *h, int lh,
-                             int64_t B, hipStream_t st) {
-    const int hl = lh - 1;
-    const int cap0 = top >= 2 ? (int)(hl + (B >> 1)) : 0, cap1 = top >= 3 ? (int)(hl + (B >> 2)) : 0;
-    hipLaunchKernelGGL(mr_pyramid_kernel, dim3(1), dim3(kPyrThreads), mr_pyramid_lds(B, top, lh), st, x, n, top, pm,
-                       h, lh, cap0, cap1);
+                             hipStream_t st) {
+    if (n <= 0 || n > INT32_MAX - kPyrSlice || n % (1 << top)) return hipErrorInvalidValue;
+    hipLaunchKernelGGL(mr_pyramid_kernel, dim3((unsigned)nblk(n, kPyrSlice)), dim3(kPyrThreads),
+                       mr_pyramid_lds(top, lh), st, x, (int)n, top, pm, h, lh, kPyrSlice,
+                       kPyrSlice + pyr_reach(0, top, lh));
     return hipGetLastError();
 }
 

@@ -177,7 +177,7 @@ int mr_piece(spiir_multirate *mr, const float *x0, int64_t np, float2 *out0, int
             pm.hist_new[r] = mr->dh[c ^ 1][r];
             pm.dst[r] = mr->xbuf[r];
         }
-        HIPCHK(launch_mr_pyramid(x0, np, top, pm, mr->h, mr->lh, mr->B, st));
+        HIPCHK(launch_mr_pyramid(x0, np, top, pm, mr->h, mr->lh, st));
         for (int r = 1; r <= top; ++r)
             if ((rc = fork(r))) return rc;
     } else {
@@ -355,7 +355,7 @@ int spiir_multirate_create(spiir_multirate **out, int32_t n_levels, int32_t n_te
     mr->lg = n_interp_taps;
     mr->hh = n_interp_taps / 2;
     mr->B = B;
-    mr->pyramid = mr_pyramid_lds(B, top, n_decim_taps) <= 64 * 1024;
+    mr->pyramid = mr_pyramid_lds(top, n_decim_taps) <= 60 * 1024;
     mr->bank.assign(R + 1, nullptr);
     mr->zrow.assign(R + 1, nullptr);
     mr->xbuf.assign(R + 1, nullptr);

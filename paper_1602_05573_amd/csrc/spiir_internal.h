@@ -197,9 +197,9 @@ struct MrChain {
 };
 hipError_t launch_mr_decimate(const float *src, int64_t n_src, const float *hist, float *hist_new,
                               const float *h, int lh, float *dst, hipStream_t stream);
-size_t mr_pyramid_lds(int64_t B, int top, int lh);
+size_t mr_pyramid_lds(int top, int lh);
 hipError_t launch_mr_pyramid(const float *x, int64_t n, int top, const MrPyramid &pm, const float *h, int lh,
-                             int64_t B, hipStream_t stream);
+                             hipStream_t stream);
 size_t mr_chain_lds(int top, int lg);
 // keys != null: keys[chunk][p] = max over the chunk's rows of (|z|^2 bits << 32 | ~j);
 // else the full-rate z to out[j * ld_out + p].

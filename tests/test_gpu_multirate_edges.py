@@ -62,3 +62,14 @@ def test_large_level_beside_the_group():
     print("[case] large level", flush=True)
     x = strain(3000, 7, 3)
     run(rand_levels(260, [40, 260, 30], 3), 24, 24, x, [0, 2048, 2052, 3000], 2048, 3)
+
+
+@pytest.mark.parametrize("lh,levels,n,mb", [(1, 4, 2048, 1024), (2, 3, 3000, 2000), (24, 8, 8192, 4096),
+                                            (64, 8, 4096, 2048), (7, 2, 1030, 1030)])
+def test_decimation_slices(lh, levels, n, mb):
+    """Slices of 512 samples: one, several, a short last one; reaches from none to many slices."""
+    print("[case] decimation taps %d levels %d" % (lh, levels), flush=True)
+    per = [0] * (levels - 1) + [12]
+    step = 1 << (levels - 1)
+    x = strain(n, 7, lh)
+    run(rand_levels(4, per, lh), lh, 8, x, [0, step, mb // (2 * step) * step + step, n], mb, lh)
