@@ -130,9 +130,8 @@ struct spiir_bank {
     float4 *pl_seg_end = nullptr, *pl_seg_start = nullptr;
     int pl_cap = 0;
     int tsplit_opt = 0;           // opts.time_split as given (the adjoint honours it too)
-    // adjoint scratch, grown on demand: (lambda, nu) pairs [2][cap][S], gpart [cap][2][S]
+    // adjoint scratch, grown on demand: gpart [cap][2][S], then (lambda, nu) pairs [cap][S]
     int bwd_cap = 0;
-    float4 *bpair = nullptr;
     double2 *bgpart = nullptr;
     // optional kernel timing ring (spiir_bank_time_kernels)
     std::vector<hipEvent_t> tev0, tev1;
@@ -267,6 +266,53 @@ SegPlan plan_group_segments(const spiir_bank *bk, int64_t n) {
     return p;
 }
 
+// Time segments of the backward, whole chunks of L samples. With the split left
+// to the library: the number (up to 32) that costs least, in FP32 issue slots of
+// the fullest SIMD. A step of the gradient pass issues 12 per wave and one of the
+// scan over all but the first segment 8 (about 2.4 ns a slot); a wave alone on its
+// SIMD waits for its own results (1.3 times); the scan's launch and prologue are
+// 9 us, a later segment's pair 0.15 us. A call of fewer chunks than segments takes
+// shorter chunks, of 64 samples or more. 128 templates of 300 filters, 9,000
+// samples: 232 us, against 395 us with the one wave per SIMD that was aimed at before.
+struct BwdPlan {
+    int L = 0, nseg = 1;
+    int32_t seg_chunks = 1;
+};
+
+BwdPlan plan_backward(const spiir_bank *bk, int64_t n) {
+    auto cut = [&](int64_t want) {
+        BwdPlan p;
+        p.L = bk->L;
+        if (bk->tsplit_opt == 0 && want > 1 && p.L > 64)
+            p.L = (int)std::min<int64_t>(p.L, std::max<int64_t>(64, ((n + want - 1) / want + 15) / 16 * 16));
+        const int64_t nch = (n + p.L - 1) / p.L;
+        want = std::max<int64_t>(1, std::min<int64_t>(want, nch));
+        const int64_t sc = (nch + want - 1) / want;
+        p.seg_chunks = (int32_t)sc;
+        p.nseg = (int)((nch + sc - 1) / sc);
+        return p;
+    };
+    if (bk->tsplit_opt != 0) return cut(bk->tsplit_opt >= 2 ? bk->tsplit_opt : 1);
+    const int64_t waves = std::max<int64_t>(1, bk->n_bwaves), simds = (int64_t)4 * bk->dev.n_cu;
+    auto rounds = [&](int64_t w) {
+        const int64_t r = (w + simds - 1) / simds;
+        return r == 1 ? 1.3 : (double)r;
+    };
+    BwdPlan best = cut(1);
+    double cost = 0.0;
+    for (int want = 1; want <= 32; ++want) {
+        const BwdPlan p = cut(want);
+        const double len = (double)std::min<int64_t>(n, (int64_t)p.seg_chunks * p.L);
+        double c = 12.0 * len * rounds(waves * p.nseg);
+        if (p.nseg > 1) c += 8.0 * len * rounds(waves * (p.nseg - 1)) + 3700.0 + 60.0 * p.nseg;
+        if (want == 1 || c < cost) {
+            cost = c;
+            best = p;
+        }
+    }
+    return best;
+}
+
 // Slot arrays on the host, then uploaded.
 int upload_coeffs(spiir_bank *bk) {
     const int64_t S = bk->lay.nslots;
@@ -327,7 +373,7 @@ void free_bank_buffers(spiir_bank *bk) {
     dfree(bk->aL); dfree(bk->dL); dfree(bk->a64); dfree(bk->state); dfree(bk->zstate);
     dfree(bk->rows); dfree(bk->hist[0]); dfree(bk->hist[1]); dfree(bk->keys); dfree(bk->xwin);
     dfree(bk->zpart); dfree(bk->split_tpl); dfree(bk->split_off); dfree(bk->group_lo);
-    dfree(bk->bpair); dfree(bk->bgpart); dfree(bk->seg_end); dfree(bk->seg_start);
+    dfree(bk->bgpart); dfree(bk->seg_end); dfree(bk->seg_start);
     dfree(bk->pl_seg_end); dfree(bk->pl_seg_start);
     bk->pl_cap = 0;
 }
@@ -1263,45 +1309,28 @@ int spiir_backward(spiir_bank *bk, const spiir_tape *tp, const float *gz, float 
     a.n_bwaves = bk->n_bwaves;
     a.xwin = tp->xwin;
     a.gz = reinterpret_cast<const float2 *>(gz);
-    // time segments only when the per-segment kernel (one filter per lane)
-    // would leave SIMDs idle: segments add a G-only scan over all but the first
-    const int64_t nch = (tp->n + bk->L - 1) / bk->L;
-    int want = 1;
-    if (bk->tsplit_opt >= 2) {
-        want = bk->tsplit_opt;
-    } else if (bk->tsplit_opt == 0) {
-        const int64_t waves = std::max<int64_t>(1, bk->n_bwaves);
-        const int64_t target = (int64_t)4 * bk->dev.n_cu;   // one wave per SIMD
-        want = (int)std::min<int64_t>(16, (target + waves - 1) / waves);
-    }
-    want = (int)std::max<int64_t>(1, std::min<int64_t>(want, nch));
-    const int64_t seg_chunks = (nch + want - 1) / want;
-    const int nseg = (int)((nch + seg_chunks - 1) / seg_chunks);
+    const BwdPlan bp = plan_backward(bk, tp->n);
+    const int nseg = bp.nseg;
     const int64_t S = bk->lay.nslots;
-    if (bk->bwd_cap < nseg) {
-        dfree(bk->bpair);
+    if (bk->bwd_cap < nseg) {   // one allocation: the sums, then the pairs
         dfree(bk->bgpart);
         bk->bwd_cap = 0;
-        hipError_t e = dalloc(&bk->bpair, (size_t)2 * nseg * S);
-        if (e == hipSuccess) e = dalloc(&bk->bgpart, (size_t)2 * nseg * S);
-        if (e != hipSuccess) {
-            dfree(bk->bpair);
+        if (dalloc(&bk->bgpart, (size_t)3 * nseg * S) != hipSuccess) {
             dfree(bk->bgpart);
-            return fail(SPIIR_ENOMEM, "adjoint scratch allocation failed: %s", hipGetErrorString(e));
+            return fail(SPIIR_ENOMEM, "adjoint scratch allocation failed: %s", hipGetErrorString(hipErrorOutOfMemory));
         }
         bk->bwd_cap = nseg;
     }
-    a.pair_loc = bk->bpair;
-    a.pair_in = bk->bpair + (size_t)nseg * S;
+    a.pair_loc = reinterpret_cast<float4 *>(bk->bgpart + (size_t)2 * nseg * S);
     a.gpart = bk->bgpart;
     a.nseg = nseg;
-    a.seg_chunks = (int32_t)seg_chunks;
+    a.seg_chunks = bp.seg_chunks;
     a.grad_a = reinterpret_cast<float2 *>(ga);
     a.grad_b = reinterpret_cast<float2 *>(gb);
     a.n = tp->n;
     a.nslots = bk->lay.nslots;
     a.dmax = bk->dmax;
-    a.L = bk->L;
+    a.L = bp.L;
     a.prec = bk->prec;
     a.wpg = bk->lay.wpg;
     HIPCHK(launch_backward(a, as_stream(stream)));

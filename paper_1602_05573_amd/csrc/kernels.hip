@@ -1166,9 +1166,9 @@ __global__ void noise_fill_kernel(float *x, int64_t n, uint32_t seed) {
 //     lambda <- conj(a)^s lambda,   nu <- conj(a)^s nu + s conj(a)^(s-1) lambda.
 // The pair recursion is linear, so the stream is cut into nseg segments of
 // whole chunks: bwd_scan_kernel runs every segment but the first from a zero
-// pair at its end (reading only G), bwd_chain_kernel composes the segments from
-// the end in FP64 with the Jordan block, which gives the true pair entering
-// each segment, and bwd_seg_kernel runs every segment from that pair with the
+// pair at its end (reading only G), and bwd_seg_kernel composes the segments
+// after its own from the end in FP64 with the Jordan block, which gives the true
+// pair entering its segment, and runs the segment from that pair with the
 // gradient sums (FP32 within a chunk, FP64 across chunks). bwd_reduce_kernel
 // adds the per-segment sums in FP64 in segment order and applies conj(b).
 // Every L samples (a chunk) the pair carried into the chunk is corrected for
@@ -1391,37 +1391,45 @@ __global__ void __launch_bounds__(256) bwd_scan_kernel(BwdArgs p) {
     p.pair_loc[(int64_t)seg * p.nslots + slot] = make_float4(lr[0], li[0], vr[0], vi[0]);
 }
 
-// True pair entering every segment from the right (zero for the last one):
-// pair[s0] = pair_loc[s0] + J^(e - s0) pair[e], J the Jordan block of conj(a),
-// in FP64 (with fl32(a) in the all-FP32 mode).
-__global__ void __launch_bounds__(256) bwd_chain_kernel(BwdArgs p) {
-    const int64_t slot = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (slot >= p.nslots) return;
-    const int64_t n = p.n, nch = (n + p.L - 1) / p.L;
+// True pair entering segment seg from the right: the later segments' local
+// pairs composed from the last one on, pair <- pair_loc[s] + J^len pair with J
+// the Jordan block of conj(a), in FP64 (with fl32(a) in the all-FP32 mode). Every
+// segment composes its own, with the loads of 8 segments in flight, instead of
+// a launch that wrote them all with a load and two powers of a per segment one
+// after the other: 32 templates of 100 filters over 4,001 samples (16 segments)
+// took 11.6 us there.
+__device__ __forceinline__ float4 pair_entering(const BwdArgs &p, int64_t slot, int seg) {
+    float4 in = make_float4(0.f, 0.f, 0.f, 0.f);   // of the last segment
+    if (seg >= p.nseg - 1) return in;
     double2 a = p.s.a64[slot];
     if (p.prec == kPrecFp32) {
         const float2 a32 = p.s.a32[slot];
         a = make_double2((double)a32.x, (double)a32.y);
     }
+    const int len = p.seg_chunks * p.L;   // of every segment but the last, which enters with a zero pair
+    const double2 a1 = cpow64(a, len - 1), al = cmul64(a1, a);   // conj(a)^k = conj(a^k)
+    const double sr = (double)len * a1.x, si = (double)len * a1.y;
     double lr = 0.0, li = 0.0, vr = 0.0, vi = 0.0;
-    for (int seg = p.nseg - 1; seg >= 0; --seg) {
-        p.pair_in[(int64_t)seg * p.nslots + slot] = make_float4((float)lr, (float)li, (float)vr, (float)vi);
-        if (seg == 0) break;
-        const int64_t cs = (int64_t)seg * p.seg_chunks, ce = min(nch, cs + p.seg_chunks);
-        const int64_t len = min(n, ce * p.L) - cs * p.L;
-        const double2 a1 = cpow64(a, (int)(len - 1));   // conj(a)^k = conj(a^k)
-        const double2 al = cmul64(a1, a);
-        const double sr = (double)len * a1.x, si = (double)len * a1.y;
-        const float4 loc = p.pair_loc[(int64_t)seg * p.nslots + slot];
-        const double nvr = (double)loc.z + (al.x * vr + al.y * vi) + (sr * lr + si * li);
-        const double nvi = (double)loc.w + (al.x * vi - al.y * vr) + (sr * li - si * lr);
-        const double nlr = (double)loc.x + al.x * lr + al.y * li;
-        const double nli = (double)loc.y + al.x * li - al.y * lr;
-        lr = nlr;
-        li = nli;
-        vr = nvr;
-        vi = nvi;
+    constexpr int kAhead = 8;
+    for (int top = p.nseg - 1; top > seg; top -= kAhead) {
+        float4 loc[kAhead];
+#pragma unroll
+        for (int u = 0; u < kAhead; ++u)
+            if (top - u > seg) loc[u] = p.pair_loc[(int64_t)(top - u) * p.nslots + slot];
+#pragma unroll
+        for (int u = 0; u < kAhead; ++u)
+            if (top - u > seg) {
+                const double nvr = (double)loc[u].z + (al.x * vr + al.y * vi) + (sr * lr + si * li);
+                const double nvi = (double)loc[u].w + (al.x * vi - al.y * vr) + (sr * li - si * lr);
+                const double nlr = (double)loc[u].x + al.x * lr + al.y * li;
+                const double nli = (double)loc[u].y + al.x * li - al.y * lr;
+                lr = nlr;
+                li = nli;
+                vr = nvr;
+                vi = nvi;
+            }
     }
+    return make_float4((float)lr, (float)li, (float)vr, (float)vi);
 }
 
 // Strain and G of one sub-chunk of the backward.
@@ -1448,7 +1456,7 @@ __global__ void __launch_bounds__(256) bwd_seg_kernel(BwdArgs p) {
     PairDrift dfull;
     if (p.prec != kPrecFp32) dfull = pair_drift(p.s, slot, p.L, ar, ai);
     double gar = 0.0, gai = 0.0, gbr = 0.0, gbi = 0.0;
-    const float4 pin = p.pair_in[(int64_t)seg * p.nslots + slot];
+    const float4 pin = pair_entering(p, slot, seg);
     float lr = pin.x, li = pin.y, vr = pin.z, vi = pin.w;   // the pair after the current chunk
     float l0r = 0.f, l0i = 0.f, v0r = 0.f, v0i = 0.f;       // the pair entering the current chunk
     float sar = 0.f, sai = 0.f, sbr = 0.f, sbi = 0.f;
@@ -1529,6 +1537,7 @@ __global__ void __launch_bounds__(256) bwd_reduce_kernel(BwdArgs p) {
     const int k = p.slot_filter[slot];
     if (k < 0) return;
     double gar = 0.0, gai = 0.0, gbr = 0.0, gbi = 0.0;
+#pragma unroll 4
     for (int seg = 0; seg < p.nseg; ++seg) {
         const double2 ga = p.gpart[((int64_t)seg * 2 + 0) * p.nslots + slot];
         const double2 gb = p.gpart[((int64_t)seg * 2 + 1) * p.nslots + slot];
@@ -1870,11 +1879,8 @@ hipError_t launch_backward_t(const BwdArgs &a, hipStream_t st) {
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
-    hipLaunchKernelGGL(bwd_chain_kernel, dim3(nblocks(a.nslots, 256)), dim3(256), 0, st, a);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
     hipLaunchKernelGGL(bwd_seg_kernel, dim3(nblocks(a.n_bwaves, 4), a.nseg), dim3(256), 0, st, a);
-    e = hipGetLastError();
+    const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(bwd_reduce_kernel, dim3(nblocks(a.nslots, 256)), dim3(256), 0, st, a);
     return hipGetLastError();

@@ -80,7 +80,6 @@ struct BwdArgs {
     const float *xwin;           // xwin[dmax + m] = x[m] for m in [-dmax, n)
     const float2 *gz;            // [T][n]
     float4 *pair_loc;            // scratch [nseg][nslots]: segment-local (lambda, nu) at the segment start
-    float4 *pair_in;             // scratch [nseg][nslots]: true (lambda, nu) entering each segment from the right
     double2 *gpart;              // scratch [nseg][2][nslots]: per-segment sum nu x, sum lambda x
     float2 *grad_a, *grad_b;     // [F] caller order
     int64_t n, nslots;
