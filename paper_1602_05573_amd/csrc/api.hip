@@ -294,7 +294,11 @@ SegPlan plan_segments(const spiir_bank *bk, int64_t n, int max_seg) {
         if (want > 1 && p.nseg == best.nseg) continue;
         if (p.nseg == 1) p.len = n;
         const double fixed = 24.0 + (double)(win + p.len) / 512.0;
-        const double rm = (double)((G * p.nseg + bk->slots_main - 1) / bk->slots_main);
+        double rm = (double)((G * p.nseg + bk->slots_main - 1) / bk->slots_main);
+        // workgroups of delay bands differ by up to a third (delays at equal steps that share
+        // LDS banks): in one round the slowest sets the time, 2.79 to 3.70 ms over four chirp
+        // banks of 256 x 400 filters with 4 segments of 16,384 samples, 2.80 to 3.28 with 8
+        if (bk->band_auto && rm < 2.0) rm = 1.1;
         const double rp = (double)((G * (p.nseg - 1) + bk->slots_pre - 1) / bk->slots_pre);
         const double c = rm * ((double)p.len + fixed) + rp * (0.4 * (double)p.len + fixed) +
                          (p.nseg > 1 ? 40.0 + p.nseg : 0.0);
@@ -698,10 +702,10 @@ int ensure_xwin(spiir_bank *bk, int64_t need) {
 
 // Working buffers of one streaming call besides the bank's state and history:
 // per-workgroup partial keys [groups][keys_ld], the time split's segment
-// states and local z, and the strain window when it is not staged in LDS.
+// states, and the strain window when it is not staged in LDS.
 struct CallScratch {
     uint64_t *keys = nullptr;
-    int64_t keys_ld = 0;
+    int64_t keys_ld = 0;   // samples per piece (at most max_block)
     int nseg = 0;   // time segments per launch for this call (0: the bank's)
     float4 *seg_end = nullptr, *seg_start = nullptr;
     float *xwin = nullptr;
@@ -728,8 +732,9 @@ int stream_call(spiir_bank *bk, const float *x, int64_t n, int mode, float *snr,
     uint64_t *keys = cs ? cs->keys : bk->keys;
     const int64_t keys_ld = cs ? cs->keys_ld : bk->max_block;
     bool hist_done = false;
-    for (int64_t P = 0; P < n; P += bk->max_block) {
-        const int64_t np = std::min<int64_t>(bk->max_block, n - P);
+    const int64_t piece = cs ? cs->keys_ld : bk->max_block;
+    for (int64_t P = 0; P < n; P += piece) {
+        const int64_t np = std::min<int64_t>(piece, n - P);
         FwdArgs a = bk->base_args();
         if (cs) {
             a.seg_end = cs->seg_end;
@@ -1131,15 +1136,15 @@ size_t align256(size_t b) { return (b + 255) & ~(size_t)255; }
 // The allocation-free call's buffers carved from the device's scratch array
 // (scr = null: only the size). Bytes needed, or 0 with an error set.
 // Carves the call's buffers out of scr (null: sizes only) for time segments
-// of nseg per launch (at most the bank's count).
-size_t plan_scratch(const spiir_bank *bk, int64_t n, int nseg, unsigned char *scr, CallScratch &cs) {
+// of nseg per launch (at most the bank's count) and pieces of at most piece samples.
+size_t plan_scratch(const spiir_bank *bk, int64_t n, int nseg, int64_t piece, unsigned char *scr, CallScratch &cs) {
     size_t at = 0;
     auto take = [&](size_t bytes) {
         unsigned char *p = scr ? scr + at : nullptr;
         at += align256(bytes);
         return p;
     };
-    const int64_t keys_ld = std::min<int64_t>(n, bk->max_block);
+    const int64_t keys_ld = std::min<int64_t>(n, piece);
     cs.keys_ld = keys_ld;
     cs.nseg = nseg;
     cs.keys = reinterpret_cast<uint64_t *>(
@@ -1164,8 +1169,13 @@ int spiir_trigger_max_noalloc(spiir_bank *bk, const float *x, int64_t n, float *
     // the bank's time segments, or as many as the array holds (the per-segment
     // states grow with the segment count)
     int nseg = std::max(1, bk->nseg);
-    size_t need = plan_scratch(bk, n, nseg, nullptr, cs);
-    while (need > kScratchBytes && nseg > 1) need = plan_scratch(bk, n, --nseg, nullptr, cs);
+    int64_t piece = bk->max_block;
+    size_t need = plan_scratch(bk, n, nseg, piece, nullptr, cs);
+    while (need > kScratchBytes && nseg > 1) need = plan_scratch(bk, n, --nseg, piece, nullptr, cs);
+    // automatic delay bands have up to a quarter more workgroups, hence keys, than the
+    // layout without them: shorter pieces keep every call that one took
+    while (need > kScratchBytes && bk->band_auto && 2 * piece > bk->max_block && piece > bk->L)
+        need = plan_scratch(bk, n, nseg, piece -= bk->L, nullptr, cs);
     if (need > kScratchBytes)
         return fail(SPIIR_EINVAL,
                     "this call needs %zu bytes of working memory, more than the %zu bytes the allocation-free "
@@ -1175,7 +1185,7 @@ int spiir_trigger_max_noalloc(spiir_bank *bk, const float *x, int64_t n, float *
     unsigned char *scr = nullptr;
     const int rc = scratch_setup(bk->device, &scr);   // the address looked up when the bank was created
     if (rc) return rc;
-    plan_scratch(bk, n, nseg, scr, cs);
+    plan_scratch(bk, n, nseg, piece, scr, cs);
     return stream_call(bk, x, n, kModeKeys, nullptr, 0, mx, am, as_stream(stream), &cs);
 }
 

@@ -142,3 +142,26 @@ def test_backward_edges(n, L, K):
             for j in range(bank.n_templates):
                 sl = slice(int(bank.offsets[j]), int(bank.offsets[j + 1]))
                 assert np.linalg.norm(g[sl] - r[sl]) <= 1e-3 * np.linalg.norm(r[sl])
+
+
+def test_automatic_delay_bands_at_the_scratch_limit():
+    """A banded bank whose keys for whole pieces exceed the allocation-free call's
+    array runs that call in shorter pieces, with the same stream."""
+    from paper_1602_05573_amd import SpiirBank
+    bank = random_bank(96, 0, 1400, 400, 420, 0.99, 1 - 1e-5, 60000)
+    x = torch.from_numpy(strain(16384, 96)).cuda()
+    print("[case] automatic delay bands, scratch limit", flush=True)
+    with SpiirBank.from_bank(bank) as bk:
+        info = bk.info
+        assert info["delay_band"] > 0 and info["n_groups"] * 16384 * 8 > 32 << 20
+        mx, am = bk.trigger_max(x)
+        bk.reset()
+        m, j = torch.empty_like(mx), torch.empty_like(am)
+        bk.trigger_max_noalloc(x, out=(m, j))
+        tail = bk.trigger_max(x[:100].contiguous())[0]
+        bk.reset()
+        bk.trigger_max(x)
+        want = bk.trigger_max(x[:100].contiguous())[0]
+    assert float((m - mx).abs().max()) <= SNR_TOL * float(mx.max())
+    assert float((tail - want).abs().max()) <= SNR_TOL * float(mx.max())
+    assert float((j == am).float().mean()) > 0.99
