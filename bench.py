@@ -568,7 +568,7 @@ def run_adjoint(args, torch):
                      "peak": PEAK_FP32 / 1e12, "unit": "TFLOP/s",
                      "frac": FLOP_ADJ * updates / (bwd * 1e-3) / PEAK_FP32, "traffic": None,
                      "frac_executed": FLOP_ADJ_PAIR * updates / (bwd * 1e-3) / PEAK_FP32,
-                     "kernel": "spiir_backward (bwd_scan, bwd_chain, bwd_seg, bwd_reduce)",
+                     "kernel": "spiir_backward (bwd_scan, bwd_seg, bwd_reduce)",
                      "launch_us": bwd * 1e3, "flop_per_launch": FLOP_ADJ * updates},
         "roofline_forward": {"bound": "alu", "achieved": FLOP_UPDATE * updates / (fwd * 1e-3) / 1e12,
                              "peak": PEAK_FP32 / 1e12, "unit": "TFLOP/s",

@@ -86,22 +86,29 @@ typedef struct {
                                  pairs on this bank and keep the fastest */
     int32_t time_split;       /* segments each launch (spiir_filter_block,
                                  spiir_trigger_max, spiir_forward_z) is cut into when the
-                                 bank alone cannot fill the device: every segment is
-                                 filtered from rest in parallel, then the true
+                                 bank alone cannot fill the device: a state pass runs every
+                                 segment but the last from rest in parallel, the true
                                  segment-start states follow from a carry chain in FP64
-                                 (with fl32(a) in SPIIR_PREC_FP32 mode) and their free
-                                 response is added. spiir_backward likewise cuts the
-                                 reverse scan into segments (automatic count up to 16
-                                 for 0, the given count for 2..32). 0 = automatic, 1 = off,
+                                 (with fl32(a) in SPIIR_PREC_FP32 mode), and a full pass
+                                 filters every segment from its true start. spiir_backward
+                                 likewise cuts the reverse scan into segments (automatic
+                                 count up to 32 for 0, with chunks down to 64 samples; the
+                                 given count for 2..32). 0 = automatic (the call's length
+                                 chooses up to 64 segments of multiples of 64 samples),
+                                 1 = off,
                                  2..32 = forced. Not used by the per-template comparator.
                                  With filters_per_lane, waves_per_group and time_split all
                                  0, a bank of more than 128 filters per compute unit that
                                  the automatic lane count cannot spread over 7 waves per
-                                 CU, with max_block >= 8192 and the strain window in LDS,
+                                 CU, with max_block >= 2048 and the strain window in LDS,
                                  takes 4 filters per lane, 8-wave workgroups and up to 16
                                  segments. */
-    int32_t delay_band;       /* 0 = no delay bands (default: the strain window is staged in
-                                 LDS when it fits, else read from global memory); w >= 1 =
+    int32_t delay_band;       /* 0 = automatic (default): the strain window is staged in LDS
+                                 when it fits; else, with filters_per_lane,
+                                 waves_per_group and time_split 0 and max_block >= 2048, a
+                                 bank of more than 128 filters per compute unit takes bands
+                                 of 16384 if that costs at most a quarter more workgroups;
+                                 else the window is read from global memory. w >= 1 =
                                  delay bands of width w: every workgroup holds filters with
                                  delays in one band [k*w, (k+1)*w) and stages only that
                                  band's window (w - 1 + sub-block samples, the sub-block at
@@ -252,11 +259,10 @@ int spiir_trigger_max(spiir_bank *bank, const float *x_dev, int64_t n,
  * call as spiir_trigger_max, with the same arguments, results and stream
  * semantics (it continues the same stream; the two may be mixed call by
  * call), but its working memory (per-workgroup partial keys, the time split's
- * segment states and local sums, the strain window when it is not staged in
- * LDS) lives in a fixed 32 MiB array per device that the library holds until
+ * segment states, the strain window when it is not staged in LDS) lives in a fixed 32 MiB array per device that the library holds until
  * the process ends. It calls no hipMalloc/hipFree. Needed bytes:
  *   groups * min(n, max_block) * 8
- *   + (time split) 2 * segments * slots * 16 + (segments - 1) * T * segment_len * 8
+ *   + (time split) 2 * segments * slots * 16
  *   + (window not in LDS) (n + max_delay + 16) * 4,
  * each rounded up to 256; the 1,024-template bank at 4,096 samples per call
  * needs 7.9 MB. When the bank's time segments do not fit, the call cuts its
@@ -280,13 +286,13 @@ int spiir_trigger_max_noalloc(spiir_bank *bank, const float *x_dev, int64_t n,
  * a separate max/argmax pass over the stored rows. Each template's launches
  * fill the device on their own: every piece of at most max_block samples is
  * cut into segments of chunk_len samples, one workgroup each, whose carries
- * are chained in FP64 (three launches per template and piece; one launch
+ * are chained in FP64 (two or three launches per template and piece; one launch
  * when the piece is a single chunk); their strain is read from a window of
  * the call's samples in global memory. The segment scratch (two states per
- * slot of one workgroup and segment, one complex sum per template-sample)
- * and the window are allocated on first use. Continues the same stream as spiir_trigger_max.
+ * slot of one workgroup and segment) and the window are allocated on first use. Continues the same stream as spiir_trigger_max.
  * n = 0 is a no-op; EINVAL for a null bank or pointer, n < 0, or a bank with
- * templates split over workgroups.
+ * templates split over workgroups (by their length or by opts.delay_band; the
+ * automatic delay bands are taken, each workgroup with parts of a template in turn).
  */
 int spiir_trigger_max_per_template(spiir_bank *bank, const float *x_dev, int64_t n,
                                    float *max_dev, int32_t *argmax_dev,
@@ -320,7 +326,7 @@ int spiir_forward_z(spiir_bank *bank, const float *x_dev, int64_t n, float *z_de
  * sum without y: from a cold start it equals conj(b_k) sum_m nu_k[m] x[m-d_k]
  * with nu_k[m] = lambda_k[m+1] + conj(a_k) nu_k[m+1] (nu_k[n-1] = 0), a second
  * reverse recursion run beside lambda. The pair is carried in FP32 with an
- * FP32 correction for fl32(a_k) every chunk_len samples; time segments (see
+ * FP32 correction for fl32(a_k) every chunk_len samples (or fewer); time segments (see
  * spiir_bank_opts.time_split) are composed in FP64. Per-chunk sums are FP32
  * and are accumulated across chunks in FP64. Returns SPIIR_ESTATE if the tape
  * belongs to another bank or the coefficients changed since it was made;
@@ -329,7 +335,9 @@ int spiir_forward_z(spiir_bank *bank, const float *x_dev, int64_t n, float *z_de
 int spiir_backward(spiir_bank *bank, const spiir_tape *tape, const float *grad_z_dev,
                    float *grad_a_dev, float *grad_b_dev, void *stream);
 
-/* Frees a tape (after the work that uses it has completed). NULL is ignored. */
+/* Frees a tape (after the work that uses it has completed: it waits for the
+ * device). The bank keeps the strain windows of up to two freed tapes for its
+ * next ones, until it and its last tape are destroyed. NULL is ignored. */
 int spiir_tape_destroy(spiir_tape *tape);
 
 /*
@@ -362,7 +370,7 @@ int spiir_batch_create(spiir_batch **out, int32_t n_streams, spiir_bank *const *
  * A batch holds two graphs. The plain one runs each (stream, workgroup) item
  * over the whole block. The time-split one cuts each live stream's block into
  * segments of whole chunks (as spiir_bank_opts.time_split does for one bank:
- * segment-local pass, FP64 carry chain, carry-only pass), which multiplies the
+ * state pass, FP64 carry chain, full pass), which multiplies the
  * parallelism of the streams still running. By default a replay uses the
  * time-split graph when the live streams' workgroups fill at most half of the
  * device's resident workgroup slots (e.g. the tail of uneven streams); the
@@ -455,21 +463,22 @@ int spiir_bank_kernel_time(spiir_bank *bank, double *total_ms, int64_t *launches
  *                    samples (rounded down to a multiple of 2^R; level r gets
  *                    max_block / 2^r). With time_split = 0, a level of at most
  *                    128 filters per compute unit (a short serial recursion
- *                    per call) takes up to 32 time segments instead of 8.
- *                    Two or more such levels run as one group of launches
- *                    when their banks agree in layout (with waves_per_group
- *                    = 0 they are built with the group's largest workgroup
- *                    size, at least 4 waves), and one bank call each while
- *                    kernel timing is on; a single such level uses 64-sample
- *                    chunks instead of chunk_len.
+ *                    per call) takes up to 32 time segments. Two or more such
+ *                    levels run as one group of launches when their banks
+ *                    agree in layout (with waves_per_group = 0 they are built
+ *                    with the group's largest workgroup size, at least 4
+ *                    waves), and one bank call each, with the same segments,
+ *                    while kernel timing is on; a single such level uses
+ *                    64-sample chunks instead of chunk_len.
  * Calls take n a multiple of 2^R and continue one stream. Device memory held:
  * the level banks, the decimated streams, the level sums and ceil(T / 16) x
  * max_block uint64 keys. The interpolation runs in one launch per piece, each
  * workgroup forming the interpolated sums its full-rate samples need in LDS,
  * so neither those sums nor the full-rate z are stored (z is only written to
  * the caller's buffer by spiir_multirate_filter_block_z). The decimation of
- * every level also runs in one launch when max_block / 2 + max_block / 4
- * samples fit in 64 KB of LDS, else one launch per level.
+ * every level also runs in one launch, a workgroup per 512 input samples, when
+ * what the taps of all levels reach before them fits in LDS, else one launch
+ * per level.
  */
 int spiir_multirate_create(spiir_multirate **out, int32_t n_levels, int32_t n_templates,
                            const int64_t *const *filter_offsets, const double *const *a,
@@ -524,8 +533,8 @@ int spiir_multirate_level_bank(spiir_multirate *mr, int32_t level, spiir_bank **
  *              the output at jH. The output is the whitened stream delayed by H
  *              samples; with S = 1 it is x delayed by H exactly.
  *
- * Transforms run in FP32 on the device (radix-2 FFT per frame in LDS); the
- * PSD average is accumulated in FP64.
+ * Transforms run in FP32 on the device (two frames per radix-8 FFT); the PSD
+ * average is accumulated in FP64.
  *
  *   frame_len   N, a power of two in [16, 8192]
  *   max_block   most samples per internal piece (0 = 65536; rounded to a
