@@ -63,6 +63,7 @@ using layout::plan_rows;
 using layout::auto_wpg;
 using layout::choose_fl;
 using layout::plan_geometry;
+using layout::plan_short_geometry;
 using layout::fwd_lds_bytes;
 
 static_assert(sizeof(layout::F2) == sizeof(float2) && sizeof(layout::D2) == sizeof(double2) &&
@@ -584,28 +585,24 @@ int create_bank(spiir_bank **out, int32_t T, const int64_t *off, const double *a
     bk->part_group.assign((size_t)bk->lay.n_parts, 0);
     for (size_t r = 0; r < bk->lay.rows.size(); ++r)
         if (bk->lay.rows[r].part >= 0) bk->part_group[(size_t)bk->lay.rows[r].part] = (int)(r / (4 * (size_t)wpg));
-    const Geometry gm = plan_geometry(wpg, win_delay, L, nb_cap, df.lds_cap);
-    if (L % gm.tt) {   // chunk ends are detected at tile ends only
-        delete bk;
-        return fail(SPIIR_EINVAL, "internal: tile length %d does not divide chunk_len %d", gm.tt, L);
-    }
-    bk->tt = gm.tt;
-    bk->xlds = gm.xlds;
-    bk->nb = gm.nb;
-    bk->lds = gm.lds;
-    bk->lds_tile = fwd_lds_bytes(wpg, 0, 0, false, gm.tt);
+    // the plan's fields change together: the comparator's LDS (lds_tile) holds the batches of tt
+    auto use_geometry = [&](const Geometry &g) {
+        bk->tt = g.tt;
+        bk->xlds = g.xlds;
+        bk->nb = g.nb;
+        bk->lds = g.lds;
+        bk->lds_tile = g.lds_tile;
+        bk->slots_main = (int64_t)df.n_cu * std::max(1, forward_occupancy(fl, wpg, g.lds));
+    };
+    use_geometry(plan_geometry(wpg, win_delay, L, nb_cap, df.lds_cap));
     bk->tsplit_opt = o.time_split;
     // time split: only when the bank's workgroups fill at most half the device
-    bk->slots_main = (int64_t)df.n_cu * std::max(1, forward_occupancy(fl, wpg, gm.lds));
-    if (o.time_split == 0 && !band && 2 * (int64_t)bk->lay.groups <= bk->slots_main) {
-        // its segments are short: a window of 2,048 samples beside the delays lets more
-        // workgroups share a compute unit than one of max_block samples
-        const Geometry gs = plan_geometry(wpg, dmax, L, std::min(max_block, std::max(L, 2048 / L * L)), df.lds_cap);
-        bk->tt = gs.tt;
-        bk->xlds = gs.xlds;
-        bk->nb = gs.nb;
-        bk->lds = gs.lds;
-        bk->slots_main = (int64_t)df.n_cu * std::max(1, forward_occupancy(fl, wpg, gs.lds));
+    if (o.time_split == 0 && !band && 2 * (int64_t)bk->lay.groups <= bk->slots_main)
+        use_geometry(plan_short_geometry(wpg, dmax, L, max_block, df.lds_cap));
+    if (L % bk->tt) {   // chunk ends are detected at tile ends only
+        const int tt = bk->tt;
+        delete bk;
+        return fail(SPIIR_EINVAL, "internal: tile length %d does not divide chunk_len %d", tt, L);
     }
     bk->lone_wg = bk->slots_main == df.n_cu;
     bk->slots_pre = (int64_t)df.n_cu * std::max(1, state_occupancy(fl, wpg, bk->base_args(), bk->xlds));

@@ -181,6 +181,7 @@ Geometry plan_geometry(int wpg, int dmax, int L, int max_block, size_t lds_cap) 
         g.xlds = nb >= L;
         g.nb = g.xlds ? (int)nb : max_block;
         g.lds = fwd_lds_bytes(wpg, dmax, g.nb, g.xlds, tt);
+        g.lds_tile = (size_t)fixed;
         if (!have) {
             best = g;
             have = true;
@@ -190,6 +191,10 @@ Geometry plan_geometry(int wpg, int dmax, int L, int max_block, size_t lds_cap) 
         }
     }
     return best;
+}
+
+Geometry plan_short_geometry(int wpg, int dmax, int L, int max_block, size_t lds_cap) {
+    return plan_geometry(wpg, dmax, L, std::min(max_block, std::max(L, 2048 / L * L)), lds_cap);
 }
 
 int check_bank_args(int32_t T, const int64_t *off, const double *a, const double *b, const int32_t *d,

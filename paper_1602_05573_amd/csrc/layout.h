@@ -65,6 +65,7 @@ struct Geometry {
     int nb = 0;          // samples per LDS window fill (a multiple of the chunk length)
     bool xlds = true;    // the strain window sits in LDS
     size_t lds = 0;      // LDS bytes per workgroup
+    size_t lds_tile = 0; // the same with the strain window in global memory (batches of the same class)
 };
 
 // Two floats / two doubles laid out as the device's float2 / double2.
@@ -102,6 +103,10 @@ int choose_fl(int T, const int64_t *off, int n_cu);
 inline int sum_batch(int tt) { return tt == 16 ? 64 : 8; }
 size_t fwd_lds_bytes(int wpg, int dmax, int nb, bool x_in_lds, int tt);
 Geometry plan_geometry(int wpg, int dmax, int L, int max_block, size_t lds_cap);
+// The plan of a bank whose calls are cut into short segments: a window of at most
+// 2,048 samples (one chunk if that is longer) beside the delays, which lets more
+// workgroups share a compute unit than one of max_block samples.
+Geometry plan_short_geometry(int wpg, int dmax, int L, int max_block, size_t lds_cap);
 
 // Validates the arguments of spiir_bank_create; returns SPIIR_OK and the
 // effective max_delay, or SPIIR_EINVAL with a message in err.
