@@ -156,7 +156,7 @@ struct spiir_bank {
     int tt = 16;                  // 16: the full pass sums batches of 64 steps, 8: of 8
     float *hist[2] = {nullptr, nullptr};
     int hist_cur = 0;
-    uint64_t *keys = nullptr;     // [groups + (split templates ? 1 : 0)][max_block]
+    uint64_t *keys = nullptr;     // [groups][max_block]
     float *xwin = nullptr;
     int64_t xwin_cap = 0;
     // templates split over workgroups (layout parts): partial sums [n_parts][max_block],
@@ -624,7 +624,7 @@ int create_bank(spiir_bank **out, int32_t T, const int64_t *off, const double *a
     A(dalloc(&bk->state, S)); A(dalloc(&bk->zstate, S)); A(dalloc(&bk->rows, (size_t)G * wpg * 4));
     A(dalloc(&bk->hist[0], (size_t)dmax)); A(dalloc(&bk->hist[1], (size_t)dmax));
     bk->n_split = (int)bk->lay.split_tpl.size();
-    A(dalloc(&bk->keys, (size_t)(G + (bk->n_split ? 1 : 0)) * max_block));
+    A(dalloc(&bk->keys, (size_t)G * max_block));
     if (bk->band) A(dalloc(&bk->group_lo, (size_t)G));
     if (bk->n_split) {
         A(dalloc(&bk->zpart, (size_t)bk->lay.n_parts * max_block));
@@ -776,11 +776,11 @@ int stream_call(spiir_bank *bk, const float *x, int64_t n, int mode, float *snr,
             HIPCHK(launch_forward(a, mode, bk->lay.fl, bk->xlds, bk->lay.groups, bk->lds, st, ev));
         if (bk->n_split)   // split templates: their parts' sums, then their SNR / z / keys
             HIPCHK(launch_combine_parts(bk->zpart, bk->max_block, bk->split_tpl, bk->split_off, bk->n_split, np,
-                                        mode, a.snr, a.z, a.ld, a.obase, keys + (int64_t)bk->lay.groups * keys_ld,
-                                        st));
+                                        mode, a.snr, a.z, a.ld, a.obase, st));
         if (mode == kModeKeys) {
-            HIPCHK(launch_finalize_keys(keys, bk->lay.groups + (bk->n_split ? 1 : 0), keys_ld, np, mx + P, am + P,
-                                        st, last ? &hc : nullptr));
+            SplitKeys sk;
+            if (bk->n_split) sk = SplitKeys{reinterpret_cast<uint64_t *>(bk->zpart), bk->max_block, bk->split_off, bk->n_split};
+            HIPCHK(launch_finalize_keys(keys, bk->lay.groups, keys_ld, np, mx + P, am + P, st, last ? &hc : nullptr, sk));
             hist_done = hist_done || last;
         }
     }
@@ -1145,7 +1145,7 @@ size_t plan_scratch(const spiir_bank *bk, int64_t n, int nseg, int64_t piece, un
     cs.keys_ld = keys_ld;
     cs.nseg = nseg;
     cs.keys = reinterpret_cast<uint64_t *>(
-        take((size_t)(bk->lay.groups + (bk->n_split ? 1 : 0)) * keys_ld * sizeof(uint64_t)));
+        take((size_t)bk->lay.groups * keys_ld * sizeof(uint64_t)));
     const size_t seg_bytes = (size_t)nseg * bk->lay.nslots * sizeof(float4);
     if (nseg > 1) {
         cs.seg_end = reinterpret_cast<float4 *>(take(seg_bytes));
@@ -1267,7 +1267,7 @@ int spiir_trigger_max_per_template(spiir_bank *bk, const float *x, int64_t n, fl
             }
             if (cut) {
                 HIPCHK(launch_combine_parts(bk->zpart, bk->max_block, bk->split_tpl + split, bk->split_off + split, 1,
-                                            np, kModeSnr, snr, nullptr, n, P, nullptr, st));
+                                            np, kModeSnr, snr, nullptr, n, P, st));
                 ++split;
             }
         }
@@ -1338,7 +1338,7 @@ int spiir_forward_z(spiir_bank *bk, const float *x, int64_t n, float *z, spiir_t
             e = launch_forward(a, kModeZ, bk->lay.fl, bk->xlds, bk->lay.groups, bk->lds, st, ev);
         if (e == hipSuccess && bk->n_split)
             e = launch_combine_parts(bk->zpart, bk->max_block, bk->split_tpl, bk->split_off, bk->n_split, np, kModeZ,
-                                     nullptr, a.z, a.ld, a.obase, nullptr, st);
+                                     nullptr, a.z, a.ld, a.obase, st);
     }
     if (e != hipSuccess) {
         if (tp) {

@@ -1006,12 +1006,12 @@ __global__ void __launch_bounds__(256) batch_chain_kernel(const BatchStream *str
     chain_segments(a.seg_end, a.seg_start, a.nslots, sl, act, st, av, nv, a.seg_len);
 }
 
-// Max over workgroup partial keys: 16 samples x 16 group slices per block.
-// Blocks from key_blocks on write the history copy (hc.new_h set), 256
-// samples each.
+// Max over workgroup partial keys and the key rows of split templates: 16
+// samples x 16 row slices per block. Blocks from key_blocks on write the
+// history copy (hc.new_h set), 256 samples each.
 __global__ void __launch_bounds__(256) finalize_keys_kernel(const uint64_t *keys, int groups, int64_t ld,
                                                             int64_t n, float *mx, int32_t *am, HistCopy hc,
-                                                            unsigned key_blocks) {
+                                                            unsigned key_blocks, SplitKeys sk) {
     if (blockIdx.x >= key_blocks) {   // uniform per block: no barrier below is reached
         const int i = (int)(blockIdx.x - key_blocks) * 256 + (int)threadIdx.x;
         if (i < hc.dmax) hist_copy_at(hc, i);
@@ -1026,6 +1026,13 @@ __global__ void __launch_bounds__(256) finalize_keys_kernel(const uint64_t *keys
             const uint64_t v = keys[(int64_t)g * ld + i];
             k = v > k ? v : k;
         }
+    if (i < n) {
+#pragma unroll 4
+        for (int r = q; r * kSplitSlice < sk.n_split; r += 16) {
+            const uint64_t v = sk.rows[(int64_t)sk.split_off[r * kSplitSlice] * sk.ld + i];
+            k = v > k ? v : k;
+        }
+    }
     red[q][si] = k;
     __syncthreads();
     if (q == 0 && i < n) {
@@ -1039,36 +1046,45 @@ __global__ void __launch_bounds__(256) finalize_keys_kernel(const uint64_t *keys
 // (in part order) for samples [0, n) of a piece, then the mode's output for
 // those templates: SNR rows, z rows (grid.y over the templates: one block per
 // template and 256 samples, since 64 blocks alone took 45 us for 256 templates
-// of 16,384 samples), or (keys, grid.y = 1) the per-sample maximum key over the
-// split templates into key_row, which the key finalisation takes as one more
-// workgroup.
-__global__ void __launch_bounds__(256) combine_parts_kernel(const float2 *zpart, int64_t ld_part,
+// of 16,384 samples), or (keys) the per-sample maximum key of kSplitSlice
+// templates (grid.y over the slices), which takes the place of the partial sums
+// in the row of the slice's first part: the same 8 bytes, read by the thread
+// that writes them and by no other.
+// With one grid row for all templates, spiir_trigger_max of 1,400 banded templates (4 parts
+// each) took 1,407 us for 64 samples and 2,334 for 4,096; in slices 63 and 949 (a window
+// in global memory without bands: 65 and 2,532).
+__global__ void __launch_bounds__(256) combine_parts_kernel(float2 *zpart, int64_t ld_part,
                                                             const int32_t *split_tpl, const int32_t *split_off,
                                                             int n_split, int64_t n, int mode, float *snr, float2 *z,
-                                                            int64_t ld, int64_t obase, uint64_t *key_row) {
+                                                            int64_t ld, int64_t obase) {
     const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (t >= n) return;
-    unsigned long long kbest = 0ull;
-    for (int i = blockIdx.y; i < n_split; i += gridDim.y) {
-        float zr = 0.f, zi = 0.f;
-        for (int q = split_off[i]; q < split_off[i + 1]; ++q) {
-            const float2 v = zpart[(int64_t)q * ld_part + t];
-            zr += v.x;
-            zi += v.y;
+    const int per = mode == kModeKeys ? kSplitSlice : 1;   // templates per grid row
+    for (int i0 = blockIdx.y * per; i0 < n_split; i0 += gridDim.y * per) {
+        unsigned long long kbest = 0ull;
+        for (int i = i0; i < min(n_split, i0 + per); ++i) {
+            float zr = 0.f, zi = 0.f;
+#pragma unroll 4
+            for (int q = split_off[i]; q < split_off[i + 1]; ++q) {
+                const float2 v = zpart[(int64_t)q * ld_part + t];
+                zr += v.x;
+                zi += v.y;
+            }
+            const int j = split_tpl[i];
+            if (mode == kModeSnr) {
+                snr[(int64_t)j * ld + obase + t] = zr * zr + zi * zi;
+            } else if (mode == kModeZ) {
+                z[(int64_t)j * ld + obase + t] = make_float2(zr, zi);
+            } else {
+                const float sn = zr * zr + zi * zi;
+                const unsigned long long key = ((unsigned long long)__float_as_uint(sn) << 32) |
+                                               (unsigned long long)(0xFFFFFFFFu - (uint32_t)j);
+                kbest = key > kbest ? key : kbest;
+            }
         }
-        const int j = split_tpl[i];
-        if (mode == kModeSnr) {
-            snr[(int64_t)j * ld + obase + t] = zr * zr + zi * zi;
-        } else if (mode == kModeZ) {
-            z[(int64_t)j * ld + obase + t] = make_float2(zr, zi);
-        } else {
-            const float sn = zr * zr + zi * zi;
-            const unsigned long long key = ((unsigned long long)__float_as_uint(sn) << 32) |
-                                           (unsigned long long)(0xFFFFFFFFu - (uint32_t)j);
-            kbest = key > kbest ? key : kbest;
-        }
+        if (mode == kModeKeys)
+            reinterpret_cast<unsigned long long *>(zpart)[(int64_t)split_off[i0] * ld_part + t] = kbest;
     }
-    if (mode == kModeKeys) key_row[t] = kbest;
 }
 
 // a^L minus what the FP32 recursion multiplies a carried state by over a chunk.
@@ -1779,24 +1795,24 @@ int state_occupancy(int fl, int wpg, const FwdArgs &a, bool x_in_lds) {
 }
 
 hipError_t launch_finalize_keys(const uint64_t *keys, int groups, int64_t ld, int64_t n,
-                                float *mx, int32_t *am, hipStream_t st, const HistCopy *hc) {
+                                float *mx, int32_t *am, hipStream_t st, const HistCopy *hc, const SplitKeys &sk) {
     HistCopy h{nullptr, nullptr, nullptr, 0, 0};
     if (hc && hc->dmax > 0) h = *hc;
     const unsigned kb = n > 0 ? nblocks(n, 16) : 0u;
     const unsigned hb = h.dmax > 0 ? nblocks(h.dmax, 256) : 0u;
     if (kb + hb == 0) return hipSuccess;
     hipLaunchKernelGGL(finalize_keys_kernel, dim3(kb + hb), dim3(256), 0, st, keys, groups, ld, n, mx, am, h,
-                       kb);
+                       kb, sk);
     return hipGetLastError();
 }
 
-hipError_t launch_combine_parts(const float2 *zpart, int64_t ld_part, const int32_t *split_tpl,
+hipError_t launch_combine_parts(float2 *zpart, int64_t ld_part, const int32_t *split_tpl,
                                 const int32_t *split_off, int n_split, int64_t n, int mode, float *snr, float2 *z,
-                                int64_t ld, int64_t obase, uint64_t *key_row, hipStream_t st) {
+                                int64_t ld, int64_t obase, hipStream_t st) {
     if (n <= 0 || n_split <= 0) return hipSuccess;
-    const unsigned by = mode == kModeKeys ? 1u : (unsigned)std::min(n_split, 65535);
-    hipLaunchKernelGGL(combine_parts_kernel, dim3(nblocks(n, 256), by), dim3(256), 0, st, zpart, ld_part, split_tpl,
-                       split_off, n_split, n, mode, snr, z, ld, obase, key_row);
+    const int rows = mode == kModeKeys ? (n_split + kSplitSlice - 1) / kSplitSlice : n_split;
+    hipLaunchKernelGGL(combine_parts_kernel, dim3(nblocks(n, 256), (unsigned)std::min(rows, 65535)), dim3(256), 0, st,
+                       zpart, ld_part, split_tpl, split_off, n_split, n, mode, snr, z, ld, obase);
     return hipGetLastError();
 }
 

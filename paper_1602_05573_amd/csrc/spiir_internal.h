@@ -135,15 +135,25 @@ int state_occupancy(int fl, int wpg, const FwdArgs &a, bool x_in_lds);
 // Adjoint over nseg time segments: segment-local (lambda, nu) scan, FP64 chain,
 // per-segment backward, FP64 reduction of the per-segment gradients.
 hipError_t launch_backward(const BwdArgs &a, hipStream_t stream);
-// Per-sample max over the groups' keys; with hc, the same launch also writes
-// the history copy (one launch fewer per streaming call).
+// Keys of split templates, one row per kSplitSlice of them: the row of the
+// partial sums of the slice's first part (launch_combine_parts).
+constexpr int kSplitSlice = 8;
+struct SplitKeys {
+    const uint64_t *rows = nullptr;        // zpart
+    int64_t ld = 0;
+    const int32_t *split_off = nullptr;
+    int n_split = 0;
+};
+// Per-sample max over the groups' keys and those of split templates; with hc,
+// the same launch also writes the history copy (one launch fewer per streaming call).
 hipError_t launch_finalize_keys(const uint64_t *keys, int groups, int64_t ld, int64_t n,
-                                float *mx, int32_t *am, hipStream_t stream, const HistCopy *hc = nullptr);
+                                float *mx, int32_t *am, hipStream_t stream, const HistCopy *hc = nullptr,
+                                const SplitKeys &sk = SplitKeys());
 // Sums the parts of split templates and writes the mode's output for them
-// (key_row: the per-sample maximum key over the split templates).
-hipError_t launch_combine_parts(const float2 *zpart, int64_t ld_part, const int32_t *split_tpl,
+// (keys: into zpart, see SplitKeys).
+hipError_t launch_combine_parts(float2 *zpart, int64_t ld_part, const int32_t *split_tpl,
                                 const int32_t *split_off, int n_split, int64_t n, int mode, float *snr, float2 *z,
-                                int64_t ld, int64_t obase, uint64_t *key_row, hipStream_t stream);
+                                int64_t ld, int64_t obase, hipStream_t stream);
 // Slot arrays of a bank from caller-order complex128 a, b on the device.
 hipError_t launch_set_coeffs(const double *a, const double *b, const int32_t *slot_filter, int64_t nslots, int L,
                              float2 *a32, float2 *b32, double2 *aL, double2 *dL, double2 *a64, int32_t *flags,
