@@ -259,15 +259,17 @@ int spiir_trigger_max(spiir_bank *bank, const float *x_dev, int64_t n,
  * call as spiir_trigger_max, with the same arguments, results and stream
  * semantics (it continues the same stream; the two may be mixed call by
  * call), but its working memory (per-workgroup partial keys, the time split's
- * segment states, the strain window when it is not staged in LDS) lives in a fixed 32 MiB array per device that the library holds until
- * the process ends. It calls no hipMalloc/hipFree. Needed bytes:
+ * segment states, the strain window when it is not staged in LDS) lives in a
+ * fixed 32 MiB array per device that the library holds until the process
+ * ends. It calls no hipMalloc/hipFree. Needed bytes:
  *   groups * min(n, max_block) * 8
  *   + (time split) 2 * segments * slots * 16
  *   + (window not in LDS) (n + max_delay + 16) * 4,
  * each rounded up to 256; the 1,024-template bank at 4,096 samples per call
  * needs 7.9 MB. When the bank's time segments do not fit, the call cuts its
  * launches into as many segments as do (results then agree with
- * spiir_trigger_max to FP32 rounding instead of bitwise). EINVAL (nothing
+ * spiir_trigger_max to FP32 rounding instead of bitwise); a bank with automatic
+ * delay bands then also takes shorter pieces of whole chunks. EINVAL (nothing
  * launched) when a call needs more than 32 MiB even without segments;
  * otherwise as spiir_trigger_max. Every call on one device shares that
  * device's array, which keeps the last call's contents: calls that overlap in

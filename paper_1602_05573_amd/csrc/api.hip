@@ -1166,12 +1166,12 @@ int spiir_trigger_max_noalloc(spiir_bank *bk, const float *x, int64_t n, float *
     // the bank's time segments, or as many as the array holds (the per-segment
     // states grow with the segment count)
     int nseg = std::max(1, bk->nseg);
-    int64_t piece = bk->max_block;
+    int64_t piece = std::min<int64_t>(bk->max_block, (n + bk->L - 1) / bk->L * bk->L);
     size_t need = plan_scratch(bk, n, nseg, piece, nullptr, cs);
     while (need > kScratchBytes && nseg > 1) need = plan_scratch(bk, n, --nseg, piece, nullptr, cs);
     // automatic delay bands have up to a quarter more workgroups, hence keys, than the
-    // layout without them: shorter pieces keep every call that one took
-    while (need > kScratchBytes && bk->band_auto && 2 * piece > bk->max_block && piece > bk->L)
+    // layout without them: shorter pieces (of whole chunks) keep every call that one took
+    while (need > kScratchBytes && bk->band_auto && piece > bk->L)
         need = plan_scratch(bk, n, nseg, piece -= bk->L, nullptr, cs);
     if (need > kScratchBytes)
         return fail(SPIIR_EINVAL,
