@@ -63,8 +63,8 @@ using layout::plan_rows;
 using layout::auto_wpg;
 using layout::choose_fl;
 using layout::plan_geometry;
+using layout::plan_global_geometry;
 using layout::plan_short_geometry;
-using layout::fwd_lds_bytes;
 
 static_assert(sizeof(layout::F2) == sizeof(float2) && sizeof(layout::D2) == sizeof(double2) &&
                   sizeof(RowInfo) == 16,
@@ -153,7 +153,7 @@ struct spiir_bank {
     double2 *aL = nullptr, *dL = nullptr, *a64 = nullptr;
     float4 *state = nullptr, *zstate = nullptr;
     RowInfo *rows = nullptr;
-    int tt = 16;                  // 16: the full pass sums batches of 64 steps, 8: of 8
+    int sumb = 64;                // steps per batch of the full pass
     float *hist[2] = {nullptr, nullptr};
     int hist_cur = 0;
     uint64_t *keys = nullptr;     // [groups][max_block]
@@ -172,7 +172,8 @@ struct spiir_bank {
     bool seg_auto = false;        // the call chooses their number and length (plan_segments)
     bool lone_wg = false;         // one workgroup of the full pass per compute unit
     int64_t slots_main = 1, slots_pre = 1;   // resident workgroups of the full / the state pass
-    size_t lds_tile = 0;          // LDS of a full pass whose window stays in global memory
+    size_t lds_tile = 0;          // LDS of a full pass of long batches whose window stays in global memory
+    Geometry lds_geo;             // the plan with the window in LDS, if one fits (batches take no other)
     float4 *seg_end = nullptr, *seg_start = nullptr;
     // per-template comparator: segment states [pl_cap][one workgroup's slots]
     float4 *pl_seg_end = nullptr, *pl_seg_start = nullptr;
@@ -198,7 +199,7 @@ struct spiir_bank {
         p.dmax = dmax;
         p.L = L;
         p.nb = nb;
-        p.sumb = layout::sum_batch(tt);
+        p.sumb = sumb;
         p.prec = prec;
         p.wpg = lay.wpg;
         p.only_tpl = -1;
@@ -544,6 +545,26 @@ int create_bank(spiir_bank **out, int32_t T, const int64_t *off, const double *a
         if (global_window && !band && plan_rows(T, off, 4).max_nr <= 4 * kMaxWaves) fl = 4;
     }
     const Plan plan = plan_rows(T, off, fl);
+    // The window goes to global memory although it fits LDS
+    //   * where LDS holds batches of 8 steps only and a lane has 1 or 2 filters: 4,096 samples
+    //     of 1,024 x 225 filters (2 per lane) with delays of 30,000 took 498 us so, 453 from
+    //     global memory, 4 x 128 filters with delays of 38,000 36 and 22; with more filters per
+    //     lane LDS is still faster (1,024 x 350 filters, 3 per lane: 533 and 690);
+    //   * where shorter batches cost a round of workgroups: 1,024 x 125 filters (266 workgroups
+    //     on 256 compute units, one each) with delays of 24,000 took 465 us with batches of
+    //     32 in LDS, 400 in one round; 2,048 x 57 filters (256 workgroups) 281 and 380.
+    auto best_window = [&](int w, int64_t groups, const Geometry &g) {
+        if (band || !g.xlds || g.sumb == layout::kLongBatch) return g;
+        const Geometry far = plan_global_geometry(w, L, max_block);
+        auto rounds = [&](const Geometry &p) {
+            const int64_t slots = (int64_t)df.n_cu * std::max(1, forward_occupancy(fl, w, p.lds_run));
+            return (groups + slots - 1) / slots;
+        };
+        return (g.sumb == 8 && fl <= 2) || rounds(far) < rounds(g) ? far : g;
+    };
+    auto geometry_for = [&](int w, int64_t groups) {
+        return best_window(w, groups, plan_geometry(w, win_delay, L, nb_cap, df.lds_cap));
+    };
     int wpg = o.waves_per_group;
     if (wpg == 0 && seg_layout) wpg = kMaxWaves;
     if (wpg == 0) {
@@ -552,11 +573,10 @@ int create_bank(spiir_bank **out, int32_t T, const int64_t *off, const double *a
         const int w0 = auto_wpg(plan.total_rows, std::min(plan.max_nr, 4 * kMaxWaves), df.n_cu);
         wpg = w0;
         for (int w = w0; w <= kMaxWaves; ++w) {
-            const Geometry gm = plan_geometry(w, win_delay, L, nb_cap, df.lds_cap);
-            const int occ = std::max(1, forward_occupancy(fl, w, gm.lds));
             Layout trial;
             if (build_layout(T, off, d, fl, w, band, trial)) continue;
             wpg = w;
+            const int occ = std::max(1, forward_occupancy(fl, w, geometry_for(w, trial.groups).lds_run));
             if (trial.groups <= (int64_t)df.n_cu * occ) break;
         }
     }
@@ -585,24 +605,28 @@ int create_bank(spiir_bank **out, int32_t T, const int64_t *off, const double *a
     bk->part_group.assign((size_t)bk->lay.n_parts, 0);
     for (size_t r = 0; r < bk->lay.rows.size(); ++r)
         if (bk->lay.rows[r].part >= 0) bk->part_group[(size_t)bk->lay.rows[r].part] = (int)(r / (4 * (size_t)wpg));
-    // the plan's fields change together: the comparator's LDS (lds_tile) holds the batches of tt
+    // the plan's fields change together
     auto use_geometry = [&](const Geometry &g) {
-        bk->tt = g.tt;
+        bk->sumb = g.sumb;
         bk->xlds = g.xlds;
         bk->nb = g.nb;
-        bk->lds = g.lds;
+        bk->lds = g.lds_run;
         bk->lds_tile = g.lds_tile;
-        bk->slots_main = (int64_t)df.n_cu * std::max(1, forward_occupancy(fl, wpg, g.lds));
+        bk->lds_geo = g.xlds ? g : plan_geometry(wpg, win_delay, L, nb_cap, df.lds_cap);
+        // 8 waves that read their strain from global memory leave a second workgroup of the
+        // compute unit nothing: 4,096 samples of 2,048 x 57 filters (256 workgroups, delays of
+        // 33,000) took 434 us cut into segments, 251 whole; 512 samples 78 and 37
+        const int occ = std::max(1, forward_occupancy(fl, wpg, g.lds_run));
+        bk->slots_main = (int64_t)df.n_cu * (g.xlds || wpg < kMaxWaves ? occ : 1);
     };
-    use_geometry(plan_geometry(wpg, win_delay, L, nb_cap, df.lds_cap));
+    use_geometry(geometry_for(wpg, bk->lay.groups));
     bk->tsplit_opt = o.time_split;
     // time split: only when the bank's workgroups fill at most half the device
     if (o.time_split == 0 && !band && 2 * (int64_t)bk->lay.groups <= bk->slots_main)
-        use_geometry(plan_short_geometry(wpg, dmax, L, max_block, df.lds_cap));
-    if (L % bk->tt) {   // chunk ends are detected at tile ends only
-        const int tt = bk->tt;
+        use_geometry(best_window(wpg, bk->lay.groups, plan_short_geometry(wpg, dmax, L, max_block, df.lds_cap)));
+    if (L % kFwdTile) {   // chunk ends are detected at tile ends only
         delete bk;
-        return fail(SPIIR_EINVAL, "internal: tile length %d does not divide chunk_len %d", tt, L);
+        return fail(SPIIR_EINVAL, "internal: tile length %d does not divide chunk_len %d", kFwdTile, L);
     }
     bk->lone_wg = bk->slots_main == df.n_cu;
     bk->slots_pre = (int64_t)df.n_cu * std::max(1, state_occupancy(fl, wpg, bk->base_args(), bk->xlds));
@@ -706,6 +730,7 @@ struct CallScratch {
     int nseg = 0;   // time segments per launch for this call (0: the bank's)
     float4 *seg_end = nullptr, *seg_start = nullptr;
     float *xwin = nullptr;
+    const Geometry *geo = nullptr;   // a plan with the window in LDS in place of the bank's
 };
 
 // Shared driver of the streaming calls (snr rows or fused keys). cs = null:
@@ -716,7 +741,10 @@ int stream_call(spiir_bank *bk, const float *x, int64_t n, int mode, float *snr,
     DeviceGuard guard(bk->device);
     const float *hist = bk->hist[bk->hist_cur];
     float *xwin = bk->xwin;
-    if (!bk->xlds) {
+    const Geometry *geo = cs ? cs->geo : nullptr;
+    const bool xlds = geo || bk->xlds;
+    const size_t lds = geo ? geo->lds_run : bk->lds;
+    if (!xlds) {
         if (cs) {
             xwin = cs->xwin;
         } else {
@@ -736,6 +764,10 @@ int stream_call(spiir_bank *bk, const float *x, int64_t n, int mode, float *snr,
         if (cs) {
             a.seg_end = cs->seg_end;
             a.seg_start = cs->seg_start;
+        }
+        if (geo) {
+            a.nb = geo->nb;
+            a.sumb = geo->sumb;
         }
         a.state = bk->state;
         a.x = x;
@@ -771,9 +803,9 @@ int stream_call(spiir_bank *bk, const float *x, int64_t n, int mode, float *snr,
         KernelEvents ev;
         HIPCHK(timer_next(bk, &ev));
         if (nseg >= 2)
-            HIPCHK(launch_forward_split(a, mode, bk->lay.fl, bk->xlds, nseg, bk->lds, st, ev));
+            HIPCHK(launch_forward_split(a, mode, bk->lay.fl, xlds, nseg, lds, st, ev));
         else
-            HIPCHK(launch_forward(a, mode, bk->lay.fl, bk->xlds, bk->lay.groups, bk->lds, st, ev));
+            HIPCHK(launch_forward(a, mode, bk->lay.fl, xlds, bk->lay.groups, lds, st, ev));
         if (bk->n_split)   // split templates: their parts' sums, then their SNR / z / keys
             HIPCHK(launch_combine_parts(bk->zpart, bk->max_block, bk->split_tpl, bk->split_off, bk->n_split, np,
                                         mode, a.snr, a.z, a.ld, a.obase, st));
@@ -1151,7 +1183,7 @@ size_t plan_scratch(const spiir_bank *bk, int64_t n, int nseg, int64_t piece, un
         cs.seg_end = reinterpret_cast<float4 *>(take(seg_bytes));
         cs.seg_start = reinterpret_cast<float4 *>(take(seg_bytes));
     }
-    if (!bk->xlds) cs.xwin = reinterpret_cast<float *>(take((size_t)(n + bk->dmax + 16) * sizeof(float)));
+    if (!bk->xlds && !cs.geo) cs.xwin = reinterpret_cast<float *>(take((size_t)(n + bk->dmax + 16) * sizeof(float)));
     return at;
 }
 
@@ -1173,6 +1205,11 @@ int spiir_trigger_max_noalloc(spiir_bank *bk, const float *x, int64_t n, float *
     // layout without them: shorter pieces (of whole chunks) keep every call that one took
     while (need > kScratchBytes && bk->band_auto && piece > bk->L)
         need = plan_scratch(bk, n, nseg, piece -= bk->L, nullptr, cs);
+    // a window that stays in global memory for speed alone goes to LDS where the array is short
+    if (need > kScratchBytes && !bk->xlds && bk->lds_geo.xlds) {
+        cs.geo = &bk->lds_geo;
+        need = plan_scratch(bk, n, nseg, piece, nullptr, cs);
+    }
     if (need > kScratchBytes)
         return fail(SPIIR_EINVAL,
                     "this call needs %zu bytes of working memory, more than the %zu bytes the allocation-free "
@@ -1251,6 +1288,7 @@ int spiir_trigger_max_per_template(spiir_bank *bk, const float *x, int64_t n, fl
                 a.obase = P;
                 a.snr = snr;
                 a.ld = n;
+                a.sumb = layout::kLongBatch;
                 a.only_tpl = j;
                 a.gbase = g;
                 a.groups = 1;
@@ -1425,9 +1463,9 @@ int spiir_batch_create(spiir_batch **out, int32_t ns, spiir_bank *const *banks, 
         if (lengths[s] < 1) return fail(SPIIR_EINVAL, "stream %d has length < 1", s);
         if (banks[s]->device != banks[0]->device) return fail(SPIIR_EINVAL, "banks on different devices");
         if (banks[s]->lay.fl != banks[0]->lay.fl || banks[s]->lay.wpg != banks[0]->lay.wpg ||
-            banks[s]->tt != banks[0]->tt)
+            banks[s]->lds_geo.tt != banks[0]->lds_geo.tt)
             return fail(SPIIR_EINVAL, "banks must share filters_per_lane, waves_per_group and tile length");
-        if (!banks[s]->xlds || banks[s]->band_auto)
+        if (!banks[s]->lds_geo.xlds || banks[s]->band_auto)
             return fail(SPIIR_EINVAL, "bank %d keeps its strain window outside LDS", s);
         if (banks[s]->n_split)
             return fail(SPIIR_EINVAL, "bank %d has templates split over workgroups; a batch takes none", s);
@@ -1446,7 +1484,7 @@ int spiir_batch_create(spiir_batch **out, int32_t ns, spiir_bank *const *banks, 
     bt->len.assign(lengths, lengths + ns);
     int max_groups = 0;
     for (int s = 0; s < ns; ++s) {
-        bt->lds = std::max(bt->lds, banks[s]->lds);
+        bt->lds = std::max(bt->lds, banks[s]->lds_geo.lds_run);
         max_groups = std::max(max_groups, banks[s]->lay.groups);
     }
     bt->key_stride = (int64_t)max_groups * B;
@@ -1466,6 +1504,8 @@ int spiir_batch_create(spiir_batch **out, int32_t ns, spiir_bank *const *banks, 
     for (int s = 0; s < ns; ++s) {
         std::memset(&hs[s], 0, sizeof(BatchStream));
         FwdArgs a = banks[s]->base_args();
+        a.nb = banks[s]->lds_geo.nb;
+        a.sumb = banks[s]->lds_geo.sumb;
         a.state = banks[s]->state;
         a.x = x[s];
         a.hist = nullptr;

@@ -158,37 +158,47 @@ int choose_fl(int T, const int64_t *off, int n_cu) {
     return 1;
 }
 
-size_t fwd_lds_bytes(int wpg, int dmax, int nb, bool x_in_lds, int tt) {
+size_t pass_lds_bytes(int wpg, int dmax, int nb, bool x_in_lds, int sumb) {
     const size_t win = x_in_lds ? (size_t)((dmax + nb + kFwdTile + 3) & ~3) * 4 : 0;
-    const size_t sb = (size_t)sum_batch(tt);
+    const size_t sb = (size_t)sumb;
     return win + (size_t)wpg * kFwdTile * 64 * 8 + 2 * sb * (size_t)(4 * wpg + 1) * 8 + 2 * sb * 8;
 }
 
-// The strain window (max_delay + nb samples) in LDS when it fits, and batches
-// of 64 steps when their row sums fit beside at least 2,048 samples of it. A
-// chunk ends at a tile end, so kFwdTile must divide L; chunk lengths that are not
-// a multiple of 16 take batches of 8.
+Geometry plan_global_geometry(int wpg, int L, int max_block) {
+    Geometry g;
+    g.tt = L % 16 ? 8 : 16;
+    g.sumb = kLongBatch;
+    g.xlds = false;
+    g.nb = max_block;
+    g.lds = fwd_lds_bytes(wpg, 0, 0, false, g.tt);
+    g.lds_run = g.lds_tile = pass_lds_bytes(wpg, 0, 0, false, kLongBatch);
+    return g;
+}
+
+// The window holds max_delay + nb samples; what the row sums of a batch take is
+// missing from nb. A step costs its share of a batch's barrier and sums, 1 / sumb, and
+// of the window's refill, about 5 / nb in the same unit (0.4 us per batch of 8 waves,
+// 2 us per refill of 28,000 samples): the batch length with the least sum. The batch need
+// not divide the chunk length, whose end is met at a tile's end. With batches of
+// 64 or 8 steps alone, 4,096 samples of 1,024 x 350 filters with delays of 24,000 took
+// 528 us (358 with 32 steps), 200 x 400 filters 196 (162), 64 x 200 filters with delays of 30,000 118 (73).
 Geometry plan_geometry(int wpg, int dmax, int L, int max_block, size_t lds_cap) {
-    Geometry best;
-    bool have = false;
-    for (int tt : {16, 8}) {
-        if (L % tt) continue;
-        Geometry g;
-        g.tt = tt;
-        const int64_t fixed = (int64_t)fwd_lds_bytes(wpg, 0, 0, false, tt);
+    Geometry best = plan_global_geometry(wpg, L, max_block);
+    double cost = 0.0;
+    for (int sb = kLongBatch; sb >= 8; sb /= 2) {
+        const int64_t fixed = (int64_t)pass_lds_bytes(wpg, 0, 0, false, sb);
         int64_t nb = ((int64_t)lds_cap - fixed - 4 * (int64_t)(dmax + kFwdTile) - 64) / (4 * L) * L;
         nb = std::min<int64_t>(nb, max_block);
-        g.xlds = nb >= L;
-        g.nb = g.xlds ? (int)nb : max_block;
-        g.lds = fwd_lds_bytes(wpg, dmax, g.nb, g.xlds, tt);
-        g.lds_tile = (size_t)fixed;
-        if (!have) {
-            best = g;
-            have = true;
-            if (g.xlds && g.nb >= std::min(max_block, 2048)) return g;
-        } else if (g.xlds && (!best.xlds || g.nb > best.nb)) {
-            return g;
-        }
+        if (nb < L) continue;
+        const double c = 1.0 / sb + 5.0 / (double)nb;
+        if (best.xlds && c >= cost) continue;
+        cost = c;
+        best.xlds = true;
+        best.sumb = sb;
+        best.tt = sb == kLongBatch && L % 16 == 0 ? 16 : 8;
+        best.nb = (int)nb;
+        best.lds = fwd_lds_bytes(wpg, dmax, best.nb, true, best.tt);
+        best.lds_run = pass_lds_bytes(wpg, dmax, best.nb, true, sb);
     }
     return best;
 }

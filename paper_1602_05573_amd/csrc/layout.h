@@ -61,11 +61,13 @@ struct Plan {
 
 // LDS plan of the forward kernel for one workgroup size.
 struct Geometry {
-    int tt = 16;         // batch class of the full pass (sum_batch); always divides the chunk length
+    int tt = 16;         // 16: batches of 64 steps and a chunk length that 16 divides, else 8
+    int sumb = 64;       // steps of the full pass between two barriers
     int nb = 0;          // samples per LDS window fill (a multiple of the chunk length)
     bool xlds = true;    // the strain window sits in LDS
-    size_t lds = 0;      // LDS bytes per workgroup
-    size_t lds_tile = 0; // the same with the strain window in global memory (batches of the same class)
+    size_t lds = 0;      // LDS bytes per workgroup with the shortest batch of class tt
+    size_t lds_run = 0;  // with batches of sumb steps: what a launch takes
+    size_t lds_tile = 0; // batches of kLongBatch steps and no window
 };
 
 // Two floats / two doubles laid out as the device's float2 / double2.
@@ -94,15 +96,20 @@ int auto_wpg(int64_t total_rows, int max_nr, int n_cu);
 // Filters per lane: the largest count that still gives about seven waves per
 // compute unit; 1 for small banks.
 int choose_fl(int T, const int64_t *off, int n_cu);
-// LDS bytes of a forward workgroup: strain window (when in LDS), one tile of
-// lane partial sums per wave, double-buffered row sums and key slots of one
-// batch.
-// Steps that a full pass runs between two barriers: 64 (one sample per lane in
-// the template sums), or 8 where the chunk length is no multiple of 16 or the
-// window needs the LDS that the larger row-sum buffer takes.
-inline int sum_batch(int tt) { return tt == 16 ? 64 : 8; }
-size_t fwd_lds_bytes(int wpg, int dmax, int nb, bool x_in_lds, int tt);
+// Steps that a full pass runs between two barriers: kLongBatch (one sample per lane in
+// the template sums), or less where the window needs the LDS that the row sums take.
+constexpr int kLongBatch = 64;
+inline int sum_batch(int tt) { return tt == 16 ? kLongBatch : 8; }
+// LDS bytes of a forward workgroup with batches of sumb steps: strain window (when in
+// LDS), one tile of lane partial sums per wave, double-buffered row sums and key slots.
+size_t pass_lds_bytes(int wpg, int dmax, int nb, bool x_in_lds, int sumb);
+inline size_t fwd_lds_bytes(int wpg, int dmax, int nb, bool x_in_lds, int tt) {
+    return pass_lds_bytes(wpg, dmax, nb, x_in_lds, sum_batch(tt));
+}
+// The window in LDS where it fits, else in global memory.
 Geometry plan_geometry(int wpg, int dmax, int L, int max_block, size_t lds_cap);
+// The window in global memory.
+Geometry plan_global_geometry(int wpg, int L, int max_block);
 // The plan of a bank whose calls are cut into short segments: a window of at most
 // 2,048 samples (one chunk if that is longer) beside the delays, which lets more
 // workgroups share a compute unit than one of max_block samples.
