@@ -1043,47 +1043,65 @@ __global__ void __launch_bounds__(256) finalize_keys_kernel(const uint64_t *keys
 }
 
 // Templates split over workgroups: z_j = the sum of its parts' partial sums
-// (in part order) for samples [0, n) of a piece, then the mode's output for
-// those templates: SNR rows, z rows (grid.y over the templates: one block per
-// template and 256 samples, since 64 blocks alone took 45 us for 256 templates
-// of 16,384 samples), or (keys) the per-sample maximum key of kSplitSlice
-// templates (grid.y over the slices), which takes the place of the partial sums
-// in the row of the slice's first part: the same 8 bytes, read by the thread
-// that writes them and by no other.
-// With one grid row for all templates, spiir_trigger_max of 1,400 banded templates (4 parts
-// each) took 1,407 us for 64 samples and 2,334 for 4,096; in slices 63 and 949 (a window
-// in global memory without bands: 65 and 2,532).
-__global__ void __launch_bounds__(256) combine_parts_kernel(float2 *zpart, int64_t ld_part,
+// (in part order).
+__device__ __forceinline__ float2 sum_parts(const float2 *zpart, int64_t ld_part, int q0, int q1, int64_t t) {
+    float zr = 0.f, zi = 0.f;
+#pragma unroll 4
+    for (int q = q0; q < q1; ++q) {
+        const float2 v = zpart[(int64_t)q * ld_part + t];
+        zr += v.x;
+        zi += v.y;
+    }
+    return make_float2(zr, zi);
+}
+
+// SNR or z rows of the split templates for samples [0, n) of a piece (grid.y over the
+// templates: one block per template and 256 samples, since 64 blocks alone took
+// 45 us for 256 templates of 16,384 samples).
+__global__ void __launch_bounds__(256) combine_parts_kernel(const float2 *zpart, int64_t ld_part,
                                                             const int32_t *split_tpl, const int32_t *split_off,
                                                             int n_split, int64_t n, int mode, float *snr, float2 *z,
                                                             int64_t ld, int64_t obase) {
     const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (t >= n) return;
-    const int per = mode == kModeKeys ? kSplitSlice : 1;   // templates per grid row
-    for (int i0 = blockIdx.y * per; i0 < n_split; i0 += gridDim.y * per) {
-        unsigned long long kbest = 0ull;
-        for (int i = i0; i < min(n_split, i0 + per); ++i) {
-            float zr = 0.f, zi = 0.f;
-#pragma unroll 4
-            for (int q = split_off[i]; q < split_off[i + 1]; ++q) {
-                const float2 v = zpart[(int64_t)q * ld_part + t];
-                zr += v.x;
-                zi += v.y;
-            }
-            const int j = split_tpl[i];
-            if (mode == kModeSnr) {
-                snr[(int64_t)j * ld + obase + t] = zr * zr + zi * zi;
-            } else if (mode == kModeZ) {
-                z[(int64_t)j * ld + obase + t] = make_float2(zr, zi);
-            } else {
-                const float sn = zr * zr + zi * zi;
-                const unsigned long long key = ((unsigned long long)__float_as_uint(sn) << 32) |
-                                               (unsigned long long)(0xFFFFFFFFu - (uint32_t)j);
-                kbest = key > kbest ? key : kbest;
-            }
+    for (int i = blockIdx.y; i < n_split; i += gridDim.y) {
+        const float2 v = sum_parts(zpart, ld_part, split_off[i], split_off[i + 1], t);
+        const int64_t o = (int64_t)split_tpl[i] * ld + obase + t;
+        if (mode == kModeSnr)
+            snr[o] = v.x * v.x + v.y * v.y;
+        else
+            z[o] = v;
+    }
+}
+
+// Per sample the largest key of each kSplitSlice split templates (grid.y over the slices),
+// left in the place of the partial sums of the slice's first part: the same 8 bytes,
+// read by the thread that writes them and by no other. A block takes 32 samples, a
+// thread per template: bound by the latency of one template's offsets and sums.
+// spiir_trigger_max of 64 / 4,096 samples of 1,400 banded templates (4 parts each): 1,407
+// / 2,334 us with one grid row for all templates, 55 / 943 so (65 / 2,532
+// without bands, the window in global memory); 200 templates, 64 samples: 205, 27 (23).
+__global__ void __launch_bounds__(256) split_keys_kernel(float2 *zpart, int64_t ld_part, const int32_t *split_tpl,
+                                                         const int32_t *split_off, int n_split, int64_t n) {
+    constexpr int kCols = 256 / kSplitSlice;
+    __shared__ uint64_t red[kSplitSlice][kCols + 1];
+    const int c = threadIdx.x % kCols, r = threadIdx.x / kCols;
+    const int64_t t = (int64_t)blockIdx.x * kCols + c;
+    for (int i0 = blockIdx.y * kSplitSlice; i0 < n_split; i0 += gridDim.y * kSplitSlice) {
+        const int i = i0 + r;
+        uint64_t k = 0;
+        if (i < n_split && t < n) {
+            const float2 z = sum_parts(zpart, ld_part, split_off[i], split_off[i + 1], t);
+            const float sn = z.x * z.x + z.y * z.y;
+            k = ((uint64_t)__float_as_uint(sn) << 32) | (uint64_t)(0xFFFFFFFFu - (uint32_t)split_tpl[i]);
         }
-        if (mode == kModeKeys)
-            reinterpret_cast<unsigned long long *>(zpart)[(int64_t)split_off[i0] * ld_part + t] = kbest;
+        red[r][c] = k;
+        __syncthreads();
+        if (r == 0 && t < n) {
+            for (int q = 1; q < kSplitSlice; ++q) k = red[q][c] > k ? red[q][c] : k;
+            reinterpret_cast<uint64_t *>(zpart)[(int64_t)split_off[i0] * ld_part + t] = k;
+        }
+        __syncthreads();
     }
 }
 
@@ -1811,8 +1829,13 @@ hipError_t launch_combine_parts(float2 *zpart, int64_t ld_part, const int32_t *s
                                 int64_t ld, int64_t obase, hipStream_t st) {
     if (n <= 0 || n_split <= 0) return hipSuccess;
     const int rows = mode == kModeKeys ? (n_split + kSplitSlice - 1) / kSplitSlice : n_split;
-    hipLaunchKernelGGL(combine_parts_kernel, dim3(nblocks(n, 256), (unsigned)std::min(rows, 65535)), dim3(256), 0, st,
-                       zpart, ld_part, split_tpl, split_off, n_split, n, mode, snr, z, ld, obase);
+    const unsigned gy = (unsigned)std::min(rows, 65535);
+    if (mode == kModeKeys)
+        hipLaunchKernelGGL(split_keys_kernel, dim3(nblocks(n, 256 / kSplitSlice), gy), dim3(256), 0, st, zpart, ld_part,
+                           split_tpl, split_off, n_split, n);
+    else
+        hipLaunchKernelGGL(combine_parts_kernel, dim3(nblocks(n, 256), gy), dim3(256), 0, st, zpart, ld_part, split_tpl,
+                           split_off, n_split, n, mode, snr, z, ld, obase);
     return hipGetLastError();
 }
 
