@@ -1462,8 +1462,9 @@ int spiir_batch_create(spiir_batch **out, int32_t ns, spiir_bank *const *banks, 
         if (!banks[s] || !x[s] || !mx[s] || !am[s]) return fail(SPIIR_EINVAL, "null entry for stream %d", s);
         if (lengths[s] < 1) return fail(SPIIR_EINVAL, "stream %d has length < 1", s);
         if (banks[s]->device != banks[0]->device) return fail(SPIIR_EINVAL, "banks on different devices");
+        // batches of steps may differ in length from bank to bank; the chunk lengths are of one class
         if (banks[s]->lay.fl != banks[0]->lay.fl || banks[s]->lay.wpg != banks[0]->lay.wpg ||
-            banks[s]->lds_geo.tt != banks[0]->lds_geo.tt)
+            (banks[s]->L % 16 == 0) != (banks[0]->L % 16 == 0))
             return fail(SPIIR_EINVAL, "banks must share filters_per_lane, waves_per_group and tile length");
         if (!banks[s]->lds_geo.xlds || banks[s]->band_auto)
             return fail(SPIIR_EINVAL, "bank %d keeps its strain window outside LDS", s);
