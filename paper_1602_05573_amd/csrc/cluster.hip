@@ -242,7 +242,9 @@ __device__ __forceinline__ void window_in_block(uint32_t k, int64_t W, int lane,
 // the direct neighbours alone left 5 or more samples in most blocks where much
 // of the series is above the threshold, each then walking its window alone:
 // 30,000 samples all above it took 77 us at W = 1,024 and 66 us at W = 16, and
-// take 24 and 28 us.
+// take 20 and 26 us. Only windows that reach out of the block are then tested
+// further (none for W = 1, whose window the neighbours are): 4,194,304 samples,
+// half of them above the threshold, W = 1: 81 us with all of them tested, 50 so.
 constexpr int kFindThreads = 1024;
 constexpr int kWaveTestMax = 4;
 
@@ -277,25 +279,33 @@ __global__ __launch_bounds__(kFindThreads) void clus_find_kernel(const float *__
             v = M[m];
             cand = m >= c_lo && m < c_hi && v >= thr;   // outside [c_lo, c_hi): neighbours only
         }
+        if (W == 0) {
+            const uint64_t bits = __ballot(cand);
+            if (lane == 0) mask[b] = bits;
+            cnt += (uint32_t)__popcll(bits);
+            continue;
+        }
         const uint32_t k = m < n ? okey(v) : 0;
         if (W >= kB1 - 1) {
             // within W of the whole block: its first maximum or none
             const uint64_t top = __ballot(k == (uint32_t)__shfl((int)mine, i));
             cand = cand && lane == __builtin_ctzll(top);
-        } else if (cand && W >= 1) {
+        } else if (cand) {
             if (m >= 1 && okey(M[m - 1]) >= k) cand = false;
             if (m + 1 < n && okey(M[m + 1]) > k) cand = false;
         }
         uint64_t cm = __ballot(cand);
-        if (W >= 1 && __popcll(cm) > kWaveTestMax) {
+        uint64_t bits = 0;
+        if (W > 1 && __popcll(cm) > kWaveTestMax) {
             uint32_t left, right;
             window_in_block(k, W, lane, left, right);
             cand = cand && left < k && right <= k;
-            cm = __ballot(cand);
+            const bool inside = lane >= W && lane + W < kB1;   // the whole window was in the block
+            bits = __ballot(cand && inside);
+            cm = __ballot(cand && !inside);
         }
-        uint64_t bits = 0;
-        if (W == 0) {
-            bits = cm;
+        if (W == 1) {
+            bits = cm;   // the neighbours are the window
         } else if (__popcll(cm) <= kWaveTestMax) {
             while (cm) {
                 const int l = __builtin_ctzll(cm);
@@ -309,8 +319,8 @@ __global__ __launch_bounds__(kFindThreads) void clus_find_kernel(const float *__
                 if (!__any(pl >= km || pr > km)) bits |= 1ull << l;
             }
         } else {
-            const bool hit = cand && is_peak_lane(M, n, m, okey(v), W, bm1, bm2);
-            bits = __ballot(hit);
+            const bool hit = ((cm >> lane) & 1) && is_peak_lane(M, n, m, okey(v), W, bm1, bm2);
+            bits |= __ballot(hit);
         }
         if (lane == 0) mask[b] = bits;
         cnt += (uint32_t)__popcll(bits);
@@ -446,6 +456,9 @@ __global__ __launch_bounds__(256) void ts_compose_kernel(const float *__restrict
 // sample src.copy_from on. Bound by the latency of its steps, not by any rate.
 // A push of 4,096 samples to a window of 1,024 (threshold at the 0.99 quantile)
 // took a join of 4.6 us, 4.8 + 44 + 4.4 us for the three launches; 11.1 us now.
+// Survivors are tested one after the other, so those whose window the block holds
+// are left out: 8,192 samples all above the threshold, W = 1: 60.5 -> 16 us
+// (25 with three launches).
 __global__ __launch_bounds__(kFindThreads) void clus_small_kernel(ClusterSrc src, float thr, uint32_t kthr, int64_t W,
                                                                   int64_t c_lo, int64_t c_hi, int64_t cap,
                                                                   int64_t *__restrict__ count, int64_t index_base,
@@ -498,7 +511,9 @@ __global__ __launch_bounds__(kFindThreads) void clus_small_kernel(ClusterSrc src
                 cand = cand && left < k && right <= k;
             }
             bits = __ballot(cand);
-            for (uint64_t cm = W > 0 ? bits : 0; cm; cm &= cm - 1) {
+            // the windows that reach out of the block
+            const uint64_t open = W < kB1 - 1 ? __ballot(lane < W || lane + W >= kB1) : ~0ull;
+            for (uint64_t cm = W > 0 ? bits & open : 0; cm; cm &= cm - 1) {
                 const int l = __builtin_ctzll(cm), mm = b * kB1 + l;
                 const uint32_t km = key[mm];
                 const int lo = mm - W > 0 ? (int)(mm - W) : 0;
