@@ -85,17 +85,23 @@ int check_bank_args(int32_t T, const int64_t *off, const double *a, const double
 
 }  // namespace
 
-// Strain windows of closed tapes, kept for the next ones of the bank: at most two, freed
-// with the bank or with its last tape. A window is given back after a wait for the
-// device, as a free would wait, so whichever stream takes it next finds it idle. An
-// allocation and a free per forward and backward were 20 of 110 us for 32 templates of
-// 100 filters over 4,001 samples.
+// Strain windows of closed tapes, kept for the next ones of the bank: at most two, the
+// last ones given back, freed with the bank or with its last tape, or when an
+// allocation fails. A window is given back after a wait for the device, as a free would
+// wait, so whichever stream takes it next finds it idle. An allocation and a free per
+// forward and backward were 20 of 110 us for 32 templates of 100 filters over 4,001 samples.
 struct WindowPool {
     std::mutex mu;
-    std::vector<std::pair<float *, size_t>> idle;   // window, samples
+    std::vector<std::pair<float *, size_t>> idle;   // window, samples; oldest first
 
-    ~WindowPool() {
-        for (auto &w : idle) (void)hipFree(w.first);
+    ~WindowPool() { drain(); }
+    void drain() {
+        std::vector<std::pair<float *, size_t>> old;
+        {
+            std::lock_guard<std::mutex> lk(mu);
+            old.swap(idle);
+        }
+        for (auto &w : old) (void)hipFree(w.first);
     }
     // A window of need samples or more, up to four times as many; not while the stream
     // is captured, where an allocation is refused.
@@ -122,12 +128,16 @@ struct WindowPool {
             const bool waited = hipDeviceSynchronize() == hipSuccess;
             if (!waited) (void)hipGetLastError();
             std::lock_guard<std::mutex> lk(mu);
-            if (waited && idle.size() < 2) {
+            if (waited) {
                 idle.emplace_back(p, cap);
-                return;
+                p = nullptr;
+                if (idle.size() > 2) {
+                    p = idle.front().first;
+                    idle.erase(idle.begin());
+                }
             }
         }
-        (void)hipFree(p);
+        if (p) (void)hipFree(p);
     }
 };
 
@@ -1338,6 +1348,11 @@ int spiir_forward_z(spiir_bank *bk, const float *x, int64_t n, float *z, spiir_t
         if (!tp->xwin) {
             tp->cap = need;
             hipError_t e = dalloc(&tp->xwin, need);
+            if (e == hipErrorOutOfMemory) {   // the idle windows may be what is missing
+                (void)hipGetLastError();
+                tp->pool->drain();
+                e = dalloc(&tp->xwin, need);
+            }
             if (e != hipSuccess) {
                 dfree(tp->xwin);
                 delete tp;
