@@ -192,6 +192,7 @@ struct spiir_bank {
     // adjoint scratch, grown on demand: gpart [cap][2][S], then (lambda, nu) pairs [cap][S]
     int bwd_cap = 0;
     double2 *bgpart = nullptr;
+    std::vector<double2 *> bgpart_old;   // outgrown ones, held for captured calls that use them
     std::shared_ptr<WindowPool> windows = std::make_shared<WindowPool>();
     // optional kernel timing ring (spiir_bank_time_kernels)
     std::vector<hipEvent_t> tev0, tev1;
@@ -341,6 +342,8 @@ SegPlan plan_group_segments(const spiir_bank *bk, int64_t n) {
 // 9 us, a later segment's pair 0.15 us. A call of fewer chunks than segments takes
 // shorter chunks, of 64 samples or more. 128 templates of 300 filters, 9,000
 // samples: 232 us, against 395 us with the one wave per SIMD that was aimed at before.
+constexpr int kMaxBwdSegments = 32;
+
 struct BwdPlan {
     int L = 0, nseg = 1;
     int32_t seg_chunks = 1;
@@ -367,7 +370,7 @@ BwdPlan plan_backward(const spiir_bank *bk, int64_t n) {
     };
     BwdPlan best = cut(1);
     double cost = 0.0;
-    for (int want = 1; want <= 32; ++want) {
+    for (int want = 1; want <= kMaxBwdSegments; ++want) {
         const BwdPlan p = cut(want);
         const double len = (double)std::min<int64_t>(n, (int64_t)p.seg_chunks * p.L);
         double c = 12.0 * len * rounds(waves * p.nseg);
@@ -433,6 +436,11 @@ void timer_free(spiir_bank *bk) {
     bk->tidx = 0;
 }
 
+void free_old_scratch(spiir_bank *bk) {
+    for (auto &p : bk->bgpart_old) dfree(p);
+    bk->bgpart_old.clear();
+}
+
 void free_bank_buffers(spiir_bank *bk) {
     timer_free(bk);
     dfree(bk->a32); dfree(bk->b32); dfree(bk->xoff); dfree(bk->flags); dfree(bk->slot_filter);
@@ -440,7 +448,7 @@ void free_bank_buffers(spiir_bank *bk) {
     dfree(bk->aL); dfree(bk->dL); dfree(bk->a64); dfree(bk->state); dfree(bk->zstate);
     dfree(bk->rows); dfree(bk->hist[0]); dfree(bk->hist[1]); dfree(bk->keys); dfree(bk->xwin);
     dfree(bk->zpart); dfree(bk->split_tpl); dfree(bk->split_off); dfree(bk->group_lo);
-    dfree(bk->bgpart); dfree(bk->seg_end); dfree(bk->seg_start);
+    dfree(bk->bgpart); free_old_scratch(bk); dfree(bk->seg_end); dfree(bk->seg_start);
     dfree(bk->pl_seg_end); dfree(bk->pl_seg_start);
     bk->pl_cap = 0;
 }
@@ -1431,13 +1439,25 @@ int spiir_backward(spiir_bank *bk, const spiir_tape *tp, const float *gz, float 
     const int nseg = bp.nseg;
     const int64_t S = bk->lay.nslots;
     if (bk->bwd_cap < nseg) {   // one allocation: the sums, then the pairs
-        dfree(bk->bgpart);
-        bk->bwd_cap = 0;
-        if (dalloc(&bk->bgpart, (size_t)3 * nseg * S) != hipSuccess) {
+        // A longer call may take more segments than a captured one had, whose replays go on
+        // using the scratch that it grew out of: that is kept until the bank is destroyed. Doubling
+        // keeps their sum below the largest.
+        int cap = std::max(nseg, std::min(2 * bk->bwd_cap, kMaxBwdSegments));
+        double2 *p = nullptr;
+        hipError_t e = dalloc(&p, (size_t)3 * cap * S);
+        if (e == hipErrorOutOfMemory) {
+            (void)hipGetLastError();
             dfree(bk->bgpart);
-            return fail(SPIIR_ENOMEM, "adjoint scratch allocation failed: %s", hipGetErrorString(hipErrorOutOfMemory));
+            free_old_scratch(bk);
+            bk->bwd_cap = 0;
+            cap = nseg;
+            e = dalloc(&p, (size_t)3 * cap * S);
         }
-        bk->bwd_cap = nseg;
+        if (e != hipSuccess)
+            return fail(SPIIR_ENOMEM, "adjoint scratch allocation failed: %s", hipGetErrorString(e));
+        if (bk->bgpart) bk->bgpart_old.push_back(bk->bgpart);
+        bk->bgpart = p;
+        bk->bwd_cap = cap;
     }
     a.pair_loc = reinterpret_cast<float4 *>(bk->bgpart + (size_t)2 * nseg * S);
     a.gpart = bk->bgpart;
