@@ -387,7 +387,7 @@ BwdPlan plan_backward(const spiir_bank *bk, int64_t n) {
 int upload_coeffs(spiir_bank *bk) {
     const int64_t S = bk->lay.nslots;
     layout::SlotHost h;
-    layout::slot_arrays(bk->lay, bk->a.data(), bk->b.data(), bk->d.data(), bk->dmax, bk->L, h);
+    layout::slot_arrays(bk->lay, bk->a.data(), bk->b.data(), bk->d.data(), bk->dmax, bk->L, h, false);
     HIPCHK(hipMemcpy(bk->a32, h.a32.data(), S * sizeof(float2), hipMemcpyHostToDevice));
     HIPCHK(hipMemcpy(bk->b32, h.b32.data(), S * sizeof(float2), hipMemcpyHostToDevice));
     HIPCHK(hipMemcpy(bk->xoff, h.xoff.data(), S * sizeof(int32_t), hipMemcpyHostToDevice));

@@ -368,14 +368,14 @@ int build_layout(int T, const int64_t *off, const int32_t *d, int fl, int wpg, i
 }
 
 void slot_arrays(const Layout &lay, const double *a, const double *b, const int32_t *d, int dmax, int L,
-                 SlotHost &o) {
+                 SlotHost &o, bool fp32_drift) {
     const size_t S = (size_t)lay.nslots;
     o.a32.assign(S, F2{0.f, 0.f});
     o.b32.assign(S, F2{0.f, 0.f});
     o.xoff.assign(S, 0);
     o.flags.assign(S, 0);
     o.aL.assign(S, D2{0.0, 0.0});
-    o.dL.assign(S, D2{0.0, 0.0});
+    o.dL.assign(fp32_drift ? S : 0, D2{0.0, 0.0});
     o.a64.assign(S, D2{0.0, 0.0});
     for (size_t s = 0; s < S; ++s) {
         const int32_t k = lay.slot_filter[s];
@@ -391,9 +391,11 @@ void slot_arrays(const Layout &lay, const double *a, const double *b, const int3
         o.xoff[s] = dmax - d[k];
         double pr, pi, qr, qi;
         cpow(ar, ai, L, pr, pi);
-        cpow((double)far, (double)fai, L, qr, qi);
         o.aL[s] = D2{pr, pi};
-        o.dL[s] = D2{pr - qr, pi - qi};
+        if (fp32_drift) {
+            cpow((double)far, (double)fai, L, qr, qi);
+            o.dL[s] = D2{pr - qr, pi - qi};
+        }
         o.a64[s] = D2{ar, ai};
         o.flags[s] = std::hypot(ar, ai) > 1.0 - 1e-5 ? 1 : 0;
     }

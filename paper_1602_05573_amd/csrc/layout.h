@@ -84,7 +84,7 @@ struct SlotHost {
     std::vector<F2> a32, b32;     // fl32(a), fl32(b)
     std::vector<int32_t> xoff;    // max_delay - d
     std::vector<int32_t> flags;   // bit 0: |a| > 1 - 1e-5
-    std::vector<D2> aL, dL, a64;  // a^L, a^L - fl32(a)^L, a (FP64)
+    std::vector<D2> aL, dL, a64;  // a^L, a^L - fl32(a)^L (only on request: the device forms its own), a (FP64)
 };
 
 // Rows of 16 lanes x fl filters that k filters need.
@@ -130,7 +130,7 @@ int build_layout(int T, const int64_t *off, const int32_t *d, int fl, int wpg, i
 // FP64 powers and FP32 roundings of every slot's coefficients (a, b complex128
 // interleaved [F], caller order).
 void slot_arrays(const Layout &lay, const double *a, const double *b, const int32_t *d, int dmax, int L,
-                 SlotHost &out);
+                 SlotHost &out, bool fp32_drift = true);
 // (re + i im)^e by binary powering in FP64.
 void cpow(double re, double im, long e, double &out_re, double &out_im);
 
