@@ -32,6 +32,8 @@ struct spiir_whitener {
 
 namespace {
 
+constexpr int64_t kMaxLaunch = (int64_t)1 << 33;   // samples per launch (a multiple of every frame)
+
 void wh_free(spiir_whitener *wh) {
     dfree(wh->wtab);
     dfree(wh->tw);
@@ -226,12 +228,14 @@ int spiir_whitener_process(spiir_whitener *wh, const float *x, int64_t n, float 
         }
         return SPIIR_OK;
     }
-    // One launch for the call, however long (262,144 samples in 4 pieces of 65,536 left most
-    // compute units without a frame). The stored halves still change places once per piece of
-    // max_block, so that a captured call of an even number of pieces leaves them where its
-    // replay takes them from.
-    HIPCHK(hops(x, n, out));
-    if ((n + wh->B - 1) / wh->B % 2 == 0) {
+    // One launch for the call (262,144 samples in 4 pieces of 65,536 left most compute
+    // units without a frame), up to the launch's limit of 2^32 threads, a quarter of a thread
+    // per sample. The stored halves still change places once per piece of max_block, so that a
+    // captured call of an even number of pieces leaves them where its replay takes them from.
+    int64_t launches = 0;
+    for (int64_t P = 0; P < n; P += kMaxLaunch, ++launches)
+        HIPCHK(hops(x + P, std::min<int64_t>(kMaxLaunch, n - P), out + P));
+    if (((n + wh->B - 1) / wh->B - launches) % 2 != 0) {
         const int c = wh->cur;
         HIPCHK(launch_wh_copy(wh->hist[c], wh->hist[c ^ 1], wh->H, wh->pend[c], wh->pend[c ^ 1], wh->H, st));
         wh->cur ^= 1;
