@@ -241,7 +241,7 @@ struct spiir_tape {
     int64_t n = 0;
     float *xwin = nullptr;
     std::shared_ptr<WindowPool> pool;   // outlives the bank while a tape holds it
-    size_t cap = 0;   // samples of xwin
+    size_t cap = 0;   // words of xwin
     int device = 0;
 };
 
@@ -729,12 +729,17 @@ int create_bank(spiir_bank **out, int32_t T, const int64_t *off, const double *a
 }
 
 
+// A strain window of so many samples: the samples, read-ahead padding, the marks.
+constexpr int64_t kWindowPad = 16;
+size_t window_words(int64_t samples) { return (size_t)(samples + kWindowPad) + window_marks(samples); }
+int32_t *marks_of(float *xwin, int64_t samples) { return reinterpret_cast<int32_t *>(xwin + samples + kWindowPad); }
+
 int ensure_xwin(spiir_bank *bk, int64_t need) {
     if (need <= bk->xwin_cap) return SPIIR_OK;
     HIPCHK(hipDeviceSynchronize());
     dfree(bk->xwin);
     bk->xwin_cap = 0;
-    HIPCHK(dalloc(&bk->xwin, (size_t)need + 16));  // one tile of read-ahead padding
+    HIPCHK(dalloc(&bk->xwin, window_words(need)));
     bk->xwin_cap = need;
     return SPIIR_OK;
 }
@@ -748,6 +753,7 @@ struct CallScratch {
     int nseg = 0;   // time segments per launch for this call (0: the bank's)
     float4 *seg_end = nullptr, *seg_start = nullptr;
     float *xwin = nullptr;
+    int32_t *xmark = nullptr;
     const Geometry *geo = nullptr;   // a plan with the window in LDS in place of the bank's
 };
 
@@ -759,18 +765,21 @@ int stream_call(spiir_bank *bk, const float *x, int64_t n, int mode, float *snr,
     DeviceGuard guard(bk->device);
     const float *hist = bk->hist[bk->hist_cur];
     float *xwin = bk->xwin;
+    int32_t *xmark = nullptr;
     const Geometry *geo = cs ? cs->geo : nullptr;
     const bool xlds = geo || bk->xlds;
     const size_t lds = geo ? geo->lds_run : bk->lds;
     if (!xlds) {
         if (cs) {
             xwin = cs->xwin;
+            xmark = cs->xmark;
         } else {
             int rc = ensure_xwin(bk, n + bk->dmax);
             if (rc) return rc;
             xwin = bk->xwin;
+            xmark = marks_of(xwin, n + bk->dmax);
         }
-        HIPCHK(launch_window_fill(xwin, hist, x, n, bk->dmax, st));
+        HIPCHK(launch_window_fill(xwin, xmark, hist, x, n, bk->dmax, st));
     }
     uint64_t *keys = cs ? cs->keys : bk->keys;
     const int64_t keys_ld = cs ? cs->keys_ld : bk->max_block;
@@ -791,6 +800,7 @@ int stream_call(spiir_bank *bk, const float *x, int64_t n, int mode, float *snr,
         a.x = x;
         a.hist = hist;
         a.xwin = xwin;
+        a.xmark = xmark;
         a.xbase = P;
         a.n = np;
         a.obase = P;
@@ -1201,7 +1211,7 @@ size_t plan_scratch(const spiir_bank *bk, int64_t n, int nseg, int64_t piece, un
         cs.seg_end = reinterpret_cast<float4 *>(take(seg_bytes));
         cs.seg_start = reinterpret_cast<float4 *>(take(seg_bytes));
     }
-    if (!bk->xlds && !cs.geo) cs.xwin = reinterpret_cast<float *>(take((size_t)(n + bk->dmax + 16) * sizeof(float)));
+    if (!bk->xlds && !cs.geo) cs.xwin = reinterpret_cast<float *>(take((size_t)(n + bk->dmax + kWindowPad) * sizeof(float)));
     return at;
 }
 
@@ -1238,6 +1248,9 @@ int spiir_trigger_max_noalloc(spiir_bank *bk, const float *x, int64_t n, float *
     const int rc = scratch_setup(bk->device, &scr);   // the address looked up when the bank was created
     if (rc) return rc;
     plan_scratch(bk, n, nseg, piece, scr, cs);
+    // the window's marks where the array has room left: a call that fits without them is taken
+    if (cs.xwin && need + window_marks(n + bk->dmax) * sizeof(int32_t) <= kScratchBytes)
+        cs.xmark = reinterpret_cast<int32_t *>(scr + need);
     return stream_call(bk, x, n, kModeKeys, nullptr, 0, mx, am, as_stream(stream), &cs);
 }
 
@@ -1258,7 +1271,7 @@ int spiir_trigger_max_per_template(spiir_bank *bk, const float *x, int64_t n, fl
     {
         int rc = ensure_xwin(bk, n + bk->dmax);
         if (rc) return rc;
-        HIPCHK(launch_window_fill(bk->xwin, hist, x, n, bk->dmax, st));
+        HIPCHK(launch_window_fill(bk->xwin, marks_of(bk->xwin, n + bk->dmax), hist, x, n, bk->dmax, st));
     }
     // Each template's launch fills the device by itself: its block is cut into
     // segments of one chunk (L samples), one workgroup per segment, chained in
@@ -1301,6 +1314,7 @@ int spiir_trigger_max_per_template(spiir_bank *bk, const float *x, int64_t n, fl
                 a.x = x;
                 a.hist = hist;
                 a.xwin = bk->xwin;
+                a.xmark = marks_of(bk->xwin, n + bk->dmax);
                 a.xbase = P;
                 a.n = np;
                 a.obase = P;
@@ -1343,6 +1357,7 @@ int spiir_forward_z(spiir_bank *bk, const float *x, int64_t n, float *z, spiir_t
     hipStream_t st = as_stream(stream);
     spiir_tape *tp = nullptr;
     float *xwin = nullptr;
+    int32_t *xmark = nullptr;
     if (tape_out || !bk->xlds) {
         tp = new (std::nothrow) spiir_tape();
         if (!tp) return fail(SPIIR_ENOMEM, "out of host memory");
@@ -1350,7 +1365,7 @@ int spiir_forward_z(spiir_bank *bk, const float *x, int64_t n, float *z, spiir_t
         tp->coeff_version = bk->coeff_version;
         tp->n = n;
         tp->pool = bk->windows;
-        const size_t need = (size_t)(n + bk->dmax) + 16;  // read-ahead padding
+        const size_t need = window_words(n + bk->dmax);
         tp->device = bk->device;
         tp->xwin = tp->pool->take(need, st, tp->cap);
         if (!tp->xwin) {
@@ -1368,7 +1383,8 @@ int spiir_forward_z(spiir_bank *bk, const float *x, int64_t n, float *z, spiir_t
             }
         }
         xwin = tp->xwin;
-        hipError_t le = launch_window_fill(xwin, nullptr, x, n, bk->dmax, st);
+        xmark = marks_of(xwin, n + bk->dmax);
+        hipError_t le = launch_window_fill(xwin, xmark, nullptr, x, n, bk->dmax, st);
         if (le != hipSuccess) {
             spiir_tape_destroy(tp);
             return fail(SPIIR_EHIP, "window fill: %s", hipGetErrorString(le));
@@ -1382,6 +1398,7 @@ int spiir_forward_z(spiir_bank *bk, const float *x, int64_t n, float *z, spiir_t
         a.x = x;
         a.hist = nullptr;
         a.xwin = xwin;
+        a.xmark = xmark;
         a.xbase = P;
         a.n = np;
         a.obase = P;

@@ -22,6 +22,8 @@
 #include <hip/hip_ext.h>
 
 #include <algorithm>
+#include <cfloat>
+#include <type_traits>
 
 #include "spiir_internal.h"
 
@@ -310,12 +312,17 @@ __device__ __forceinline__ void row_add(const RowReads &r, float2 *wsum, int Rp,
 // xs[i] = src[off + i] (0 if ZERO) for i in [i0, i1), by the whole workgroup:
 // a scalar head up to a 16-byte LDS boundary, then 16-byte global loads (4-byte
 // aligned) with four per thread in flight and 16-byte LDS stores, then a scalar
-// tail. Indices off + i are in range for every i in [i0, i1).
+// tail. Indices off + i are in range for every i in [i0, i1). Returns the
+// largest magnitude that the thread saw.
 template <bool ZERO>
-__device__ __forceinline__ void stage_range(float *xs, const float *src, int64_t off, int i0, int i1) {
+__device__ __forceinline__ float stage_range(float *xs, const float *src, int64_t off, int i0, int i1) {
     const int tid = threadIdx.x, nt = blockDim.x;
     const int ia = min(i1, (i0 + 3) & ~3);
-    for (int i = i0 + tid; i < ia; i += nt) xs[i] = ZERO ? 0.f : src[off + i];
+    float top = 0.f;
+    for (int i = i0 + tid; i < ia; i += nt) {
+        xs[i] = ZERO ? 0.f : src[off + i];
+        if (!ZERO) top = fmaxf(top, fabsf(xs[i]));
+    }
     const int nv = (i1 - ia) >> 2;
     for (int v0 = tid; v0 < nv; v0 += 4 * nt) {
         float4 q[4];
@@ -332,9 +339,17 @@ __device__ __forceinline__ void stage_range(float *xs, const float *src, int64_t
         for (int u = 0; u < 4; ++u) {
             const int v = v0 + u * nt;
             if (v < nv) *reinterpret_cast<float4 *>(xs + ia + 4 * v) = q[u];
+            if (!ZERO) {
+                top = fmaxf(fmaxf(top, fabsf(q[u].x)), fabsf(q[u].y));
+                top = fmaxf(fmaxf(top, fabsf(q[u].z)), fabsf(q[u].w));
+            }
         }
     }
-    for (int i = ia + 4 * nv + tid; i < i1; i += nt) xs[i] = ZERO ? 0.f : src[off + i];
+    for (int i = ia + 4 * nv + tid; i < i1; i += nt) {
+        xs[i] = ZERO ? 0.f : src[off + i];
+        if (!ZERO) top = fmaxf(top, fabsf(xs[i]));
+    }
+    return top;
 }
 
 // Template sum over its nr row sums of one step, in a fixed order.
@@ -482,9 +497,25 @@ __device__ __forceinline__ bool load_lane(Lane<FL> &s, const FwdArgs &p, int g, 
     return plain;
 }
 
+// An infinite sample makes S infinite in both parts, and the products v_j S are then NaN in
+// the steps of its block where y is still infinite: a workgroup whose window holds one
+// runs the plain recursion from that window on. Windows in LDS are looked over while they are
+// staged, those in global memory while they are filled (one mark per kMarkSamples). That
+// costs 6 us of the headline call's 450 (rows; the fused call is 5 us faster), nothing that
+// shows in the time-split calls, 1 us of 31 with the window in global memory. A vote on the
+// final states and a second run of the whole item cost 0.4 us per launch.
+template <int FL>
+__device__ __forceinline__ void to_plain(Lane<FL> &s, const FwdArgs &p, bool ract) {
+#pragma unroll
+    for (int f = 0; f < FL; ++f)
+        if (ract) s.a4[f] = p.s.a32[s.slot(f)];   // c[3] is b in both forms
+}
+
 // Stages xs[i] = x[m0 + i], i in [0, gw + nbs), m0 = first sample - glo - gw;
-// samples before x[0] come from the history. The caller syncs around it.
-__device__ __forceinline__ void stage_window(float *xs, const FwdArgs &p, int64_t xfirst, int glo, int gw, int nbs) {
+// samples before x[0] come from the history. Sets *inf if one of them is infinite.
+// The caller syncs around it.
+__device__ __forceinline__ void stage_window(float *xs, const FwdArgs &p, int64_t xfirst, int glo, int gw, int nbs,
+                                             int *inf) {
     const int cnt = gw + nbs;
     const int64_t m0 = xfirst - glo - gw;
     const int nneg = (int)min((int64_t)cnt, max((int64_t)0, -m0));
@@ -492,13 +523,28 @@ __device__ __forceinline__ void stage_window(float *xs, const FwdArgs &p, int64_
     // samples before the history (m < -max_delay) are read by no filter and
     // staged as zeros, so the history is only read at indices >= 0
     const int nz = (int)min((int64_t)nneg, max((int64_t)0, -(int64_t)p.dmax - m0));
+    float top = 0.f;
     if (p.hist) {
         stage_range<true>(xs, nullptr, 0, 0, nz);
-        stage_range<false>(xs, p.hist, p.dmax + m0, nz, nneg);
+        top = stage_range<false>(xs, p.hist, p.dmax + m0, nz, nneg);
     } else {
         stage_range<true>(xs, nullptr, 0, 0, nneg);
     }
-    stage_range<false>(xs, p.x, m0, nneg, cnt);
+    top = fmaxf(top, stage_range<false>(xs, p.x, m0, nneg, cnt));
+    if (top > FLT_MAX) *inf = 1;
+}
+
+// This lane's share of the same question for a window in global memory, from the marks
+// that its fill left (one per kMarkSamples): two loads that nothing waits for before the
+// coefficients are there, more only beyond 128 marks.
+__device__ __forceinline__ int window_marked(const FwdArgs &p, int64_t xfirst, int nbs) {
+    if (!p.xmark) return 0;
+    const int64_t m0 = xfirst / kMarkSamples + (threadIdx.x & 63), m1 = (xfirst + p.dmax + nbs - 1) / kMarkSamples;
+    const int a = p.xmark[min(m0, m1)], b = p.xmark[min(m0 + 64, m1)];
+    if (xfirst / kMarkSamples + 128 > m1) return a | b;
+    int more = 0;
+    for (int64_t m = m0 + 128; m <= m1; m += 64) more |= p.xmark[m];
+    return a | b | more;
 }
 
 __host__ __device__ __forceinline__ size_t window_bytes(int gw, int nb) {
@@ -556,8 +602,11 @@ __device__ void fwd_group(const FwdArgs &p, int g, unsigned char *smem, const Se
     if (MODE == kModeKeys)
         for (int i = tid; i < 2 * sb; i += W * 64) kmax[i] = 0ull;
 
+    __shared__ int inf;
+    if (tid == 0) inf = 0;
+    int marked = XLDS ? 0 : window_marked(p, p.xbase + sc.tb, (int)min((int64_t)p.nb, sc.tn));
     Lane<FL> s;
-    const bool plain = load_lane<FL>(s, p, g, wave, lane, ract, p.dmax - glo - gw, sc);
+    bool plain = load_lane<FL>(s, p, g, wave, lane, ract, p.dmax - glo - gw, sc);
     const int64_t n = sc.tn;
     const int64_t xbase = p.xbase + sc.tb;
 
@@ -599,44 +648,61 @@ __device__ void fwd_group(const FwdArgs &p, int g, unsigned char *smem, const Se
         if (MODE == kModeKeys && best != 0ull) atomicMax(&kmax[buf * sb + lane], best);
     };
 
-    for (int64_t s0 = 0; s0 < n; s0 += p.nb) {
-        const int nbs = (int)min((int64_t)p.nb, n - s0);
-        const float *xw;
-        __syncthreads();
-        if (XLDS) {
-            stage_window(xs, p, xbase + s0, glo, gw, nbs);
-            __syncthreads();
-            xw = xs;
-        } else {
-            xw = p.xwin + (xbase + s0);
-        }
-        if (wact && !plain) fill_ring<FL, true, !XLDS>(s, xv, xw, 0);
-
-        for (int b0 = 0; b0 < nbs; b0 += sb) {
-            const int bsteps = min(sb, nbs - b0);
-            if (wact) {
-                float2 *ws = wsum + buf * sb * Rp;
-                run_tiles<FL, true, !XLDS>(s, xv, xw, b0, b0 + bsteps, wt, lane, plain, [&](int t0, int steps) {
-                    if (t0 > b0) {
-                        row_add(rr, ws, Rp, wave, lane);
-                        ws += kFwdTile * Rp;
-                    }
-                    rr = row_reads(wt, lane);
-                    chunk_done += steps;
-                    if (chunk_done == p.L) {
-                        carry_correct<FL>(s, p.s, p.prec, plain, p.L, p.L);
-                        chunk_done = 0;
-                    }
-                });
-                row_add(rr, ws, Rp, wave, lane);
+    // Sub-blocks from launch sample `from` on, up to the first whose window holds an infinite
+    // sample; with COLD all of them, in the plain recursion, the first one's window being
+    // staged. Two instances: one loop for both cost the headline call 2.5 %.
+    auto sub_blocks = [&](auto cold, int64_t from) -> int64_t {
+        constexpr bool COLD = decltype(cold)::value;
+        for (int64_t s0 = from; s0 < n; s0 += p.nb) {
+            const int nbs = (int)min((int64_t)p.nb, n - s0);
+            const float *xw = XLDS ? xs : p.xwin + (xbase + s0);
+            if (!COLD || s0 > from) {
+                __syncthreads();
+                if (XLDS) {
+                    stage_window(xs, p, xbase + s0, glo, gw, nbs, &inf);
+                    __syncthreads();
+                } else if (s0 > 0) {
+                    marked = window_marked(p, xbase + s0, nbs);
+                }
             }
-            __syncthreads();
-            flush_keys(buf ^ 1);
-            emit(s0 + b0, bsteps);
-            pend_t = s0 + b0;
-            pend_steps = bsteps;
-            buf ^= 1;
+            // the same answer in every wave
+            if (!COLD && (XLDS ? __builtin_amdgcn_readfirstlane(inf) != 0 : __ballot(marked != 0) != 0)) return s0;
+            const bool pl = COLD || plain;
+            if (wact && !pl) fill_ring<FL, true, !XLDS>(s, xv, xw, 0);
+
+            for (int b0 = 0; b0 < nbs; b0 += sb) {
+                const int bsteps = min(sb, nbs - b0);
+                if (wact) {
+                    float2 *ws = wsum + buf * sb * Rp;
+                    run_tiles<FL, true, !XLDS>(s, xv, xw, b0, b0 + bsteps, wt, lane, pl, [&](int t0, int steps) {
+                        if (t0 > b0) {
+                            row_add(rr, ws, Rp, wave, lane);
+                            ws += kFwdTile * Rp;
+                        }
+                        rr = row_reads(wt, lane);
+                        chunk_done += steps;
+                        if (chunk_done == p.L) {
+                            carry_correct<FL>(s, p.s, p.prec, pl, p.L, p.L);
+                            chunk_done = 0;
+                        }
+                    });
+                    row_add(rr, ws, Rp, wave, lane);
+                }
+                __syncthreads();
+                flush_keys(buf ^ 1);
+                emit(s0 + b0, bsteps);
+                pend_t = s0 + b0;
+                pend_steps = bsteps;
+                buf ^= 1;
+            }
         }
+        return n;
+    };
+    const int64_t from = sub_blocks(std::false_type(), 0);
+    if (from < n) {
+        to_plain<FL>(s, p, ract);
+        plain = true;
+        sub_blocks(std::true_type(), from);
     }
     if (wact && chunk_done) carry_correct<FL>(s, p.s, p.prec, plain, chunk_done, p.L);
     if (MODE == kModeKeys) {
@@ -661,8 +727,11 @@ __device__ void state_group(const FwdArgs &p, int g, unsigned char *smem, const 
     const RowInfo ri = p.rows[(int64_t)g * 4 * p.wpg + wave * 4 + (lane >> 4)];
     const bool ract = ri.tpl >= 0 && (p.only_tpl < 0 || ri.tpl == p.only_tpl);
     const bool wact = __ballot(ract) != 0;
+    __shared__ int inf;
+    if (threadIdx.x == 0) inf = 0;
+    int marked = XLDS ? 0 : window_marked(p, p.xbase + sc.tb, (int)min((int64_t)p.nb, sc.tn));
     Lane<FL> s;
-    const bool plain = load_lane<FL>(s, p, g, wave, lane, ract, p.dmax - glo - gw, sc);
+    bool plain = load_lane<FL>(s, p, g, wave, lane, ract, p.dmax - glo - gw, sc);
     if (ract && st_copy) {
 #pragma unroll
         for (int f = 0; f < FL; ++f)
@@ -671,29 +740,42 @@ __device__ void state_group(const FwdArgs &p, int g, unsigned char *smem, const 
     const int64_t n = sc.tn, xbase = p.xbase + sc.tb;
     int chunk_done = 0;
     float xv[Ring<false, !XLDS>::value][FL];
-    for (int64_t s0 = 0; s0 < n; s0 += p.nb) {
-        const int nbs = (int)min((int64_t)p.nb, n - s0);
-        const float *xw;
-        if (XLDS) {
-            __syncthreads();
-            stage_window(xs, p, xbase + s0, glo, gw, nbs);
-            __syncthreads();
-            xw = xs;
-        } else {
-            xw = p.xwin + (xbase + s0);
-        }
-        if (!wact) continue;
-        if (!plain) fill_ring<FL, false, !XLDS>(s, xv, xw, 0);
-        for (int t0 = 0; t0 < nbs;) {   // whole stretches up to a chunk end
-            const int t1 = min(nbs, t0 + p.L - chunk_done);
-            run_tiles<FL, false, !XLDS>(s, xv, xw, t0, t1, nullptr, lane, plain, [](int, int) {});
-            chunk_done += t1 - t0;
-            t0 = t1;
-            if (chunk_done == p.L) {
-                carry_correct<FL>(s, p.s, p.prec, plain, p.L, p.L);
-                chunk_done = 0;
+    auto sub_blocks = [&](auto cold, int64_t from) -> int64_t {   // as in fwd_group
+        constexpr bool COLD = decltype(cold)::value;
+        for (int64_t s0 = from; s0 < n; s0 += p.nb) {
+            const int nbs = (int)min((int64_t)p.nb, n - s0);
+            const float *xw = XLDS ? xs : p.xwin + (xbase + s0);
+            if (!COLD || s0 > from) {
+                if (XLDS) {
+                    __syncthreads();
+                    stage_window(xs, p, xbase + s0, glo, gw, nbs, &inf);
+                    __syncthreads();
+                } else if (s0 > 0) {
+                    marked = window_marked(p, xbase + s0, nbs);
+                }
+            }
+            if (!COLD && (XLDS ? __builtin_amdgcn_readfirstlane(inf) != 0 : __ballot(marked != 0) != 0)) return s0;
+            const bool pl = COLD || plain;
+            if (!wact) continue;
+            if (!pl) fill_ring<FL, false, !XLDS>(s, xv, xw, 0);
+            for (int t0 = 0; t0 < nbs;) {   // whole stretches up to a chunk end
+                const int t1 = min(nbs, t0 + p.L - chunk_done);
+                run_tiles<FL, false, !XLDS>(s, xv, xw, t0, t1, nullptr, lane, pl, [](int, int) {});
+                chunk_done += t1 - t0;
+                t0 = t1;
+                if (chunk_done == p.L) {
+                    carry_correct<FL>(s, p.s, p.prec, pl, p.L, p.L);
+                    chunk_done = 0;
+                }
             }
         }
+        return n;
+    };
+    const int64_t from = sub_blocks(std::false_type(), 0);
+    if (from < n) {
+        to_plain<FL>(s, p, ract);
+        plain = true;
+        sub_blocks(std::true_type(), from);
     }
     if (wact && chunk_done) carry_correct<FL>(s, p.s, p.prec, plain, chunk_done, p.L);
     if (ract && sc.st_out) {
@@ -1161,11 +1243,22 @@ __global__ void hist_update_kernel(HistCopy hc) {
     if (i < hc.dmax) hist_copy_at(hc, i);
 }
 
-__global__ void window_fill_kernel(float *xwin, const float *hist, const float *x, int64_t n,
-                                   int dmax) {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n + dmax) return;
-    xwin[i] = i < dmax ? (hist ? hist[i] : 0.f) : x[i - dmax];
+// A block fills kMarkSamples samples and marks whether one of them is infinite.
+__global__ void __launch_bounds__(kMarkSamples) window_fill_kernel(float *xwin, int32_t *mark, const float *hist,
+                                                                   const float *x, int64_t n, int dmax) {
+    __shared__ int inf;
+    const int64_t i = (int64_t)blockIdx.x * kMarkSamples + threadIdx.x;
+    float v = 0.f;
+    if (i < n + dmax) {
+        v = i < dmax ? (hist ? hist[i] : 0.f) : x[i - dmax];
+        xwin[i] = v;
+    }
+    if (!mark) return;
+    if (threadIdx.x == 0) inf = 0;
+    __syncthreads();
+    if (fabsf(v) > FLT_MAX) inf = 1;
+    __syncthreads();
+    if (threadIdx.x == 0) mark[blockIdx.x] = inf;
 }
 
 __global__ void fill_zero_kernel(uint32_t *p, int64_t words) {
@@ -1872,10 +1965,10 @@ hipError_t launch_hist_update(const float *old_h, float *new_h, const float *x, 
     return hipGetLastError();
 }
 
-hipError_t launch_window_fill(float *xwin, const float *hist, const float *x, int64_t n, int dmax,
+hipError_t launch_window_fill(float *xwin, int32_t *mark, const float *hist, const float *x, int64_t n, int dmax,
                               hipStream_t st) {
     if (n + dmax <= 0) return hipSuccess;
-    hipLaunchKernelGGL(window_fill_kernel, dim3(nblocks(n + dmax, 256)), dim3(256), 0, st, xwin,
+    hipLaunchKernelGGL(window_fill_kernel, dim3(nblocks(n + dmax, kMarkSamples)), dim3(kMarkSamples), 0, st, xwin, mark,
                        hist, x, n, dmax);
     return hipGetLastError();
 }

@@ -40,6 +40,7 @@ struct FwdArgs {
     const float *x;       // samples; launch sample t is x[xbase + t]
     const float *hist;    // max_delay samples before x[0] (null: zeros); hist[dmax + m], m < 0
     const float *xwin;    // global-window mode: xwin[dmax + m] = sample m (m >= -dmax)
+    const int32_t *xmark; // its marks (launch_window_fill), or null
     int64_t xbase;
     int64_t n;            // samples in this launch
     int32_t dmax, L, nb, prec, wpg, only_tpl;
@@ -165,7 +166,10 @@ hipError_t launch_rows_argmax(const float *snr, int T, int64_t ld, int64_t n, fl
                               int32_t *am, hipStream_t stream);
 hipError_t launch_hist_update(const float *old_h, float *new_h, const float *x, int64_t n,
                               int dmax, hipStream_t stream);
-hipError_t launch_window_fill(float *xwin, const float *hist, const float *x, int64_t n,
+// mark (or null): one per kMarkSamples samples of xwin, whether one of them is infinite.
+constexpr int kMarkSamples = 1024;
+inline size_t window_marks(int64_t samples) { return (size_t)(samples / kMarkSamples + 1); }
+hipError_t launch_window_fill(float *xwin, int32_t *mark, const float *hist, const float *x, int64_t n,
                               int dmax, hipStream_t stream);
 int batch_occupancy(int fl, int wpg, size_t lds);
 hipError_t launch_fill_zero(void *p, size_t bytes, hipStream_t stream);
