@@ -104,11 +104,15 @@ typedef struct {
                                  takes 4 filters per lane, 8-wave workgroups and up to 16
                                  segments. */
     int32_t delay_band;       /* 0 = automatic (default): the strain window is staged in LDS
-                                 when it fits; else, with filters_per_lane,
-                                 waves_per_group and time_split 0 and max_block >= 2048, a
-                                 bank of more than 128 filters per compute unit takes bands
-                                 of 16384 if that costs at most a quarter more workgroups;
-                                 else the window is read from global memory. w >= 1 =
+                                 when it fits beside the workgroup's row sums, unless LDS
+                                 would cost another round of workgroups or leaves 1 or 2
+                                 filters per lane sums of 8 steps at a time; a window that
+                                 does not fit even a workgroup of one wave gives, with
+                                 filters_per_lane, waves_per_group and time_split 0 and
+                                 max_block >= 2048, a bank of more than 128 filters per
+                                 compute unit bands of 16384 if that costs at most a
+                                 quarter more workgroups; else the window is read from
+                                 global memory. w >= 1 =
                                  delay bands of width w: every workgroup holds filters with
                                  delays in one band [k*w, (k+1)*w) and stages only that
                                  band's window (w - 1 + sub-block samples, the sub-block at
@@ -189,8 +193,8 @@ int spiir_bank_set_coeffs(spiir_bank *bank, const double *a, const double *b);
  * library's extension; see spiir_forward_z).
  *   a_dev, b_dev  complex128 [F] (interleaved), caller's filter order, device
  * The slot values are formed by a kernel exactly as the host call forms them
- * (fl32 roundings, a^chunk_len and its FP32 drift in FP64, the FP64-carry
- * flag). The values are not checked: the caller keeps every |a_k| < 1 and
+ * (fl32 roundings, a^chunk_len in FP64 and its difference from what the FP32
+ * recursion multiplies a carried state by, the FP64-carry flag). The values are not checked: the caller keeps every |a_k| < 1 and
  * every value finite (the host call rejects others with EINVAL). Work already
  * enqueued on other streams that uses this bank must complete first (a bank
  * is used from one stream at a time). Tapes made before the call become stale
@@ -339,7 +343,8 @@ int spiir_backward(spiir_bank *bank, const spiir_tape *tape, const float *grad_z
 
 /* Frees a tape (after the work that uses it has completed: it waits for the
  * device). The bank keeps the strain windows of up to two freed tapes for its
- * next ones, until it and its last tape are destroyed. NULL is ignored. */
+ * next ones (the last two freed), until it and its last tape are destroyed or
+ * an allocation needs them. NULL is ignored. */
 int spiir_tape_destroy(spiir_tape *tape);
 
 /*

@@ -85,6 +85,14 @@ int check_bank_args(int32_t T, const int64_t *off, const double *a, const double
 
 }  // namespace
 
+// Whether st is captured (or cannot say): allocations are refused then.
+static bool capturing(hipStream_t st) {
+    hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(st, &cs) == hipSuccess && cs == hipStreamCaptureStatusNone) return false;
+    (void)hipGetLastError();
+    return true;
+}
+
 // Strain windows of closed tapes, kept for the next ones of the bank: at most two, the
 // last ones given back, freed with the bank or with its last tape, or when an
 // allocation fails. A window is given back after a wait for the device, as a free would
@@ -106,11 +114,7 @@ struct WindowPool {
     // A window of need samples or more, up to four times as many; not while the stream
     // is captured, where an allocation is refused.
     float *take(size_t need, hipStream_t st, size_t &cap) {
-        hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
-        if (hipStreamIsCapturing(st, &cs) != hipSuccess || cs != hipStreamCaptureStatusNone) {
-            (void)hipGetLastError();
-            return nullptr;
-        }
+        if (capturing(st)) return nullptr;
         std::lock_guard<std::mutex> lk(mu);
         for (size_t i = 0; i < idle.size(); ++i) {
             if (idle[i].second < need || idle[i].second / 4 > need) continue;
@@ -510,6 +514,11 @@ int create_bank(spiir_bank **out, int32_t T, const int64_t *off, const double *a
     max_block = std::max(L, (max_block / L) * L);
     // Delay bands: every workgroup takes filters of one band of delays and stages only that
     // band's window in LDS (an option, and the automatic choice below for large banks).
+    // A window counts as beyond LDS when a workgroup of one wave has no room for it. Delays that
+    // leave room beside one wave but not beside eight (31,408 to 39,471 with the default chunk)
+    // take neither bands nor 4 filters per lane for that reason: with delays of 33,000 and
+    // 4,096 samples that would take 200 x 400 filters from 350 to 215 us, but 1,024 x 125 from 379
+    // to 630 and, at 38,000, 300 x 150 from 217 to 412.
     const bool global_window = !plan_geometry(1, dmax, L, max_block, df.lds_cap).xlds;
     int band = 0;
     if (o.delay_band > 0) {
@@ -767,6 +776,8 @@ int stream_call(spiir_bank *bk, const float *x, int64_t n, int mode, float *snr,
     float *xwin = bk->xwin;
     int32_t *xmark = nullptr;
     const Geometry *geo = cs ? cs->geo : nullptr;
+    // a window kept in global memory for speed alone goes to LDS where it cannot be allocated
+    if (!cs && !bk->xlds && bk->lds_geo.xlds && n + bk->dmax > bk->xwin_cap && capturing(st)) geo = &bk->lds_geo;
     const bool xlds = geo || bk->xlds;
     const size_t lds = geo ? geo->lds_run : bk->lds;
     if (!xlds) {
@@ -1358,7 +1369,12 @@ int spiir_forward_z(spiir_bank *bk, const float *x, int64_t n, float *z, spiir_t
     spiir_tape *tp = nullptr;
     float *xwin = nullptr;
     int32_t *xmark = nullptr;
-    if (tape_out || !bk->xlds) {
+    // without a tape a window kept in global memory for speed alone goes to LDS: it would be
+    // allocated, waited for and freed in this call
+    const Geometry *geo = !tape_out && !bk->xlds && bk->lds_geo.xlds ? &bk->lds_geo : nullptr;
+    const bool xlds = geo || bk->xlds;
+    const size_t lds = geo ? geo->lds_run : bk->lds;
+    if (tape_out || !xlds) {
         tp = new (std::nothrow) spiir_tape();
         if (!tp) return fail(SPIIR_ENOMEM, "out of host memory");
         tp->bank = bk;
@@ -1394,6 +1410,10 @@ int spiir_forward_z(spiir_bank *bk, const float *x, int64_t n, float *z, spiir_t
     for (int64_t P = 0; P < n && e == hipSuccess; P += bk->max_block) {
         const int64_t np = std::min<int64_t>(bk->max_block, n - P);
         FwdArgs a = bk->base_args();
+        if (geo) {
+            a.nb = geo->nb;
+            a.sumb = geo->sumb;
+        }
         a.state = bk->zstate;
         a.x = x;
         a.hist = nullptr;
@@ -1411,9 +1431,9 @@ int spiir_forward_z(spiir_bank *bk, const float *x, int64_t n, float *z, spiir_t
         e = timer_next(bk, &ev);
         if (e != hipSuccess) break;
         if (nseg >= 2)
-            e = launch_forward_split(a, kModeZ, bk->lay.fl, bk->xlds, nseg, bk->lds, st, ev);
+            e = launch_forward_split(a, kModeZ, bk->lay.fl, xlds, nseg, lds, st, ev);
         else
-            e = launch_forward(a, kModeZ, bk->lay.fl, bk->xlds, bk->lay.groups, bk->lds, st, ev);
+            e = launch_forward(a, kModeZ, bk->lay.fl, xlds, bk->lay.groups, lds, st, ev);
         if (e == hipSuccess && bk->n_split)
             e = launch_combine_parts(bk->zpart, bk->max_block, bk->split_tpl, bk->split_off, bk->n_split, np, kModeZ,
                                      nullptr, a.z, a.ld, a.obase, st);

@@ -434,7 +434,7 @@ __device__ __forceinline__ float4 hi_lo(double2 c) {
 }
 
 // Up to this many segments every workgroup of the full pass composes its own
-// start state (at most 7 reads per slot); beyond it a launch of its own does.
+// start state (at most 15 reads per slot); beyond it a launch of its own does.
 // The launch costs about 6 us with its gaps: 21.7 -> 15.1 us per 512-sample
 // call of a 4 x 128-filter bank.
 constexpr int kChainInline = 16;
@@ -822,7 +822,8 @@ __global__ void __launch_bounds__(512) fwd_kernel(FwdArgs p) {
 // Every segment but the last is first run for its states alone (segment 0
 // from the carried state, the others from rest), seg_chain_kernel composes the
 // segments' true start states in FP64, and then every segment runs in full
-// from its true start. The state pass costs 3.2 VALU operations per update; the
+// from its true start. The state pass costs 4.4 VALU operations per update (3 of them the
+// recursion, the rest window reads, chunk ends and the start); the
 // other way round (every segment in full from rest, then the free response of
 // the true starts added to stored template sums) cost about 6.5 and wrote and
 // read the sums. 64 x 1,000 filters, 16,384 samples, 16 segments: state pass

@@ -67,6 +67,21 @@ def test_window_that_would_take_another_round():
         m, j = torch.empty(many, device="cuda"), torch.empty(many, dtype=torch.int32, device="cuda")
         bk.trigger_max_noalloc(big, out=(m, j))
         check_argmax(m[:n].cpu().numpy(), j[:n].cpu().numpy(), ref)
+    # a first call under capture has no window to allocate, nor has a forward without a tape
+    with SpiirBank.from_bank(bank, **opts) as bk:
+        snr = torch.empty((bank.n_templates, n), device="cuda")
+        side = torch.cuda.Stream()
+        side.wait_stream(torch.cuda.current_stream())
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph, stream=side):
+            bk.filter_block(xd, snr, stream=side)
+            z = bk.forward_z(xd, stream=side)
+        graph.replay()
+        torch.cuda.synchronize()
+        assert snr_err(snr.cpu().numpy(), ref)[0] <= SNR_TOL
+        z = (z[0] if isinstance(z, tuple) else z).cpu().numpy()
+        assert snr_err(z.real ** 2 + z.imag ** 2, ref)[0] <= SNR_TOL
+        del graph
     # a batch stages the window in LDS all the same
     banks = [SpiirBank.from_bank(bank, **opts) for _ in range(2)]
     bt = SpiirBatch(banks, [xd, xd[:1500].contiguous()], block_len=1024)
