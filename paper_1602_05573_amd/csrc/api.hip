@@ -579,7 +579,7 @@ int create_bank(spiir_bank **out, int32_t T, const int64_t *off, const double *a
     //     lane LDS is still faster (1,024 x 350 filters, 3 per lane: 533 and 690);
     //   * where shorter batches cost a round of workgroups: 1,024 x 125 filters (266 workgroups
     //     on 256 compute units, one each) with delays of 24,000 took 465 us with batches of
-    //     32 in LDS, 400 in one round; 2,048 x 57 filters (256 workgroups) 281 and 380.
+    //     32 in LDS, 345 in one round; 2,048 x 57 filters (256 workgroups) 281 and 380.
     auto best_window = [&](int w, int64_t groups, const Geometry &g) {
         if (band || !g.xlds || g.sumb == layout::kLongBatch) return g;
         const Geometry far = plan_global_geometry(w, L, max_block);
